@@ -24,159 +24,19 @@
 // blocks sharing a gathered B tile (or an A panel) run on the same XCD at the
 // same time and meet in its L2.
 //
-// Epilogues: the cloud epilogue scales fp8 columns, adds the bias, writes
-// fp32 partial logits and the tile's row maxima of |clamp(z)|; the fuse
-// epilogue dequantises the payload (eq. 13), writes fused logits on request
-// and the tile's per-row (value, position) argmax key.  The endpoint
-// projection with K a multiple of the K step (k_fuse_dma) computes the
-// transposed tile, so that a lane holds consecutive subset positions of one
-// row: four payload codes per LDS read and an argmax that stays in the lane.
-#include <atomic>
-#include <type_traits>
-
-#include "sph_internal.h"
+// Epilogue: scales fp8 columns, adds the bias, writes fp32 partial logits and
+// the tile's row maxima of |clamp(z)|.  (The endpoint projection has its own
+// kernel.)
+#include "mfma_tile.h"
 
 namespace sph {
-
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x16_t __attribute__((ext_vector_type(16)));
-typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-
-template <bool HI>
-__device__ __forceinline__ uint32_t e4m3x2_to_bf16x2_m(uint32_t x) {
-  return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(x, 1.0f, HI));
-}
-
-__device__ __forceinline__ unsigned long long argmax_key_m(float v, int pos) {
-  v = v + 0.0f;  // -0 -> +0
-  uint32_t u = __float_as_uint(v);
-  u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-  return ((unsigned long long)u << 32) | (unsigned long long)(0xFFFFFFFFu - (uint32_t)pos);
-}
-
-constexpr int kBK = 64;          // K elements per staged step
-constexpr int kLDK = kBK + 8;    // padded LDS row, bf16 elements (144 bytes)
-constexpr int kGM = 8;           // m-tiles grouped per n-tile in the tile order
-
-__device__ __forceinline__ void tile_of_block(int b, int m_tiles, int n_tiles, int& mt, int& nt) {
-  const int total = m_tiles * n_tiles;
-  const int full = total / 8 * 8;
-  const int tile = b < full ? (b % 8) * (full / 8) + b / 8 : b;
-  const int gm_max = m_tiles < kGM ? m_tiles : kGM;
-  const int group = gm_max * n_tiles;
-  const int g = tile / group;
-  const int first_m = g * gm_max;
-  const int gm = min(m_tiles - first_m, gm_max);
-  const int in = tile - g * group;
-  mt = first_m + in % gm;
-  nt = in / gm;
-}
-
-
-// Lane exchanges of the butterfly below, all VALU except the 4-lane step:
-// v_permlane16_swap exchanges the upper 16 lanes of each 32-lane half of one
-// register with the lower 16 of another, so the larger of its two results is,
-// in lanes l & 16 == 0, max(x[l], x[l ^ 16]) and otherwise max(y[l], y[l ^ 16]);
-// DPP row_ror:8 and quad permutations read lane l ^ 8, l ^ 2 and l ^ 1.
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);
-}
-template <int O>
-__device__ __forceinline__ uint32_t lane_xor_u32(uint32_t v) {
-  if constexpr (O == 8) return dpp_u32<0x128>(v);       // row_ror:8
-  else if constexpr (O == 2) return dpp_u32<0x4E>(v);   // quad_perm 2,3,0,1
-  else if constexpr (O == 1) return dpp_u32<0xB1>(v);   // quad_perm 1,0,3,2
-  else return (uint32_t)__shfl_xor((int)v, O, 64);
-}
-template <class T>
-__device__ __forceinline__ T vmax(T a, T b) { return a > b ? a : b; }
-
-// The 64-bit value of lane l ^ 32.
-// v of lane l ^ 32: a permlane32 swap trades lanes [32, 64) of its first
-// operand with lanes [0, 32) of its second, so with v in both a low lane
-// finds its partner's value in the second result, a high lane in the first
-__device__ __forceinline__ unsigned long long xor_lane_u64_32(unsigned long long v) {
-  const uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
-  const auto sl = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
-  const auto sh = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
-  const bool low = (threadIdx.x & 32) == 0;
-  return ((unsigned long long)(low ? sh[1] : sh[0]) << 32) | (low ? sl[1] : sl[0]);
-}
-
-// Values are float or 64-bit keys, moved as 32-bit words.
-template <class T, int O>
-__device__ __forceinline__ T xor_lane(T v) {
-  if constexpr (sizeof(T) == 8) {
-    const uint32_t lo = lane_xor_u32<O>((uint32_t)v), hi = lane_xor_u32<O>((uint32_t)(v >> 32));
-    return ((T)hi << 32) | lo;
-  } else {
-    return __uint_as_float(lane_xor_u32<O>(__float_as_uint(v)));
-  }
-}
-template <class T>
-__device__ __forceinline__ void swap16(T& x, T& y) {
-  if constexpr (sizeof(T) == 8) {
-    const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)y, false, false);
-    const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
-    x = ((T)hi[0] << 32) | lo[0];
-    y = ((T)hi[1] << 32) | lo[1];
-  } else {
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
-    x = __uint_as_float(r[0]);
-    y = __uint_as_float(r[1]);
-  }
-}
-
-template <int O, int CNT, int P, class T>
-__device__ __forceinline__ void half_wave_max_step(T (&v)[P], int lane) {
-  if constexpr (O >= 1) {
-    constexpr int H = CNT / 2;
-    const bool upper = (lane & O) != 0;
-#pragma unroll
-    for (int i = 0; i < H; ++i) {
-      if constexpr (O == 16) {
-        T x = v[i], y = v[i + H];
-        swap16(x, y);
-        v[i] = vmax(x, y);
-      } else {
-        const T t0 = vmax(v[i], xor_lane<T, O>(v[i]));
-        const T t1 = vmax(v[i + H], xor_lane<T, O>(v[i + H]));
-        v[i] = upper ? t1 : t0;
-      }
-    }
-    half_wave_max_step<O / 2, H, P>(v, lane);
-  }
-}
-
-// Transposing butterfly inside each 32-lane half of a wave: on entry lane l
-// holds P values; after log2(32) exchanges lane (l & 31) holds the max over
-// the half's 32 lanes of values (l & 31) * P/32 .. + P/32 - 1.
-template <int P, class T>
-__device__ __forceinline__ void half_wave_max_transpose(T (&v)[P], int lane) {
-  static_assert(P >= 32 && P % 32 == 0, "values per lane");
-  half_wave_max_step<16, P, P>(v, lane);
-}
 
 // Epilogue of a BM x BN tile held as acc[FM][FN] 32x32 fragments by the
 // WM x WN waves.  Row of accumulator r in fragment (i, j):
 // 8*(r/4) + 4*(lane/32) + r%4; column: lane % 32.
-// For the fuse epilogue the payload tile q[m0:m0+BM, n0:n0+BN] and the row
-// scales are first staged in LDS the main loop no longer needs (s_q: BM*BN
-// bytes, s_qs: BM payload scales, then BM factors of the dot products: the
-// hidden-state code scales, or 1) with coalesced loads, instead of one byte load per
-// accumulator.  The caller has passed a barrier after its last LDS read.
+// s_q: LDS the main loop no longer needs (BM*BN bytes; kEpiCloudQ only).  The
+// caller has passed a barrier after its last LDS read.
 // z of one accumulator: fp8 row scale, then the bias (eq. 12)
-// A pointer that is the same in every lane, made visibly uniform (scalar
-// registers) so that memory instructions can take it as their scalar base.
-__device__ __forceinline__ const uint8_t* scalar_ptr(const void* p) {
-  const uint64_t v = reinterpret_cast<uint64_t>(p);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return reinterpret_cast<const uint8_t*>(((uint64_t)hi << 32) | lo);
-}
-
 template <int WT>
 __device__ __forceinline__ float cloud_value(float dot, const MfmaArgs& a, int id) {
   float zv = dot;
@@ -187,64 +47,17 @@ __device__ __forceinline__ float cloud_value(float dot, const MfmaArgs& a, int i
 
 template <int BM, int BN, int WM, int WN, int WT, int EPI, int FM, int FN>
 __device__ __forceinline__ void tile_epilogue(f32x16_t (&acc)[FM][FN], const MfmaArgs& a,
-                                              const int32_t* s_ids, uint32_t* s_rmax,
-                                              unsigned long long* s_rkey, int m0, int n0,
-                                              int nt, int8_t* s_q, float* s_qs) {
+                                              const int32_t* s_ids, uint32_t* s_rmax, int m0,
+                                              int n0, int nt, int8_t* s_q) {
   constexpr int NT = 64 * WM * WN;
   constexpr int TM = BM / WM, TN = BN / WN;
   constexpr int P = (FM * 16 + 31) / 32 * 32;  // row values per lane, padded for the butterfly
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WN, wn = wave % WN;
   const int M = a.M, n = a.n;
-  if constexpr (EPI == kEpiFuse) {
-    // the payload tile: BN codes of a row are BN * qbits / 8 bytes starting
-    // at byte n0 * qbits / 8 of the row
-    const int qb = a.qbits;
-    const int TB = BN * qb / 8;  // tile bytes per row
-    const int64_t c0 = (int64_t)n0 * qb / 8;
-    const int64_t rowbytes = ((int64_t)n * qb + 7) / 8;
-    const bool vec = (a.qstride & 15) == 0 && (reinterpret_cast<uintptr_t>(a.q) & 15) == 0;
-    if (vec) {
-      // all of a thread's 16-byte chunks are loaded before any is stored
-      constexpr int PT = BM * (BN / 16) / NT;  // chunks per thread at 8 bits
-      static_assert(PT * NT == BM * (BN / 16), "payload tile / threads");
-      const int CPR = TB / 16;  // 16-byte chunks per tile row
-      u32x4_t v[PT];
+  float red[P];
 #pragma unroll
-      for (int t = 0; t < PT; ++t) {
-        const int c = tid + t * NT, r = c / CPR, k = c % CPR;
-        const int row = m0 + r;
-        const int64_t col = c0 + k * 16;
-        v[t] = (r < BM && row < M && col < rowbytes)
-                   ? *reinterpret_cast<const u32x4_t*>(a.q + (int64_t)row * a.qstride + col)
-                   : u32x4_t{0u, 0u, 0u, 0u};
-      }
-#pragma unroll
-      for (int t = 0; t < PT; ++t) {
-        const int c = tid + t * NT, r = c / CPR, k = c % CPR;
-        if (r < BM) *reinterpret_cast<u32x4_t*>(s_q + r * TB + k * 16) = v[t];
-      }
-    } else {
-      for (int c = tid; c < BM * TB; c += NT) {
-        const int r = c / TB, k = c % TB;
-        const int row = m0 + r;
-        const int64_t col = c0 + k;
-        s_q[c] = (row < M && col < rowbytes) ? (int8_t)a.q[(int64_t)row * a.qstride + col] : (int8_t)0;
-      }
-    }
-    // a tile lies in one block of positions (blocks are multiples of BN)
-    const int kb = a.qshift < 0 ? 0 : (n0 >> a.qshift);
-    for (int r = tid; r < BM; r += NT) {
-      s_qs[r] = m0 + r < M ? a.qscale[(int64_t)(m0 + r) * a.qnb + kb] : 0.0f;
-      s_qs[BM + r] = (a.hscale && m0 + r < M) ? a.hscale[m0 + r] : 1.0f;
-    }
-    __syncthreads();
-  }
-  constexpr bool kCloud = EPI != kEpiFuse;  // kEpiCloud or kEpiCloudQ
-  using V = typename std::conditional<kCloud, float, unsigned long long>::type;
-  V red[P];
-#pragma unroll
-  for (int t = FM * 16; t < P; ++t) red[t] = V(0);
+  for (int t = FM * 16; t < P; ++t) red[t] = 0.0f;
   auto fill = [&]() {
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
@@ -252,40 +65,17 @@ __device__ __forceinline__ void tile_epilogue(f32x16_t (&acc)[FM][FN], const Mfm
       for (int r = 0; r < 16; ++r) {
         const int lrow = wm * TM + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
         const int row = m0 + lrow;
-        V best = V(0);
-        // fuse: the lane's largest fused value of the row and its column (the
-        // first, so the lowest, of equal values); one key per row afterwards
-        float bv = 0.0f;
-        int bc = -1;
+        float best = 0.0f;
 #pragma unroll
         for (int j = 0; j < FN; ++j) {
           const int lcol = wn * TN + j * 32 + (lane & 31);
           const int col = n0 + lcol;
           if (row < M && col < n) {
-            const float dot = acc[i][j][r];
-            if constexpr (kCloud) {
-              const float zv = cloud_value<WT>(dot, a, s_ids[lcol]);
-              if (EPI == kEpiCloud || a.z) __builtin_nontemporal_store(zv, a.z + (int64_t)row * n + col);
-              best = fmaxf(best, fabsf(fminf(fmaxf(zv, -a.clip), a.clip)));
-            } else {
-              int code;
-              if (a.qbits == 8) {
-                code = s_q[lrow * BN + lcol];
-              } else {
-                const int byte = (uint8_t)s_q[lrow * (BN / 2) + (lcol >> 1)];
-                const int nib = (lcol & 1) ? (byte >> 4) : (byte & 15);
-                code = nib >= 8 ? nib - 16 : nib;
-              }
-              const float f = __builtin_fmaf((float)code, s_qs[lrow], dot * s_qs[BM + lrow]);
-              if (a.f) __builtin_nontemporal_store(f, a.f + (int64_t)row * n + col);
-              if (bc < 0 || f > bv) {
-                bv = f;
-                bc = col;
-              }
-            }
+            const float zv = cloud_value<WT>(acc[i][j][r], a, s_ids[lcol]);
+            if (EPI == kEpiCloud || a.z) __builtin_nontemporal_store(zv, a.z + (int64_t)row * n + col);
+            best = fmaxf(best, fabsf(fminf(fmaxf(zv, -a.clip), a.clip)));
           }
         }
-        if constexpr (!kCloud) best = bc >= 0 ? argmax_key_m(bv, bc) : 0ull;
         red[i * 16 + r] = best;
       }
     }
@@ -327,23 +117,21 @@ __device__ __forceinline__ void tile_epilogue(f32x16_t (&acc)[FM][FN], const Mfm
             __builtin_nontemporal_store(zv, (__attribute__((address_space(1))) float*)(rb + loff + j * 128));
           best = fmaxf(best, fminf(fabsf(zv), clip));
         }
-        red[i * 16 + r] = V(best);
+        red[i * 16 + r] = best;
       }
     }
   };
   bool done = false;
-  if constexpr (kCloud) {
-    if (m0 + BM <= M && n0 + BN <= n && n <= (1 << 27)) {
-      const bool st = EPI == kEpiCloud || a.z != nullptr;
-      if (a.bias) {
-        if (st) fill_full(std::true_type{}, std::true_type{});
-        else fill_full(std::true_type{}, std::false_type{});
-      } else {
-        if (st) fill_full(std::false_type{}, std::true_type{});
-        else fill_full(std::false_type{}, std::false_type{});
-      }
-      done = true;
+  if (m0 + BM <= M && n0 + BN <= n && n <= (1 << 27)) {
+    const bool st = EPI == kEpiCloud || a.z != nullptr;
+    if (a.bias) {
+      if (st) fill_full(std::true_type{}, std::true_type{});
+      else fill_full(std::true_type{}, std::false_type{});
+    } else {
+      if (st) fill_full(std::false_type{}, std::true_type{});
+      else fill_full(std::false_type{}, std::false_type{});
     }
+    done = true;
   }
   if (!done) fill();
   half_wave_max_transpose<P>(red, lane);
@@ -354,10 +142,7 @@ __device__ __forceinline__ void tile_epilogue(f32x16_t (&acc)[FM][FN], const Mfm
     if (idx >= FM * 16) continue;
     const int i = idx / 16, r = idx % 16;
     const int lrow = wm * TM + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-    if constexpr (kCloud)
-      atomicMax(&s_rmax[lrow], __float_as_uint(red[t]));
-    else
-      atomicMax(&s_rkey[lrow], red[t]);
+    atomicMax(&s_rmax[lrow], __float_as_uint(red[t]));
   }
   __syncthreads();
   if constexpr (EPI == kEpiCloudQ) {
@@ -431,11 +216,7 @@ __device__ __forceinline__ void tile_epilogue(f32x16_t (&acc)[FM][FN], const Mfm
   }
   for (int i = tid; i < BM; i += NT) {
     const int row = m0 + i;
-    if (row >= M) continue;
-    if constexpr (kCloud)
-      a.amax_part[(int64_t)row * kMaxBlocks + nt] = __uint_as_float(s_rmax[i]);
-    else
-      a.best_part[(int64_t)row * kMaxBlocks + nt] = s_rkey[i];
+    if (row < M) a.amax_part[(int64_t)row * kMaxBlocks + nt] = __uint_as_float(s_rmax[i]);
   }
 }
 
@@ -458,7 +239,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   uint16_t* Bs = As + 2 * BM * kLDK;                             // [2][BN][kLDK]
   int32_t* s_ids = reinterpret_cast<int32_t*>(Bs + 2 * BN * kLDK);
   uint32_t* s_rmax = reinterpret_cast<uint32_t*>(s_ids + BN);
-  unsigned long long* s_rkey = reinterpret_cast<unsigned long long*>(s_rmax + BM + (BM & 1));
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
@@ -468,10 +248,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   const int M = a.M, K = a.K, n = a.n;
 
   for (int i = tid; i < BN; i += NT) s_ids[i] = n0 + i < n ? a.ids[n0 + i] : -1;
-  for (int i = tid; i < BM; i += NT) {
-    s_rmax[i] = 0u;
-    s_rkey[i] = 0ull;
-  }
+  for (int i = tid; i < BM; i += NT) s_rmax[i] = 0u;
   __syncthreads();
 
   u32x4_t ra[A_CH], rb[B_CH];
@@ -564,8 +341,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     buf ^= 1;
   }
 
-  tile_epilogue<BM, BN, 2, 2, WT, EPI>(acc, a, s_ids, s_rmax, s_rkey, m0, n0, nt,
-                                 reinterpret_cast<int8_t*>(As), reinterpret_cast<float*>(Bs));
+  tile_epilogue<BM, BN, 2, 2, WT, EPI>(acc, a, s_ids, s_rmax, m0, n0, nt, reinterpret_cast<int8_t*>(As));
 }
 
 
@@ -582,39 +358,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 // Waves: WM x WN (wave tile (BM/WM) x (BN/WN)); 2 x 2 with one wave per SIMD,
 // or 2 x 4 for 320-row tiles (wave tile 160 x 64) with two waves per SIMD,
 // whose accumulators then live in the 256 registers each wave has.
-typedef __attribute__((address_space(3))) void lds_void_t;
-
-__device__ __forceinline__ int swz8(int row) { return (row & 7) ^ ((row >> 3) & 1); }
-
-// Copy addressing of the direct-to-LDS kernels.  With O32 every lane keeps
-// its row's byte offset (below 4 GiB) in a 32-bit register and the step's
-// base stays scalar: each copy is then the scalar-base + 32-bit-offset form
-// of global_load_lds with no address arithmetic of its own (the empty asm
-// keeps the compiler from folding the base into 64-bit lane addresses, which
-// costs a 64-bit add per copy and chains the copies through one register
-// pair).  Measured on dense_sub's cloud projection: 1106 -> 1033 us.
-
-template <bool O32>
-struct LaneAddr;
-template <>
-struct LaneAddr<true> {
-  uint32_t off;
-  __device__ __forceinline__ void set(const uint8_t*, int64_t o) { off = (uint32_t)o; }
-  // base: the step's scalar base (from scalar_ptr)
-  __device__ __forceinline__ void copy(const uint8_t* base, int64_t, lds_void_t* dst) {
-    asm volatile("" : "+v"(off));
-    __builtin_amdgcn_global_load_lds(base + off, dst, 16, 0, 0);
-  }
-};
-template <>
-struct LaneAddr<false> {
-  const uint8_t* p;
-  __device__ __forceinline__ void set(const uint8_t* base, int64_t o) { p = base + o; }
-  __device__ __forceinline__ void copy(const uint8_t*, int64_t step, lds_void_t* dst) {
-    __builtin_amdgcn_global_load_lds(p + step, dst, 16, 0, 0);
-  }
-};
-
 template <int BM, int BN, int WM, int WN, int EPI, bool O32>
 __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(WM * WN / 4, WM * WN / 4)))
 void k_mfma_dma(const MfmaArgs a) {
@@ -635,7 +378,6 @@ void k_mfma_dma(const MfmaArgs a) {
   uint16_t* Bs = As + 2 * BM * kBK;                       // [2][BN][64]
   int32_t* s_ids = reinterpret_cast<int32_t*>(Bs + 2 * BN * kBK);
   uint32_t* s_rmax = reinterpret_cast<uint32_t*>(s_ids + BN);
-  unsigned long long* s_rkey = reinterpret_cast<unsigned long long*>(s_rmax + BM + (BM & 1));
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int iw = wave < IW ? wave : 0;  // issuing slot (waves >= IW issue nothing)
@@ -646,10 +388,7 @@ void k_mfma_dma(const MfmaArgs a) {
   const int M = a.M, K = a.K, n = a.n;
   const int last_id = a.ids[min(n, n0 + BN) - 1];
   for (int i = tid; i < BN; i += NT) s_ids[i] = n0 + i < n ? a.ids[n0 + i] : last_id;
-  for (int i = tid; i < BM; i += NT) {
-    s_rmax[i] = 0u;
-    s_rkey[i] = 0ull;
-  }
+  for (int i = tid; i < BM; i += NT) s_rmax[i] = 0u;
   __syncthreads();
 
   // lane -> row (lane / 8) of its 8-row group and the logical chunk it fetches
@@ -725,8 +464,7 @@ void k_mfma_dma(const MfmaArgs a) {
     __syncthreads();
     stage ^= 1;
   }
-  tile_epilogue<BM, BN, WM, WN, 0, EPI>(acc, a, s_ids, s_rmax, s_rkey, m0, n0, nt,
-                                reinterpret_cast<int8_t*>(As), reinterpret_cast<float*>(Bs));
+  tile_epilogue<BM, BN, WM, WN, 0, EPI>(acc, a, s_ids, s_rmax, m0, n0, nt, reinterpret_cast<int8_t*>(As));
 #endif
 }
 
@@ -1109,7 +847,6 @@ void k_mfma_dma8(const MfmaArgs a) {
   uint8_t* Bs = reinterpret_cast<uint8_t*>(As + 2 * BM * kBK);   // [2][BN][64] fp8
   int32_t* s_ids = reinterpret_cast<int32_t*>(Bs + 2 * BN * kBK);
   uint32_t* s_rmax = reinterpret_cast<uint32_t*>(s_ids + BN);
-  unsigned long long* s_rkey = reinterpret_cast<unsigned long long*>(s_rmax + BM + (BM & 1));
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int iw = wave < IW ? wave : 0;  // issuing slot (waves >= IW issue nothing)
@@ -1120,10 +857,7 @@ void k_mfma_dma8(const MfmaArgs a) {
   const int M = a.M, K = a.K, n = a.n;
   const int last_id = a.ids[min(n, n0 + BN) - 1];
   for (int i = tid; i < BN; i += NT) s_ids[i] = n0 + i < n ? a.ids[n0 + i] : last_id;
-  for (int i = tid; i < BM; i += NT) {
-    s_rmax[i] = 0u;
-    s_rkey[i] = 0ull;
-  }
+  for (int i = tid; i < BM; i += NT) s_rmax[i] = 0u;
   __syncthreads();
 
   const uint8_t* hbase = reinterpret_cast<const uint8_t*>(a.h);
@@ -1265,355 +999,23 @@ void k_mfma_dma8(const MfmaArgs a) {
     __syncthreads();
     stage ^= 1;
   }
-  tile_epilogue<BM, BN, WM, WN, 1, EPI>(acc, a, s_ids, s_rmax, s_rkey, m0, n0, nt,
-                                reinterpret_cast<int8_t*>(As), reinterpret_cast<float*>(Bs));
-#endif
-}
-
-// Endpoint projection with its fuse epilogue (eqs. 11, 13-14), K a multiple
-// of the K step.  The block computes the transposed tile C^T[n][m] =
-// W[S_n] . h[m]: the weight rows are the MFMA's A operand and the rows of h
-// its B operand.  The weight rows of each 32-row group are staged in the
-// order that puts subset position 16*(l/32) + r of the group in accumulator
-// r of lane l: a lane holds 16 consecutive positions of row j*32 + l%32 (in
-// the wave's tile) per fragment.  Operands are otherwise staged exactly as
-// in k_mfma_dma.  A BM x 256 tile runs WNN x WMM waves (WNN along the
-// positions, WMM along the rows).
-//
-// Payload: the tile's codes (BM rows of 256 * qbits / 8 bytes) are staged
-// in LDS as 16-byte chunks, swizzled per row, so one 16-byte read gives a
-// lane its 16 8-bit codes (an 8-byte read its 16 4-bit codes) and the rows
-// a read touches spread over the banks.  With 8-bit codes on 16-byte
-// aligned rows the tile is copied global-to-LDS during the last K step into
-// the operand buffers that step does not read (rows [0, BM/2) into the idle
-// A buffer, the rest into the idle B buffer), where it lands while the last
-// MFMAs run; otherwise it is loaded after the main loop.
-//
-// Selection: f = fma(code, s, dot * hs) (the product only with hidden-state
-// scales), the lane's largest f, then the lowest of the lane's positions
-// holding it; the two lanes holding a row (l, l ^ 32) keep the larger
-// orderable key (value, then lowest position), and LDS atomics combine the
-// WNN waves sharing the row.  Against the row-major epilogue (one LDS byte
-// read per code and a 32-lane butterfly of 64-bit keys) the first form of
-// this kernel (four positions per register group, a 32-bit code read and a
-// running compare per value) ran dense_full's endpoint projection in 358 us
-// instead of 505, dense_sub in 85 instead of 114 and batched in 29 instead
-// of 47; the 16-position layout then took dense_sub to 81 us and batched to
-// 27, with identical keys throughout.  One wave per SIMD instead (the cloud
-// kernel's explicit schedule with 128 x 128 wave tiles, the payload copied in
-// place of the copies past the end) kept the keys identical but ran slower:
-// with 8 K steps a tile's prologue and epilogue weigh more than the LDS
-// traffic the larger wave tiles save (dense_full 379-396 against 350-364 us,
-// dense_sub 87 against 76).
-template <int BM, int WNN, int WMM>
-constexpr size_t fuse_dma_lds_bytes() {
-  return (size_t)2 * (BM + kMfmaBN) * kBK * 2 + (size_t)kMfmaBN * 4 + (size_t)2 * BM * 4 +
-         (size_t)BM * 8;
-}
-
-template <int BM, int WNN, int WMM, bool O32>
-__global__ __launch_bounds__(64 * WNN * WMM)
-__attribute__((amdgpu_waves_per_eu(WNN * WMM / 4, WNN * WMM / 4)))
-void k_fuse_dma(const MfmaArgs a) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  constexpr int BN = kMfmaBN, NT = 64 * WNN * WMM;
-  constexpr int FI = BN / WNN / 32, FJ = BM / WMM / 32;  // position / row fragments per wave
-  static_assert(FI * WNN * 32 == BN && FJ * WMM * 32 == BM, "wave grid");
-  constexpr int IW = 4;  // waves issuing the operand copies (one per SIMD)
-  constexpr int A_INS = BM / 8 / IW, B_INS = BN / 8 / IW;
-  static_assert(A_INS * 8 * IW == BM && B_INS * 8 * IW == BN, "copy instructions");
-  constexpr int STAGE_B = (BM + BN) * kBK * 2;  // bytes of one operand stage
-  constexpr bool kLastStep = BM * BN <= STAGE_B && BM <= BN;  // 8-bit tile fits in one stage
-  extern __shared__ __align__(16) uint8_t smem[];
-  uint16_t* As = reinterpret_cast<uint16_t*>(smem);                 // [2][BM][64]
-  uint16_t* Bs = As + 2 * BM * kBK;                                  // [2][BN][64]
-  int32_t* s_ids = reinterpret_cast<int32_t*>(smem + 2 * STAGE_B);
-  float* s_sc = reinterpret_cast<float*>(s_ids + BN);               // [2][BM]: scale, dot factor
-  unsigned long long* s_rkey = reinterpret_cast<unsigned long long*>(s_sc + 2 * BM);
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int iw = wave < IW ? wave : 0;
-  const int wn = wave % WNN, wm = wave / WNN;
-  int mt, nt;
-  tile_of_block(blockIdx.x, a.m_tiles, a.n_tiles, mt, nt);
-  const int m0 = mt * BM, n0 = nt * BN;
-  const int M = a.M, K = a.K, n = a.n;
-  const int last_id = a.ids[min(n, n0 + BN) - 1];
-  for (int i = tid; i < BN; i += NT) s_ids[i] = n0 + i < n ? a.ids[n0 + i] : last_id;
-  // a tile lies in one block of positions (blocks are multiples of BN)
-  const int kb = a.qshift < 0 ? 0 : (n0 >> a.qshift);
-  for (int i = tid; i < BM; i += NT) {
-    s_rkey[i] = 0ull;
-    s_sc[i] = m0 + i < M ? a.qscale[(int64_t)(m0 + i) * a.qnb + kb] : 0.0f;
-    s_sc[BM + i] = (a.hscale && m0 + i < M) ? a.hscale[m0 + i] : 1.0f;
-  }
-  __syncthreads();
-  const int lr = lane >> 3;
-  const uint8_t* hbase = reinterpret_cast<const uint8_t*>(a.h);
-  LaneAddr<O32> pa[A_INS], pb[B_INS];
-#pragma unroll
-  for (int i = 0; i < A_INS; ++i) {
-    const int r = (iw * A_INS + i) * 8 + lr;
-    const int lc = (lane & 7) ^ swz8(r);
-    pa[i].set(hbase, (int64_t)min(m0 + r, M - 1) * a.ldh * 2 + lc * 16);
-  }
-#pragma unroll
-  for (int i = 0; i < B_INS; ++i) {
-    const int r = (iw * B_INS + i) * 8 + lr;
-    const int lc = (lane & 7) ^ swz8(r);
-    // weight row r of a 32-row group holds subset position pr: MFMA row
-    // 8g + 4h + e (g = register group, h = lane / 32, e = element) gets
-    // position 16h + 4g + e, so a lane's 16 accumulators cover 16
-    // consecutive positions
-    const int pr = (r & ~31) | (((r >> 2) & 1) << 4) | (((r >> 3) & 3) << 2) | (r & 3);
-    pb[i].set(a.w, (int64_t)s_ids[pr] * a.ldw_bytes + lc * 16);
-  }
-  auto issue = [&](int k0, int stage) {
-    if (wave >= IW) return;
-    uint8_t* as = reinterpret_cast<uint8_t*>(As + stage * BM * kBK);
-    uint8_t* bs = reinterpret_cast<uint8_t*>(Bs + stage * BN * kBK);
-    const int64_t step = (int64_t)k0 * 2;
-    const uint8_t* ha = O32 ? scalar_ptr(hbase + step) : nullptr;
-    const uint8_t* wb = O32 ? scalar_ptr(a.w + step) : nullptr;
-#pragma unroll
-    for (int i = 0; i < A_INS; ++i) pa[i].copy(ha, step, (lds_void_t*)(as + (iw * A_INS + i) * 1024));
-#pragma unroll
-    for (int i = 0; i < B_INS; ++i) pb[i].copy(wb, step, (lds_void_t*)(bs + (iw * B_INS + i) * 1024));
-  };
-  const int qb = a.qbits;
-  const int TB = BN * qb / 8;  // code bytes of a tile row
-  const int CPR = TB / 16;     // 16-byte chunks of a tile row
-  const int64_t c0 = (int64_t)n0 * qb / 8;
-  const int64_t rowbytes = ((int64_t)n * qb + 7) / 8;
-  const bool vec_q = (a.qstride & 15) == 0 && (reinterpret_cast<uintptr_t>(a.q) & 15) == 0;
-  const bool dma_q = qb == 8 && vec_q;
-  // chunk swizzle of payload row r: 16 chunks of 8-bit codes, 8 of 4-bit
-  // codes (by r / 2, so that the 8-byte reads of 32 rows spread over the banks)
-  auto qswz = [&](int r) { return qb == 8 ? (r & 15) : ((r >> 1) & 7); };
-  // payload row r: staged in the last K step, rows [0, BM/2) in the idle
-  // stage's A buffer and [BM/2, BM) in its B buffer; staged after the
-  // loop, consecutive rows from the start of LDS
-  auto prow = [&](bool in_stage, int st, int r) -> uint8_t* {
-    if (!in_stage) return smem + r * TB;
-    return r < BM / 2 ? reinterpret_cast<uint8_t*>(As + st * BM * kBK) + r * TB
-                      : reinterpret_cast<uint8_t*>(Bs + st * BN * kBK) + (r - BM / 2) * TB;
-  };
-  // global-to-LDS copies of an 8-bit payload tile: a wave instruction fills
-  // 4 rows (1 KB, contiguous in either placement); rows past M read row
-  // M-1 and chunks past the row's end read the tile's first chunk (their
-  // positions are never selected)
-  auto stage_payload_dma = [&](bool in_stage, int st) {
-    for (int t = wave; t < BM / 4; t += WNN * WMM) {
-      const int r = t * 4 + (lane >> 4);
-      const int k = (lane & 15) ^ (r & 15);
-      const int64_t col = c0 + k * 16 < rowbytes ? c0 + k * 16 : c0;
-      __builtin_amdgcn_global_load_lds(a.q + (int64_t)min(m0 + r, M - 1) * a.qstride + col,
-                                       (lds_void_t*)prow(in_stage, st, t * 4), 16, 0, 0);
-    }
-  };
-
-  f32x16_t acc[FI][FJ];
-#pragma unroll
-  for (int i = 0; i < FI; ++i)
-#pragma unroll
-    for (int j = 0; j < FJ; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-
-  if (K > 0) {
-    issue(0, 0);
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-  }
-  int stage = 0;
-  bool staged = false;
-  for (int k0 = 0; k0 < K; k0 += kBK) {
-    if (k0 + kBK < K) {
-      issue(k0 + kBK, stage ^ 1);
-    } else if (kLastStep && dma_q) {
-      // the last step reads one stage; the payload tile goes to the other
-      stage_payload_dma(true, stage ^ 1);
-      staged = true;
-    }
-    const uint16_t* as = As + stage * BM * kBK;
-    const uint16_t* bs = Bs + stage * BN * kBK;
-#pragma unroll
-    for (int kk = 0; kk < kBK / 16; ++kk) {
-      bf16x8_t hf[FJ], wf[FI];
-      const int c = kk * 2 + (lane >> 5);
-#pragma unroll
-      for (int j = 0; j < FJ; ++j) {
-        const int row = wm * (BM / WMM) + j * 32 + (lane & 31);
-        hf[j] = *reinterpret_cast<const bf16x8_t*>(as + row * kBK + ((c ^ swz8(row)) << 3));
-      }
-#pragma unroll
-      for (int i = 0; i < FI; ++i) {
-        const int row = wn * (BN / WNN) + i * 32 + (lane & 31);
-        wf[i] = *reinterpret_cast<const bf16x8_t*>(bs + row * kBK + ((c ^ swz8(row)) << 3));
-      }
-#pragma unroll
-      for (int i = 0; i < FI; ++i)
-#pragma unroll
-        for (int j = 0; j < FJ; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[i], hf[j], acc[i][j], 0, 0, 0);
-    }
-    __builtin_amdgcn_s_waitcnt(0);  // this wave's copies (operands or payload) have landed
-    __syncthreads();
-    stage ^= 1;
-  }
-  // after the last step's toggle, `stage` names the buffer that step did not read
-  const int pst = stage;
-  if (!staged) {
-    if (dma_q) {
-      stage_payload_dma(false, 0);
-      __builtin_amdgcn_s_waitcnt(0);
-    } else if (vec_q) {
-      for (int c = tid; c < BM * CPR; c += NT) {
-        const int r = c / CPR, k = c % CPR;
-        const int64_t col = c0 + k * 16;
-        const u32x4_t v = (m0 + r < M && col < rowbytes)
-                              ? *reinterpret_cast<const u32x4_t*>(a.q + (int64_t)(m0 + r) * a.qstride + col)
-                              : u32x4_t{0u, 0u, 0u, 0u};
-        *reinterpret_cast<u32x4_t*>(prow(false, 0, r) + ((k ^ qswz(r)) << 4)) = v;
-      }
-    } else {
-      for (int c = tid; c < BM * TB; c += NT) {
-        const int r = c / TB, byte = c % TB, k = byte >> 4;
-        const int64_t col = c0 + byte;
-        prow(false, 0, r)[((k ^ qswz(r)) << 4) | (byte & 15)] =
-            (m0 + r < M && col < rowbytes) ? a.q[(int64_t)(m0 + r) * a.qstride + col] : (uint8_t)0;
-      }
-    }
-    __syncthreads();
-  }
-  // lane l of fragment (i, j) holds positions i*32 + 16*(l/32) + r of row
-  // j*32 + l%32 in its 16 accumulators r: one 16-byte (8-bit) or 8-byte
-  // (4-bit) LDS read gives the lane its codes; the lane's largest fused
-  // value, then the lowest of its positions holding it
-  const bool hq = a.hscale != nullptr;
-  const int hh = lane >> 5;
-  auto run = [&](auto edge, auto hidden) {
-    constexpr bool kEdge = decltype(edge)::value;  // bounds checks and the fused output
-    constexpr bool kHq = decltype(hidden)::value;  // rows carry hidden-state scales
-#pragma unroll
-    for (int j = 0; j < FJ; ++j) {
-      const int ml = wm * (BM / WMM) + j * 32 + (lane & 31);
-      const float sc = s_sc[ml];
-      const uint8_t* qrow = prow(staged, pst, ml);
-      u32x4_t cq[FI];
-#pragma unroll
-      for (int i = 0; i < FI; ++i) {
-        const int nl0 = wn * (BN / WNN) + i * 32 + 16 * hh;
-        if (qb == 8) {
-          cq[i] = *reinterpret_cast<const u32x4_t*>(qrow + (((nl0 >> 4) ^ (ml & 15)) << 4));
-        } else {
-          const int bo = nl0 >> 1;
-          const uint2 h2 = *reinterpret_cast<const uint2*>(qrow + ((((bo >> 4) ^ ((ml >> 1) & 7)) << 4) | (bo & 15)));
-#pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            const uint32_t h = ((g < 2 ? h2.x : h2.y) >> (16 * (g & 1))) & 0xFFFFu;
-            uint32_t c4 = (h & 0xFu) | ((h & 0xF0u) << 4) | ((h & 0xF00u) << 8) | ((h & 0xF000u) << 12);
-            c4 |= (c4 & 0x08080808u) * 0x1Eu;  // a nibble's sign bit fills bits 4..7 of its byte
-            cq[i][g] = c4;
-          }
-        }
-      }
-      if constexpr (kHq) {
-        const float hsc = s_sc[BM + ml];
-#pragma unroll
-        for (int i = 0; i < FI; ++i)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) acc[i][j][r] *= hsc;
-      }
-      float bv = -__builtin_inff();
-#pragma unroll
-      for (int i = 0; i < FI; ++i) {
-        const int nl0 = wn * (BN / WNN) + i * 32 + 16 * hh;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int code = (int)(int8_t)(cq[i][r >> 2] >> (8 * (r & 3)));
-          acc[i][j][r] = __builtin_fmaf((float)code, sc, acc[i][j][r]);
-        }
-        if constexpr (kEdge) {
-          if (a.f) {
-            // lanes l and l + 32 trade halves so that each holds positions
-            // 8q + 4*(l/32) + [0, 4) in registers 4*ro(q), ro = 0, 2, 1, 3:
-            // each store instruction then covers 32 contiguous bytes of a row
-            float x[16];
-#pragma unroll
-            for (int r = 0; r < 16; ++r) x[r] = acc[i][j][r];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-#pragma unroll
-              for (int b = 0; b < 16; b += 8) {
-                const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[b + e]),
-                                                                 __float_as_uint(x[b + 4 + e]), false, false);
-                x[b + e] = __uint_as_float(sw[0]);
-                x[b + 4 + e] = __uint_as_float(sw[1]);
-              }
-            }
-            const int m = m0 + ml;
-            if (m < M) {
-              const int nlb = wn * (BN / WNN) + i * 32 + 4 * hh;
-              float* dst = a.f + (int64_t)m * n + n0 + nlb;
-#pragma unroll
-              for (int q = 0; q < 4; ++q) {
-                const int ro = ((q & 1) << 3) | ((q >> 1) << 2);
-                if (n0 + nlb + 8 * q + 4 <= n && (reinterpret_cast<uintptr_t>(dst + 8 * q) & 15) == 0) {
-                  *reinterpret_cast<float4*>(dst + 8 * q) = make_float4(x[ro], x[ro + 1], x[ro + 2], x[ro + 3]);
-                } else {
-#pragma unroll
-                  for (int e = 0; e < 4; ++e)
-                    if (n0 + nlb + 8 * q + e < n) dst[8 * q + e] = x[ro + e];
-                }
-              }
-            }
-          }
-#pragma unroll
-          for (int r = 0; r < 16; ++r)
-            if (n0 + nl0 + r >= n) acc[i][j][r] = -__builtin_inff();
-        }
-#pragma unroll
-        for (int r = 0; r < 16; ++r) bv = fmaxf(bv, acc[i][j][r]);
-      }
-      int bn = 0;
-#pragma unroll
-      for (int t = FI * 16 - 1; t >= 0; --t) bn = acc[t >> 4][j][t & 15] == bv ? t : bn;
-      const int pos = wn * (BN / WNN) + (bn >> 4) * 32 + 16 * hh + (bn & 15);
-      unsigned long long key = bv > -__builtin_inff() ? argmax_key_m(bv, n0 + pos) : 0ull;
-      const unsigned long long other = xor_lane_u64_32(key);
-      key = key > other ? key : other;
-      if (lane < 32) atomicMax(&s_rkey[ml], key);
-    }
-  };
-  if (a.f || m0 + BM > M || n0 + BN > n) {
-    if (hq) run(std::true_type{}, std::true_type{});
-    else run(std::true_type{}, std::false_type{});
-  } else {
-    if (hq) run(std::false_type{}, std::true_type{});
-    else run(std::false_type{}, std::false_type{});
-  }
-  __syncthreads();
-  for (int i = tid; i < BM; i += NT)
-    if (m0 + i < M) a.best_part[(int64_t)(m0 + i) * kMaxBlocks + nt] = s_rkey[i];
+  tile_epilogue<BM, BN, WM, WN, 1, EPI>(acc, a, s_ids, s_rmax, m0, n0, nt, reinterpret_cast<int8_t*>(As));
 #endif
 }
 
 template <int BM, int BN>
 constexpr size_t mfma_lds_bytes() {
-  return (size_t)2 * (BM + BN) * kLDK * 2 + (size_t)BN * 4 + (size_t)(BM + 1) * 4 + 8 +
-         (size_t)BM * 8;
+  return (size_t)2 * (BM + BN) * kLDK * 2 + (size_t)BN * 4 + (size_t)BM * 4;
 }
 
 template <int BM, int BN>
 constexpr size_t mfma_dma_lds_bytes() {
-  return (size_t)2 * (BM + BN) * kBK * 2 + (size_t)BN * 4 + (size_t)(BM + 1) * 4 + 8 +
-         (size_t)BM * 8;
+  return (size_t)2 * (BM + BN) * kBK * 2 + (size_t)BN * 4 + (size_t)BM * 4;
 }
 
 template <int BM, int BN>
 constexpr size_t mfma_dma8_lds_bytes() {
-  return (size_t)2 * (BM * 2 + BN) * kBK + (size_t)BN * 4 + (size_t)(BM + 1) * 4 + 8 +
-         (size_t)BM * 8;
+  return (size_t)2 * (BM * 2 + BN) * kBK + (size_t)BN * 4 + (size_t)BM * 4;
 }
 
 // Waves of a cloud row tile (the direct-to-LDS kernels).  256- and 320-row
@@ -1630,27 +1032,6 @@ struct WaveGrid {
   static constexpr int WN = BM == 32 ? 4 : kEight ? 4 : 2;
 };
 
-// The dynamic-LDS limit of a kernel is raised once per device (a host call,
-// kept out of every launch so that launches can be captured in a graph).
-// `done` is one instantiation's mask of devices already set.
-static hipError_t set_lds_limit_once(std::atomic<uint64_t>& done, const void* kern, size_t bytes) {
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  const uint64_t bit = dev < 64 ? (uint64_t(1) << dev) : 0;
-  if (bit && (done.load(std::memory_order_acquire) & bit)) return hipSuccess;
-  e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-  if (e == hipSuccess && bit) done.fetch_or(bit, std::memory_order_release);
-  return e;
-}
-
-// 32-bit copy offsets (LaneAddr<true>) when every row the copies address
-// lies below 4 GiB of its operand's base.
-static bool copy_offsets_fit(const MfmaArgs& a) {
-  constexpr int64_t kLim = 0xFFFFFFFFll;
-  return a.w_rows > 0 && (int64_t)a.M * a.ldh * 2 <= kLim && a.w_rows * a.ldw_bytes <= kLim;
-}
-
 template <int BM, int BN, int WT, int EPI>
 static hipError_t launch_tile(MfmaArgs a, hipStream_t s) {
   static std::atomic<uint64_t> lds_set_dma{0}, lds_set_dma64{0}, lds_set_reg{0};
@@ -1659,21 +1040,7 @@ static hipError_t launch_tile(MfmaArgs a, hipStream_t s) {
   a.n_tiles = (a.n + BN - 1) / BN;
   if (a.n_tiles > kMaxBlocks) return hipErrorInvalidValue;
   const bool o32 = copy_offsets_fit(a);
-  if constexpr (EPI == kEpiFuse) {
-    if (a.K % kBK == 0) {
-      // transposed tiles: waves along the positions x waves along the rows
-      constexpr int WNN = BM == 256 ? 2 : BM == 320 ? 4 : BM == 128 ? 2 : 4;
-      constexpr int WMM = BM == 256 ? 4 : BM == 320 ? 2 : BM == 128 ? 2 : 1;
-      auto kf = o32 ? k_fuse_dma<BM, WNN, WMM, true> : k_fuse_dma<BM, WNN, WMM, false>;
-      constexpr size_t lds_f = fuse_dma_lds_bytes<BM, WNN, WMM>();
-      static std::atomic<uint64_t> lds_set_fuse{0}, lds_set_fuse64{0};
-      hipError_t e = set_lds_limit_once(o32 ? lds_set_fuse : lds_set_fuse64,
-                                        reinterpret_cast<const void*>(kf), lds_f);
-      if (e != hipSuccess) return e;
-      launch_kernel(kf, dim3(a.m_tiles * a.n_tiles), dim3(64 * WNN * WMM), lds_f, s, a);
-      return hipGetLastError();
-    }
-  } else if (a.K % kBK == 0) {
+  if (a.K % kBK == 0) {
     if constexpr (BM == 256 && WT == 0 && EPI == kEpiCloud) {
       // (the one-wave kernels copy their first steps unconditionally: they
       // need at least 6 or 2 steps; a zero-width slice takes the kernel below)
@@ -1770,8 +1137,7 @@ hipError_t launch_mfma(int epi, int wtype, const MfmaArgs& a, hipStream_t s) {
   if (epi == kEpiCloudQ) return wtype == 0 ? launch_bm_q<0>(a, s) : launch_bm_q<1>(a, s);
   if (epi == kEpiCloud)
     return wtype == 0 ? launch_bm<0, kEpiCloud>(a, s) : launch_bm<1, kEpiCloud>(a, s);
-  if (wtype != 0) return hipErrorInvalidValue;
-  return launch_bm<0, kEpiFuse>(a, s);
+  return wtype == 0 ? launch_fuse_mfma(a, s) : hipErrorInvalidValue;
 }
 
 }  // namespace sph

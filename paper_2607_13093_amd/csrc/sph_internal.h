@@ -123,6 +123,7 @@ int gemv_rows_per_iter(int lpr);
 int gemv_lpr(int K, int wtype);
 
 hipError_t launch_mfma(int epi, int wtype, const MfmaArgs& a, hipStream_t s);
+hipError_t launch_fuse_mfma(const MfmaArgs& a, hipStream_t s);
 // true where the cloud projection can quantise blocks of 256 positions in its epilogue
 bool mfma_quantises_in_epilogue(int M, int K);
 int mfma_n_tiles(int n);
