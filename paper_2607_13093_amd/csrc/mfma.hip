@@ -355,9 +355,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 // M and subset positions past n read a valid row (row M-1 / the last id):
 // they only feed outputs that are never written.  On the decode-sized dense
 // shape this loop ran 1.2x faster than register staging.
-// Waves: WM x WN (wave tile (BM/WM) x (BN/WN)); 2 x 2 with one wave per SIMD,
-// or 2 x 4 for 320-row tiles (wave tile 160 x 64) with two waves per SIMD,
-// whose accumulators then live in the 256 registers each wave has.
+// Waves: WM x WN (wave tile (BM/WM) x (BN/WN)), two per SIMD, whose
+// accumulators live in the 256 registers each wave has.
 template <int BM, int BN, int WM, int WN, int EPI, bool O32>
 __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(WM * WN / 4, WM * WN / 4)))
 void k_mfma_dma(const MfmaArgs a) {
@@ -365,12 +364,12 @@ void k_mfma_dma(const MfmaArgs a) {
   constexpr int NT = 64 * WM * WN;
   constexpr int TM = BM / WM, TN = BN / WN;
   constexpr int FM = TM / 32, FN = TN / 32;
-  // With two waves per SIMD only the first wave of each SIMD issues the
+  // Only the first wave of each SIMD issues the
   // copies (all of them): a copy instruction can hold its wave at issue
   // until the load path accepts it, and the SIMD's other wave keeps the
   // matrix pipe busy meanwhile.  Measured on the dense 2048-row shape: 3-5%
   // faster than all 8 waves issuing an eighth of the copies each.
-  constexpr int IW = WM * WN >= 8 ? WM * WN / 2 : WM * WN;
+  constexpr int IW = WM * WN / 2;
   constexpr int A_INS = BM / 8 / IW, B_INS = BN / 8 / IW;  // copy instructions per issuing wave per step
   static_assert(A_INS * 8 * IW == BM && B_INS * 8 * IW == BN, "tile rows / issuing waves");
   extern __shared__ __align__(16) uint8_t smem[];
@@ -822,13 +821,9 @@ void k_mfma_w1(const MfmaArgs a) {
 // the 32 rows a fragment read touches spread over the LDS banks.  Each lane
 // reads its 8 codes of a fragment (ds_read_b64) and widens them to bf16
 // (exact) in registers right before the MFMA; the per-row scale is applied
-// in the epilogue.  With one wave per SIMD all fragments of a step are read
-// before the next step's loads are issued (the compiler would otherwise make
-// the reads wait for those loads), and scheduling barriers keep the loads
-// ahead of the MFMAs.  With two waves per SIMD (320-row tiles) those
-// fragments would not fit next to the accumulators: the loads go out first,
-// each sub-step reads its own fragments, and the SIMD's other wave covers
-// the wait.
+// in the epilogue.  The step's codes are read first, then the next stage's
+// loads go out and each sub-step reads its own fragments of h; the SIMD's
+// other wave covers the wait.
 __device__ __forceinline__ int swz4(int row) { return (row >> 2) & 3; }
 
 template <int BM, int BN, int WM, int WN, int EPI, bool O32>
@@ -838,8 +833,7 @@ void k_mfma_dma8(const MfmaArgs a) {
   constexpr int NT = 64 * WM * WN;
   constexpr int TM = BM / WM, TN = BN / WN;
   constexpr int FM = TM / 32, FN = TN / 32;
-  // as in k_mfma_dma: with two waves per SIMD one of them issues the copies
-  constexpr int IW = WM * WN >= 8 ? WM * WN / 2 : WM * WN;
+  constexpr int IW = WM * WN / 2;  // as in k_mfma_dma
   constexpr int A_INS = BM / 8 / IW, B_INS = BN / 16 / IW;  // copy instructions per issuing wave per step
   static_assert(A_INS * 8 * IW == BM && B_INS * 16 * IW == BN, "tile rows / issuing waves");
   extern __shared__ __align__(16) uint8_t smem[];
@@ -904,98 +898,48 @@ void k_mfma_dma8(const MfmaArgs a) {
   for (int k0 = 0; k0 < K; k0 += kBK) {
     const uint16_t* as = As + stage * BM * kBK;
     const uint8_t* bs = Bs + stage * BN * kBK;
-    if constexpr (WM * WN > 4) {
-      // Two waves per SIMD: a step's fragments for all four sub-steps do not
-      // fit in registers next to the accumulators, so the next stage's loads
-      // go out first and each sub-step reads its own fragments (the other
-      // wave of the SIMD covers any wait on the loads).
-      // The step's fp8 codes (8 bytes per fragment and sub-step, 16 VGPRs)
-      // are read before the next stage's copies go out.  The compiler makes
-      // an LDS read behind pending copies wait for them where it cannot
-      // tell the two apart, and it did so for these 8-byte reads: placed
-      // after the copies, they held the issuing wave of each SIMD until its
-      // copies had landed, every step (sample_fp8 cloud 438 against 365 us).
-      uint2 qb[kBK / 16][FN];
+    // The step's fp8 codes (8 bytes per fragment and sub-step, 16 VGPRs)
+    // are read before the next stage's copies go out.  The compiler makes
+    // an LDS read behind pending copies wait for them where it cannot
+    // tell the two apart, and it did so for these 8-byte reads: placed
+    // after the copies, they held the issuing wave of each SIMD until its
+    // copies had landed, every step (sample_fp8 cloud 438 against 365 us).
+    uint2 qb[kBK / 16][FN];
 #pragma unroll
-      for (int kk = 0; kk < kBK / 16; ++kk)
-#pragma unroll
-        for (int j = 0; j < FN; ++j) {
-          const int row = wn * TN + j * 32 + (lane & 31);
-          qb[kk][j] = *reinterpret_cast<const uint2*>(bs + row * kBK + ((kk ^ swz4(row)) << 4) + 8 * (lane >> 5));
-        }
-      if (k0 + kBK < K) issue(k0 + kBK, stage ^ 1);
-#pragma unroll
-      for (int kk = 0; kk < kBK / 16; ++kk) {
-        const int c = kk * 2 + (lane >> 5);
-        bf16x8_t af[FM], bfr[FN];
-#pragma unroll
-        for (int i = 0; i < FM; ++i) {
-          const int row = wm * TM + i * 32 + (lane & 31);
-          af[i] = *reinterpret_cast<const bf16x8_t*>(as + row * kBK + ((c ^ swz8(row)) << 3));
-        }
-#pragma unroll
-        for (int j = 0; j < FN; ++j) {
-          const uint2 q = qb[kk][j];
-          u32x4_t w;
-          w.x = e4m3x2_to_bf16x2_m<false>(q.x);
-          w.y = e4m3x2_to_bf16x2_m<true>(q.x);
-          w.z = e4m3x2_to_bf16x2_m<false>(q.y);
-          w.w = e4m3x2_to_bf16x2_m<true>(q.y);
-          bfr[j] = __builtin_bit_cast(bf16x8_t, w);
-        }
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-          for (int j = 0; j < FN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      __builtin_amdgcn_s_waitcnt(0);
-      __syncthreads();
-      stage ^= 1;
-      continue;
-    }
-    bf16x8_t af[kBK / 16][FM];
-    uint2 bq[kBK / 16][FN];
-#pragma unroll
-    for (int kk = 0; kk < kBK / 16; ++kk) {
-      const int c = kk * 2 + (lane >> 5);
-#pragma unroll
-      for (int i = 0; i < FM; ++i) {
-        const int row = wm * TM + i * 32 + (lane & 31);
-        af[kk][i] = *reinterpret_cast<const bf16x8_t*>(as + row * kBK + ((c ^ swz8(row)) << 3));
-      }
+    for (int kk = 0; kk < kBK / 16; ++kk)
 #pragma unroll
       for (int j = 0; j < FN; ++j) {
         const int row = wn * TN + j * 32 + (lane & 31);
-        bq[kk][j] = *reinterpret_cast<const uint2*>(bs + row * kBK + ((kk ^ swz4(row)) << 4) +
-                                                    8 * (lane >> 5));
+        qb[kk][j] = *reinterpret_cast<const uint2*>(bs + row * kBK + ((kk ^ swz4(row)) << 4) + 8 * (lane >> 5));
       }
-    }
-    // the other stage was last read in the previous step, finished by all
-    // waves before that step's closing barrier
     if (k0 + kBK < K) issue(k0 + kBK, stage ^ 1);
-    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int kk = 0; kk < kBK / 16; ++kk) {
-      bf16x8_t bfr[FN];
+      const int c = kk * 2 + (lane >> 5);
+      bf16x8_t af[FM], bfr[FN];
+#pragma unroll
+      for (int i = 0; i < FM; ++i) {
+        const int row = wm * TM + i * 32 + (lane & 31);
+        af[i] = *reinterpret_cast<const bf16x8_t*>(as + row * kBK + ((c ^ swz8(row)) << 3));
+      }
 #pragma unroll
       for (int j = 0; j < FN; ++j) {
+        const uint2 q = qb[kk][j];
         u32x4_t w;
-        w.x = e4m3x2_to_bf16x2_m<false>(bq[kk][j].x);
-        w.y = e4m3x2_to_bf16x2_m<true>(bq[kk][j].x);
-        w.z = e4m3x2_to_bf16x2_m<false>(bq[kk][j].y);
-        w.w = e4m3x2_to_bf16x2_m<true>(bq[kk][j].y);
+        w.x = e4m3x2_to_bf16x2_m<false>(q.x);
+        w.y = e4m3x2_to_bf16x2_m<true>(q.x);
+        w.z = e4m3x2_to_bf16x2_m<false>(q.y);
+        w.w = e4m3x2_to_bf16x2_m<true>(q.y);
         bfr[j] = __builtin_bit_cast(bf16x8_t, w);
       }
 #pragma unroll
       for (int i = 0; i < FM; ++i)
 #pragma unroll
         for (int j = 0; j < FN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[kk][i], bfr[j], acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
     }
     __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(0);  // this wave's loads for the next stage have landed
+    __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     stage ^= 1;
   }
@@ -1018,24 +962,17 @@ constexpr size_t mfma_dma8_lds_bytes() {
   return (size_t)2 * (BM * 2 + BN) * kBK + (size_t)BN * 4 + (size_t)BM * 4;
 }
 
-// Waves of a cloud row tile (the direct-to-LDS kernels).  256- and 320-row
-// tiles use 8 waves, two per SIMD, so one wave's MFMAs run while the other
-// waits at a barrier or on LDS: 2 x 4 (wave tiles 128 x 64 / 160 x 64),
-// whose long K loop ran 6% faster so than with 4 x 2; on the dense 2048-row
-// shape 8 waves ran 9% faster than 4 (wave tile 128 x 128).  128-row tiles
-// use 2 x 2, 32-row tiles (9 to 32 rows) 1 x 4 waves of 32 x 64.  (The
-// endpoint projection's transposed tiles choose their own grid.)
-template <int BM, int EPI>
-struct WaveGrid {
-  static constexpr bool kEight = BM >= 256;
-  static constexpr int WM = BM == 32 ? 1 : kEight ? 2 : 2;
-  static constexpr int WN = BM == 32 ? 4 : kEight ? 4 : 2;
-};
+// Waves of a cloud row tile (the direct-to-LDS kernels): 8, two per SIMD, so
+// one wave's MFMAs run while the other waits at a barrier or on LDS: 2 x 4
+// (wave tiles 128 x 64 / 160 x 64), whose long K loop ran 6% faster so than
+// with 4 x 2; on the dense 2048-row shape 8 waves ran 9% faster than 4 (wave
+// tile 128 x 128).
+constexpr int kTileWM = 2, kTileWN = 4;
 
 template <int BM, int BN, int WT, int EPI>
 static hipError_t launch_tile(MfmaArgs a, hipStream_t s) {
   static std::atomic<uint64_t> lds_set_dma{0}, lds_set_dma64{0}, lds_set_reg{0};
-  constexpr int WM = WaveGrid<BM, EPI>::WM, WN = WaveGrid<BM, EPI>::WN, NT = 64 * WM * WN;
+  constexpr int WM = kTileWM, WN = kTileWN, NT = 64 * WM * WN;
   a.m_tiles = (a.M + BM - 1) / BM;
   a.n_tiles = (a.n + BN - 1) / BN;
   if (a.n_tiles > kMaxBlocks) return hipErrorInvalidValue;
@@ -1072,9 +1009,8 @@ static hipError_t launch_tile(MfmaArgs a, hipStream_t s) {
     return hipGetLastError();
   }
   // K not a multiple of the K step: the register-staged kernel (2 x 2 waves),
-  // which exists for 128- and 256-row tiles (the tile rule picks neither 32
-  // nor 320 then)
-  if constexpr (BM >= 128 && BM <= 256 && EPI != kEpiCloudQ) {
+  // which exists for 256-row tiles (the tile rule picks no other then)
+  if constexpr (BM == 256 && EPI != kEpiCloudQ) {
     auto kern = k_mfma<BM, BN, WT, EPI>;
     constexpr size_t lds = mfma_lds_bytes<BM, BN>();
     hipError_t e = set_lds_limit_once(lds_set_reg, reinterpret_cast<const void*>(kern), lds);
@@ -1085,18 +1021,12 @@ static hipError_t launch_tile(MfmaArgs a, hipStream_t s) {
   return hipErrorInvalidValue;
 }
 
-// Row tile for M rows: 32 up to 32 rows (K a multiple of the K step), 128
-// up to 128 rows, else whichever of 256 and 320
+// Row tile for M rows (more than kStreamMaxRows): whichever of 256 and 320
 // pads M less (320-row tiles need K a multiple of the K step).  Measured on
 // the batched shape (M = 320, 60000 ids): 320-row tiles, one per 256 ids,
-// 156 us against 265 us for 256-row and 289 us for 128-row tiles; M = 640
-// with fp8 weights: 460 us against 537 us for 256-row tiles.
+// 156 us against 265 us for 256-row tiles; M = 640 with fp8 weights: 460 us
+// against 537 us for 256-row tiles.
 static int mfma_bm(int M, int K) {
-  // up to 32 rows the projection streams its weights like the skinny kernel
-  // does; a 32-row tile wastes at most 23 of 32 rows of MFMA work instead of
-  // 119 of 128, and two blocks fit on a CU
-  if (M <= 32 && K % kBK == 0) return 32;
-  if (M <= 128) return 128;
   const int pad256 = (M + 255) / 256 * 256 - M;
   const int pad320 = (M + 319) / 320 * 320 - M;
   return (K % kBK == 0 && pad320 < pad256) ? 320 : 256;
@@ -1106,17 +1036,13 @@ int mfma_n_tiles(int n) { return (n + kMfmaBN - 1) / kMfmaBN; }
 
 template <int WT, int EPI>
 static hipError_t launch_bm(const MfmaArgs& a, hipStream_t s) {
-  switch (mfma_bm(a.M, a.K)) {
-    case 32: return launch_tile<32, kMfmaBN, WT, EPI>(a, s);
-    case 320: return launch_tile<320, kMfmaBN, WT, EPI>(a, s);
-    case 256: return launch_tile<256, kMfmaBN, WT, EPI>(a, s);
-    default: return launch_tile<128, kMfmaBN, WT, EPI>(a, s);
-  }
+  return mfma_bm(a.M, a.K) == 320 ? launch_tile<320, kMfmaBN, WT, EPI>(a, s)
+                                  : launch_tile<256, kMfmaBN, WT, EPI>(a, s);
 }
 
 // Cloud projection with the block quantiser in the epilogue, for the row
-// tiles whose accumulators and row maxima fit in the registers together
-// (32, 128, 256 rows, K a multiple of the K step).  Where the tile rule picks
+// tile whose accumulators and row maxima fit in the registers together
+// (256 rows, K a multiple of the K step).  Where the tile rule picks
 // 320 rows the separate quantiser is used: on 640 rows, 256-row tiles with
 // the fused quantiser ran 598 us against 428 + 43 us.
 bool mfma_quantises_in_epilogue(int M, int K) {
@@ -1126,11 +1052,7 @@ bool mfma_quantises_in_epilogue(int M, int K) {
 template <int WT>
 static hipError_t launch_bm_q(const MfmaArgs& a, hipStream_t s) {
   if (!mfma_quantises_in_epilogue(a.M, a.K)) return hipErrorInvalidValue;
-  switch (mfma_bm(a.M, a.K)) {
-    case 32: return launch_tile<32, kMfmaBN, WT, kEpiCloudQ>(a, s);
-    case 128: return launch_tile<128, kMfmaBN, WT, kEpiCloudQ>(a, s);
-    default: return launch_tile<256, kMfmaBN, WT, kEpiCloudQ>(a, s);
-  }
+  return launch_tile<256, kMfmaBN, WT, kEpiCloudQ>(a, s);
 }
 
 hipError_t launch_mfma(int epi, int wtype, const MfmaArgs& a, hipStream_t s) {

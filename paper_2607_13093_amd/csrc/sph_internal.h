@@ -90,6 +90,7 @@ struct MfmaArgs {
   const int32_t* ids;     // subset ids [n]
   int n;
   int m_tiles, n_tiles;   // set by the launcher
+  int width;              // streaming kernel: positions per block, set by its launcher
   // cloud epilogue
   const float* bias;
   float clip;
@@ -123,6 +124,15 @@ int gemv_rows_per_iter(int lpr);
 int gemv_lpr(int K, int wtype);
 
 hipError_t launch_mfma(int epi, int wtype, const MfmaArgs& a, hipStream_t s);
+constexpr int kCUs = 256;             // compute units of an MI355X
+// Most rows of the streaming cloud projection (stream.hip).  Measured on 60000
+// x 3840 columns: 192 rows 124 us against 142 for a 256-row tile, 256 rows 149
+// against 135.
+constexpr int kStreamMaxRows = 192;
+// Few rows (kGemvMaxRows < M <= kStreamMaxRows): row maxima go to slot j /
+// stream_width(n), one per block of positions.
+int stream_width(int n);
+hipError_t launch_stream(int wtype, MfmaArgs a, hipStream_t s);
 hipError_t launch_fuse_mfma(const MfmaArgs& a, hipStream_t s);
 // true where the cloud projection can quantise blocks of 256 positions in its epilogue
 bool mfma_quantises_in_epilogue(int M, int K);
