@@ -8,26 +8,34 @@
 // so every pass is a short rolled loop of coalesced loads.
 //
 // Weights.  e = exp((f - fmax) / tau) in fp64 by the table-driven method of
-// Tang (ACM TOMS 15(2), 1989): with t = (f - fmax) / (tau ln2) * 64,
-// N = rint(t), r = t - N (|r| <= 1/2), e = 2^(N>>6) * 2^((N&63)/64) * 2^(r/64),
-// the middle factor from a 64-entry table and 2^(r/64) a degree-5 Taylor
+// Tang (ACM TOMS 15(2), 1989): with t = (f - fmax) / (tau ln2) * 256,
+// N = rint(t), r = t - N (|r| <= 1/2), e = 2^(N>>8) * 2^((N&255)/256) * 2^(r/256),
+// the middle factor from a 256-entry table and 2^(r/256) a degree-4 Taylor
 // polynomial (truncation below 4e-17).  Every use of a weight evaluates the
 // same operations with contraction off, so it is bit-identical wherever it is
 // recomputed.
 //
-// Exact masses.  Each weight e in [0, 1] becomes E = floor(e * 2^56), held as
-// E = a * 2^28 + b (a <= 2^28, b < 2^28).  Masses are exact integer sums of
-// E, so the nucleus cut and the inverse CDF are exact for these weights,
-// independent of summation order, and the kernel is deterministic.  E misses
-// e * 2^56 by less than one unit.
+// Exact masses.  Each weight e in [0, 1] becomes E = floor(e * 2^56), the
+// mantissa of the product of table entry and polynomial shifted into place.
+// Masses are exact integer sums of E (added as E = a * 2^28 + b), so the
+// nucleus cut and the inverse CDF are exact for these weights, independent of
+// summation order, and the kernel is deterministic.  E misses e * 2^56 by less
+// than one unit.
 //
-//   1. An approximate histogram (fp32 weights, integer atomics) over 4096
-//      value buckets of y = (fmax - f)/tau in [0, 40) (the last bucket also
-//      takes y >= 40, whose elements each weigh below 5e-18) locates the
-//      bucket where the running mass reaches top_p * Z: bucket order is value
-//      order, so the nucleus -- the shortest prefix of (p desc, id asc)
-//      reaching the target -- ends there.  The window is that bucket, widened
-//      by a neighbour where the estimate lies near a bucket edge.
+// The passes are bound by their instructions (65536 positions keep a CU's
+// SIMDs busy for 31 us in the exact pass, of 61): N comes out of the low word
+// of t + 1.5 * 2^52 and E out of shifts, as rounding to and converting from
+// fp64 are quarter-rate operations, and pass 1 counts elements instead of
+// adding weights.
+//
+//   1. A histogram of element counts over 4096 value buckets of
+//      y = (fmax - f)/tau in [0, 24) (the last bucket also takes y >= 24, whose
+//      elements each weigh below 4e-11); a bucket's mass is estimated as its
+//      count times the weight of its middle.  Bucket order is value order, so
+//      the nucleus -- the shortest prefix of (p desc, id asc) reaching
+//      top_p * Z -- ends in or near the bucket where the running estimate
+//      reaches top_p of the total.  The window is that bucket, widened by a
+//      neighbour where the estimate lies near a bucket edge.
 //   2. One exact pass: Z; the masses of the buckets below the window, per
 //      segment (runs of consecutive positions, at most 512 per row); the
 //      window's elements into an LDS list.  An exact histogram of the list
@@ -35,9 +43,9 @@
 //      one wave ranks its few elements by (key desc, position asc) to find
 //      the element completing the nucleus.  The nucleus is
 //      {key > T} + {key == T, position <= cut}.
-//      Should the window miss the cut or overflow the list, an exact
-//      histogram over groups of 4 buckets picks the group and the pass is
-//      redone on it; a sub-bucket holding more than 64 elements is ranked by
+//      Should the window miss the cut (the estimate is only an estimate) or
+//      overflow the list, an exact histogram over groups of 4 buckets picks the
+//      group and the pass is redone on it; a sub-bucket holding more than 64 elements is ranked by
 //      a bitonic sort of the list, and a group with more than 1024 elements
 //      goes through an exact radix select over its keys (8 bits per pass),
 //      the cut among elements tied at the threshold key being the c-th in id
@@ -62,19 +70,19 @@ constexpr int kMaxSeg = kSThreads; // segments per row, one per thread in scans
 constexpr int kMaxCand = 1024;     // window elements held in LDS
 constexpr int kChunk = 256;        // positions per wave iteration
 constexpr int kSegChunks = 4;      // chunks per segment at least
-constexpr float kYSpan = 40.0f;
+constexpr float kYSpan = 24.0f;
 static_assert(kMaxCand == 2 * kSThreads, "two list entries per thread");
 static_assert(kCoarse == 2 * kSThreads, "two coarse buckets per thread");
 static_assert(kMaxSub == kSThreads, "one sub-bucket per thread");
 
-// 2^(r/64) = exp(r * ln2/64): Taylor coefficients (ln2/64)^k / k!
+// 2^(r/256) = exp(r * ln2/256): Taylor coefficients (ln2/256)^k / k!
+constexpr int kTab = 256;
 constexpr double kLn2 = 0.6931471805599453;
-constexpr double kL64 = kLn2 / 64.0;
-constexpr double kC1 = kL64;
-constexpr double kC2 = kL64 * kL64 / 2.0;
-constexpr double kC3 = kL64 * kL64 * kL64 / 6.0;
-constexpr double kC4 = kL64 * kL64 * kL64 * kL64 / 24.0;
-constexpr double kC5 = kL64 * kL64 * kL64 * kL64 * kL64 / 120.0;
+constexpr double kL = kLn2 / kTab;
+constexpr double kC1 = kL;
+constexpr double kC2 = kL * kL / 2.0;
+constexpr double kC3 = kL * kL * kL / 6.0;
+constexpr double kC4 = kL * kL * kL * kL / 24.0;
 
 // ---------------------------------------------------------------------------
 // 128-bit unsigned integers (masses in units of 2^-56)
@@ -136,17 +144,10 @@ __device__ U128 u128_ceil(double x) {
   return U128{0ull, m << (sh - 64)};
 }
 
-// E = floor(w * 2^56) = a * 2^28 + b from w28 = w * 2^28 in [0, 2^28].
-struct Fix {
-  uint32_t a, b;
-};
-
-__device__ __forceinline__ Fix fix_of(double w28) {
-#pragma clang fp contract(off)
-  const uint32_t a = (uint32_t)w28;
-  const double r = w28 - (double)a;  // exact, in [0, 1)
-  return Fix{a, (uint32_t)(r * 268435456.0)};
-}
+// The two parts that a sum of E is accumulated in.
+constexpr uint32_t kLow28 = (1u << 28) - 1u;
+__device__ __forceinline__ uint64_t part_a(uint64_t e) { return e >> 28; }
+__device__ __forceinline__ uint64_t part_b(uint64_t e) { return (uint32_t)e & kLow28; }
 
 // ---------------------------------------------------------------------------
 
@@ -161,17 +162,21 @@ __device__ __forceinline__ float from_orderable(uint32_t k) {
   return __uint_as_float(u);
 }
 
-// exp((x - fmax) / tau) * 2^28 with kk = 64 / (tau ln2), c0 = -fmax * kk.
-__device__ __forceinline__ double weight28(float x, double kk, double c0,
-                                           const double* __restrict__ tab) {
+// floor(exp((x - fmax) / tau) * 2^56) with kk = kTab / (tau ln2), c0 = -fmax * kk.
+__device__ __forceinline__ uint64_t weight56(float x, double kk, double c0,
+                                             const double* __restrict__ tab) {
 #pragma clang fp contract(off)
   double t = fma((double)x, kk, c0);
-  t = fmin(fmax(t, -90000.0), 0.0);  // 2^(-90000/64) is zero in fp64; x <= fmax
-  const double nn = rint(t);
-  const double r = t - nn;  // exact, |r| <= 1/2
-  const double p = fma(r, fma(r, fma(r, fma(r, fma(r, kC5, kC4), kC3), kC2), kC1), 1.0);
-  const int j = (int)nn;
-  return ldexp(tab[j & 63] * p, (j >> 6) + 28);
+  t = fmin(fmax(t, -58.0 * kTab), 0.0);  // below 2^-57 the result is 0; x <= fmax
+  const double s = t + 0x1.8p52;         // rint(t) in the low word
+  const int j = (int)(uint32_t)__double_as_longlong(s);
+  const double r = t - (s - 0x1.8p52);   // exact, |r| <= 1/2
+  const double p = fma(r, fma(r, fma(r, fma(r, kC4, kC3), kC2), kC1), 1.0);
+  // in [0.998, 1.998): exponent 0 or -1
+  const uint64_t q = (uint64_t)__double_as_longlong(tab[j & (kTab - 1)] * p);
+  const int e = (int)(q >> 52) - 1023 + (j >> 8);  // of the weight, in [-59, 0]
+  const uint64_t m = (q & 0xFFFFFFFFFFFFFull) | 0x10000000000000ull;  // weight = m * 2^(e - 52)
+  return (m << 4) >> (-e);
 }
 
 // (fmax - x) * kb with kb = kBuckets / (kYSpan tau): bucket units, >= 0.
@@ -217,24 +222,6 @@ __device__ uint32_t philox_x0(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3
 // ---------------------------------------------------------------------------
 // wave and block primitives (fixed order)
 
-__device__ __forceinline__ uint64_t shfl_up_u64(uint64_t x, int o) {
-  const uint32_t lo = __shfl_up((uint32_t)x, o, 64);
-  const uint32_t hi = __shfl_up((uint32_t)(x >> 32), o, 64);
-  return ((uint64_t)hi << 32) | lo;
-}
-
-__device__ __forceinline__ uint64_t shfl_u64(uint64_t x, int src) {
-  const uint32_t lo = __shfl((uint32_t)x, src, 64);
-  const uint32_t hi = __shfl((uint32_t)(x >> 32), src, 64);
-  return ((uint64_t)hi << 32) | lo;
-}
-
-__device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t x, int o) {
-  const uint32_t lo = __shfl_xor((uint32_t)x, o, 64);
-  const uint32_t hi = __shfl_xor((uint32_t)(x >> 32), o, 64);
-  return ((uint64_t)hi << 32) | lo;
-}
-
 // Sum over the wave, in every lane, without the LDS crossbar: the 32- and
 // 16-lane steps swap register halves with v_permlane32_swap /
 // v_permlane16_swap (both results summed), then DPP rotations by 8, 4, 2
@@ -266,34 +253,69 @@ __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
   return v;
 }
 
-__device__ __forceinline__ U128 wave_inscan_u128(U128 v) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const U128 y{shfl_up_u64(v.lo, o), shfl_up_u64(v.hi, o)};
-    if (lane >= o) v = u128_add(v, y);
-  }
-  return v;
+// Maximum over the wave, in every lane, by the same moves.
+template <bool W32>
+__device__ __forceinline__ uint64_t swap_max_u64(uint64_t v) {
+  const uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
+  const auto l = W32 ? __builtin_amdgcn_permlane32_swap(lo, lo, false, false)
+                     : __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+  const auto h = W32 ? __builtin_amdgcn_permlane32_swap(hi, hi, false, false)
+                     : __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+  return max(((uint64_t)h[0] << 32) | l[0], ((uint64_t)h[1] << 32) | l[1]);
+}
+__device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
+  v = swap_max_u64<true>(v);
+  v = swap_max_u64<false>(v);
+  v = max(v, dpp_u64<0x128>(v));
+  v = max(v, dpp_u64<0x124>(v));
+  v = max(v, dpp_u64<0x122>(v));
+  return max(v, dpp_u64<0x121>(v));
 }
 
-__device__ __forceinline__ uint32_t wave_inscan_u32(uint32_t v) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t y = __shfl_up(v, o, 64);
-    if (lane >= o) v += y;
-  }
-  return v;
+// Inclusive sums over the wave by DPP moves (no LDS crossbar): shifts by 1, 2,
+// 4 and 8 lanes inside each 16-lane row, then lane 15 of a row into the next
+// row (rows 1 and 3) and lane 31 into the upper half.  F adds the value that
+// a move brings (0 where the lane has no source).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_zero(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint64_t dpp_zero(uint64_t v) {
+  return ((uint64_t)dpp_zero<CTRL, ROWS>((uint32_t)(v >> 32)) << 32) | dpp_zero<CTRL, ROWS>((uint32_t)v);
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ U128 dpp_zero(U128 v) {
+  return U128{dpp_zero<CTRL, ROWS>(v.lo), dpp_zero<CTRL, ROWS>(v.hi)};
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_zero(double v) {
+  return __longlong_as_double((long long)dpp_zero<CTRL, ROWS>((uint64_t)__double_as_longlong(v)));
+}
+__device__ __forceinline__ uint32_t plus(uint32_t a, uint32_t b) { return a + b; }
+__device__ __forceinline__ double plus(double a, double b) { return a + b; }
+__device__ __forceinline__ U128 plus(U128 a, U128 b) { return u128_add(a, b); }
+template <class T>
+__device__ __forceinline__ T wave_inscan(T v) {
+  v = plus(v, dpp_zero<0x111, 0xF>(v));  // row_shr:1
+  v = plus(v, dpp_zero<0x112, 0xF>(v));  // row_shr:2
+  v = plus(v, dpp_zero<0x114, 0xF>(v));  // row_shr:4
+  v = plus(v, dpp_zero<0x118, 0xF>(v));  // row_shr:8
+  v = plus(v, dpp_zero<0x142, 0xA>(v));  // row_bcast:15
+  return plus(v, dpp_zero<0x143, 0xC>(v));  // row_bcast:31
+}
+__device__ __forceinline__ uint64_t readlane_u64(uint64_t v, int lane) {
+  return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), lane) << 32) |
+         (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
 }
 
 struct SampleShared {
   union {
-    unsigned long long hf[kBuckets + 64];  // approximate bucket masses (units of 2^-32)
+    uint32_t hf[kBuckets + 64];  // element counts of the buckets, 64 per-lane spill slots
     struct {
       uint64_t key[kMaxCand];  // (~orderable key) << 32 | position: ascending = nucleus order
-      uint64_t a[kMaxCand];
-      uint64_t b[kMaxCand];
-      uint64_t sa[kMaxSub];  // exact sub-bucket masses of the window
+      uint64_t e[kMaxCand];    // weights
+      uint64_t sa[kMaxSub];    // exact sub-bucket masses of the window
       uint64_t sb[kMaxSub];
       uint32_t scnt[kMaxSub];
     } c;
@@ -307,10 +329,9 @@ struct SampleShared {
   uint64_t seg_b[kMaxSeg];
   uint32_t seg_t[kMaxSeg];  // elements tied at the threshold key per segment
   uint64_t wkey[64];        // the crossing sub-bucket's elements
-  uint64_t wa[64];
-  uint64_t wb[64];
-  double tab[64];
-  U128 xred[kSWaves];
+  uint64_t we[64];
+  double tab[kTab];
+  U128 xred[kSWaves], yred[kSWaves];
   double dred[kSWaves];
   uint64_t kred[kSWaves];
   uint32_t ured[kSWaves];
@@ -321,8 +342,7 @@ struct SampleShared {
 
 __device__ unsigned long long block_max_u64(unsigned long long v, SampleShared& sh) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v = max(v, (unsigned long long)shfl_xor_u64(v, o));
+  v = wave_max_u64(v);
   __syncthreads();
   if (lane == 0) sh.kred[wave] = v;
   __syncthreads();
@@ -334,7 +354,7 @@ __device__ unsigned long long block_max_u64(unsigned long long v, SampleShared& 
 // Exclusive prefix sums over threads (thread order); *total = sum.
 __device__ U128 block_exscan_u128(U128 v, SampleShared& sh, U128* total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const U128 inc = wave_inscan_u128(v);
+  const U128 inc = wave_inscan(v);
   __syncthreads();
   if (lane == 63) sh.xred[wave] = inc;
   __syncthreads();
@@ -347,15 +367,27 @@ __device__ U128 block_exscan_u128(U128 v, SampleShared& sh, U128* total) {
   return u128_add(base, u128_sub(inc, v));
 }
 
+// Sums of two values over the block, in every thread.
+__device__ __forceinline__ void block_sum2_u128(U128 v, U128 w, SampleShared& sh, U128& sv, U128& sw) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const U128 iv = wave_inscan(v), iw = wave_inscan(w);
+  __syncthreads();
+  if (lane == 63) {
+    sh.xred[wave] = iv;
+    sh.yred[wave] = iw;
+  }
+  __syncthreads();
+  sv = sh.xred[0];
+  sw = sh.yred[0];
+  for (int i = 1; i < kSWaves; ++i) {
+    sv = u128_add(sv, sh.xred[i]);
+    sw = u128_add(sw, sh.yred[i]);
+  }
+}
+
 __device__ double block_exscan_f64(double v, SampleShared& sh, double* total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  double inc = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const double y =
-        __longlong_as_double((long long)shfl_up_u64((uint64_t)__double_as_longlong(inc), o));
-    if (lane >= o) inc += y;
-  }
+  const double inc = wave_inscan(v);
   __syncthreads();
   if (lane == 63) sh.dred[wave] = inc;
   __syncthreads();
@@ -370,7 +402,7 @@ __device__ double block_exscan_f64(double v, SampleShared& sh, double* total) {
 
 __device__ uint32_t block_exscan_u32(uint32_t v, SampleShared& sh, uint32_t* total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint32_t inc = wave_inscan_u32(v);
+  const uint32_t inc = wave_inscan(v);
   __syncthreads();
   if (lane == 63) sh.ured[wave] = inc;
   __syncthreads();
@@ -389,64 +421,52 @@ __device__ __forceinline__ U128 block_sum_u128(U128 v, SampleShared& sh) {
   return tot;
 }
 
-// The lane's four positions p .. p+3 of a chunk; positions past the row are
-// invalid and not read.
-template <bool VEC>
-__device__ __forceinline__ void load4(const float* __restrict__ row, int n, int p, float (&x)[4],
-                                      bool (&v)[4]) {
-  if (VEC && p + 3 < n) {
-    const float4 q = *reinterpret_cast<const float4*>(row + p);
+// The lane's four positions p .. p+3; positions past the row are not read and
+// give -inf, whose weight is 0 and whose bucket is the last.
+__device__ __forceinline__ void load4(const float* __restrict__ row, int n, int p, float (&x)[4]) {
+  if (p + 3 < n) {
+    float4 q;
+    __builtin_memcpy(&q, row + p, 16);  // one load at any alignment
     x[0] = q.x;
     x[1] = q.y;
     x[2] = q.z;
     x[3] = q.w;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = true;
   } else {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      v[e] = p + e < n;
-      x[e] = v[e] ? row[p + e] : 0.0f;
-    }
+    for (int e = 0; e < 4; ++e) x[e] = p + e < n ? row[p + e] : -__builtin_inff();
   }
 }
 
-// fn(q, p, x, v) on every chunk q of the row, chunks dealt to waves in turn,
-// two chunks loaded ahead per wave iteration.
-template <bool VEC, class F>
+// fn(q, p, x) on chunks q0, q0 + step, ... below q1, UN chunks loaded ahead.
+template <int UN, class F>
+__device__ __forceinline__ void walk_chunks(const float* __restrict__ row, int n, int q0, int q1, int step, F&& fn) {
+  const int lane = threadIdx.x & 63;
+  for (int q = q0; q < q1; q += UN * step) {
+    float x[UN][4];
+#pragma unroll
+    for (int u = 0; u < UN; ++u)
+      if (u == 0 || q + u * step < q1) load4(row, n, (q + u * step) * kChunk + 4 * lane, x[u]);
+#pragma unroll
+    for (int u = 0; u < UN; ++u)
+      if (u == 0 || q + u * step < q1) fn(q + u * step, (q + u * step) * kChunk + 4 * lane, x[u]);
+  }
+}
+
+// Every chunk of the row, dealt to the waves in turn.
+template <int UN = 2, class F>
 __device__ __forceinline__ void for_chunks(const float* __restrict__ row, int n, int NC, F&& fn) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int q = wave; q < NC; q += 2 * kSWaves) {
-    const int q2 = q + kSWaves;
-    float x0[4], x1[4];
-    bool v0[4], v1[4];
-    load4<VEC>(row, n, q * kChunk + 4 * lane, x0, v0);
-    load4<VEC>(row, n, q2 * kChunk + 4 * lane, x1, v1);
-    fn(q, q * kChunk + 4 * lane, x0, v0);
-    if (q2 < NC) fn(q2, q2 * kChunk + 4 * lane, x1, v1);
-  }
+  walk_chunks<UN>(row, n, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), NC, kSWaves, fn);
 }
 
-// fn(q, p, x, v) on every chunk q of the row, each wave on one contiguous
-// range of chunks (so that a segment's chunks mostly fall to one wave), two
-// chunks loaded per iteration.
-template <bool VEC, class F>
+// Every chunk of the row, each wave on one contiguous range (so that a
+// segment's chunks mostly fall to one wave).
+template <int UN = 2, class F>
 __device__ __forceinline__ void for_chunks_contig(const float* __restrict__ row, int n, int NC, F&& fn) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int per = (NC + kSWaves - 1) / kSWaves;
-  const int q1 = min(NC, (wave + 1) * per);
-  for (int q = wave * per; q < q1; q += 2) {
-    float x0[4], x1[4];
-    bool v0[4], v1[4];
-    load4<VEC>(row, n, q * kChunk + 4 * lane, x0, v0);
-    if (q + 1 < q1) load4<VEC>(row, n, (q + 1) * kChunk + 4 * lane, x1, v1);
-    fn(q, q * kChunk + 4 * lane, x0, v0);
-    if (q + 1 < q1) fn(q + 1, (q + 1) * kChunk + 4 * lane, x1, v1);
-  }
+  walk_chunks<UN>(row, n, wave * per, min(NC, (wave + 1) * per), 1, fn);
 }
 
-// VEC: rows start 16-byte aligned (n % 4 == 0), positions load as float4.
-template <bool VEC>
 __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(6))) void k_sample(
     const float* __restrict__ f, int n, const unsigned long long* __restrict__ best, int nblk,
     const int32_t* __restrict__ ids, int R, float temperature, float top_p, uint32_t seed_lo,
@@ -461,7 +481,7 @@ __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(6))) 
   const int NS = (n + G - 1) / G;
   const int NC = (n + kChunk - 1) / kChunk;
 
-  if (t < 64) sh.tab[t] = exp2((double)t * (1.0 / 64.0));
+  if (t < kTab) sh.tab[t] = exp2((double)t * (1.0 / kTab));
   sh.seg_a[t] = 0ull;
   sh.seg_b[t] = 0ull;
   sh.seg_t[t] = 0u;
@@ -479,130 +499,134 @@ __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(6))) 
   for (int i = t; i < nblk; i += kSThreads) kmax = max(kmax, best[(int64_t)m * kMaxBlocks + i]);
   kmax = block_max_u64(kmax, sh);  // its barriers also publish the table and the zeroed state
   const float vmax = from_orderable((uint32_t)(kmax >> 32));
-  const double kk = 64.0 / (kLn2 * (double)temperature);
+  const double kk = (double)kTab / (kLn2 * (double)temperature);
   const double c0 = -(double)vmax * kk;
   const float kb = (float)kBuckets / (kYSpan * temperature);
   const double* tab = sh.tab;
-  auto fix = [&](float x) { return fix_of(weight28(x, kk, c0, tab)); };
+  auto fix = [&](float x) { return weight56(x, kk, c0, tab); };
   auto member = [&](float x, int pos, uint32_t T, int cut) {
     const uint32_t k = orderable(x);
     return k > T || (k == T && pos <= cut);
   };
 
   // Exact pass with the window [lo, hi]: segment masses of the buckets below
-  // lo, the window's elements into the list.  Returns the total mass Z.  A
-  // wave's chunks are contiguous, so each lane sums its share of a segment
-  // and the wave reduces it once per segment (one wave-wide sum per chunk
-  // cost a quarter of the pass); one vote per chunk skips the list code
-  // where no element of the chunk falls in the window.
-  auto collect = [&](int lo, int hi) -> U128 {
-    uint64_t za = 0ull, zb = 0ull;
-    uint64_t sa = 0ull, sbm = 0ull;  // the lane's masses below the window in segment cur
+  // lo, the window's elements into the list.  Returns the total mass Z and the
+  // mass `above` of the buckets below lo.  A wave's chunks are contiguous, so
+  // each lane sums its share of a segment and the wave reduces it once per
+  // segment (one wave-wide sum per chunk cost a quarter of the pass); one vote
+  // per chunk skips the list code where no element of the chunk falls in the
+  // window.
+  auto collect = [&](int lo, int hi, U128& Z, U128& above) {
+    uint64_t za = 0ull, zb = 0ull, ma = 0ull, mb = 0ull;
+    // the lane's masses in segment cur (at most 128 weights): all, below the window
+    uint64_t sz = 0ull, sm = 0ull;
     int cur = -1;
+    // floor(y) < b is y < b; the last bucket has no upper end
+    const float ylo = (float)lo, yhi = (float)(hi + 1);
+    const bool window = lo <= hi, last = hi >= kBuckets - 1;
     auto flush = [&]() {
-      const uint64_t A = wave_sum_u64(sa), B = wave_sum_u64(sbm);
+      za += part_a(sz);
+      zb += part_b(sz);
+      ma += part_a(sm);
+      mb += part_b(sm);
+      const uint64_t A = wave_sum_u64(part_a(sm)), B = wave_sum_u64(part_b(sm));
       if (lane == 0 && (A | B)) {
         atomicAdd(reinterpret_cast<unsigned long long*>(&sh.seg_a[cur]), (unsigned long long)A);
         atomicAdd(reinterpret_cast<unsigned long long*>(&sh.seg_b[cur]), (unsigned long long)B);
       }
-      sa = 0ull;
-      sbm = 0ull;
+      sz = 0ull;
+      sm = 0ull;
     };
-    for_chunks_contig<VEC>(row, n, NC, [&](int q, int p, const float (&x)[4], const bool (&v)[4]) {
+    for_chunks_contig(row, n, NC, [&](int q, int p, const float (&x)[4]) {
       const int sg = q * kChunk / G;
       if (sg != cur) {
         if (cur >= 0) flush();
         cur = sg;
       }
-      uint32_t ca = 0u, cb = 0u, ma = 0u, mb = 0u;  // four weights of at most 2^28 each
-      Fix w[4];
+      uint64_t w[4];
       bool cand[4];
       bool anyc = false;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         w[e] = fix(x[e]);
-        const int b = bucket_of(ypos(x[e], vmax, kb));
-        ca += v[e] ? w[e].a : 0u;
-        cb += v[e] ? w[e].b : 0u;
-        const bool mem = v[e] && b < lo;
-        ma += mem ? w[e].a : 0u;
-        mb += mem ? w[e].b : 0u;
-        cand[e] = v[e] && b >= lo && b <= hi;
+        const float y = ypos(x[e], vmax, kb);
+        const bool mem = y < ylo || !window;
+        sz += w[e];
+        sm += mem ? w[e] : 0ull;
+        cand[e] = !mem && (last || y < yhi);
         anyc |= cand[e];
       }
       if (__ballot(anyc)) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
+          cand[e] = cand[e] && p + e < n;
           const uint64_t bal = __ballot(cand[e]);
           if (bal) {
             const int leader = __ffsll((unsigned long long)bal) - 1;
             int base = 0;
             if (lane == leader) base = atomicAdd(&sh.ncand, __popcll(bal));
-            base = __shfl(base, leader, 64);
+            base = __builtin_amdgcn_readlane(base, leader);
             if (cand[e]) {
               const int slot = base + __popcll(bal & ((1ull << lane) - 1ull));
               if (slot < kMaxCand) {
-                const Fix wr = w[e];
                 sh.u.c.key[slot] = ((uint64_t)(~orderable(x[e])) << 32) | (uint32_t)(p + e);
-                sh.u.c.a[slot] = wr.a;
-                sh.u.c.b[slot] = wr.b;
+                sh.u.c.e[slot] = w[e];
               }
             }
           }
         }
       }
-      za += ca;
-      zb += cb;
-      sa += ma;
-      sbm += mb;
     });
     if (cur >= 0) flush();
-    return block_sum_u128(u128_join(za, zb), sh);  // barriers: segments and list complete
+    // barriers: segments and list complete
+    block_sum2_u128(u128_join(za, zb), u128_join(ma, mb), sh, Z, above);
   };
   const bool all = !(top_p < 1.0f);
   int lo = kBuckets, hi = kBuckets - 1;  // all: every bucket below lo, no window
   if (!all) {
-    // 1. approximate histogram (fp32 weights in units of 2^-32) -> window
-    for (int b = t; b < kBuckets + 64; b += kSThreads) sh.u.hf[b] = 0ull;
+    // 1. histogram of element counts -> window
+    for (int b = t; b < kBuckets + 64; b += kSThreads) sh.u.hf[b] = 0u;
     __syncthreads();
-    const float c32 = 1.4426950408889634f / temperature;
-    for_chunks<VEC>(row, n, NC, [&](int, int, const float (&x)[4], const bool (&v)[4]) {
+    for_chunks(row, n, NC, [&](int, int p, const float (&x)[4]) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const float y = ypos(x[e], vmax, kb);
-        const float w = exp2f((x[e] - vmax) * c32);
+        // the last bucket, which many may share (positions past the row among
+        // them), counts in a slot per lane: its weight is nil
         int b = bucket_of(y);
-        if (!v[e] || b == kBuckets - 1) b = kBuckets + lane;
-        atomicAdd(&sh.u.hf[b], v[e] ? (unsigned long long)(uint32_t)(w * 4294967040.0f) : 0ull);
+        if (b == kBuckets - 1) b = kBuckets + lane;
+        atomicAdd(&sh.u.hf[b], 1u);
       }
     });
     __syncthreads();
-    if (wave == 0) {
-      const uint64_t tail = wave_sum_u64(sh.u.hf[kBuckets + lane]);
-      if (lane == 0) sh.u.hf[kBuckets - 1] += tail;
-    }
-    __syncthreads();
-    double d[kBPT];
+    float d[kBPT];
     double dl = 0.0;
+    {
+      // weight of the middle of thread t's first bucket, then from bucket to bucket
+      constexpr float kStep = kYSpan / kBuckets;
+      float w = __expf(-kStep * ((float)(kBPT * t) + 0.5f));
+      constexpr float kRatio = 0.994157758f;  // exp(-kStep)
 #pragma unroll
-    for (int i = 0; i < kBPT; ++i) {
-      d[i] = (double)sh.u.hf[kBPT * t + i];
-      dl += d[i];
+      for (int i = 0; i < kBPT; ++i) {
+        d[i] = (float)sh.u.hf[kBPT * t + i] * w;
+        dl += (double)d[i];
+        w *= kRatio;
+      }
     }
     double ztot;
     double acc = block_exscan_f64(dl, sh, &ztot);
     const double need_a = (double)top_p * ztot;
-    // error of the estimate: fp32 exponent and exp2 rounding, truncation
-    const double slack = 1e-5 * ztot + 2.0 * (double)n;
+    // error of the estimate: the elements' spread inside their buckets
+    const double slack = 1e-4 * ztot;
 #pragma unroll
     for (int i = 0; i < kBPT; ++i) {
-      if (acc < need_a && acc + d[i] >= need_a) {
+      if (acc < need_a && acc + (double)d[i] >= need_a) {
         const int b = kBPT * t + i;
         sh.lo = (acc >= need_a - slack && b > 0) ? b - 1 : b;
-        sh.hi = (acc + d[i] <= need_a + slack && b < kBuckets - 1) ? b + 1 : b;
+        sh.hi = (acc + (double)d[i] <= need_a + slack && b < kBuckets - 1) ? b + 1 : b;
         sh.bsel = b;
       }
-      acc += d[i];
+      acc += (double)d[i];
     }
     __syncthreads();
     if (sh.bsel >= 0) {
@@ -615,44 +639,81 @@ __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(6))) 
     __syncthreads();
   }
 
-  // 2. exact pass: Z, segment masses below the window, the window's list
-  const U128 Z = collect(lo, hi);
-  if (!all) {
-    U128 need = u128_ceil((double)top_p * u128_to_f64(Z));
-    if (need.lo == 0ull && need.hi == 0ull) need.lo = 1ull;
-    U128 above = block_sum_u128(u128_join(sh.seg_a[t], sh.seg_b[t]), sh);
-    int nc = sh.ncand;
-    U128 wmass{0ull, 0ull};
-    if (nc <= kMaxCand) {
-      U128 cl{0ull, 0ull};
-      for (int i = t; i < nc; i += kSThreads) cl = u128_add(cl, u128_join(sh.u.c.a[i], sh.u.c.b[i]));
-      wmass = block_sum_u128(cl, sh);
+  // 2. exact pass: Z, segment masses below the window, the window's list; then
+  // the list's sub-bucket that holds the cut.  The estimate may have missed the
+  // cut by a bucket, or a widened window overflow the list: the pass is redone
+  // on another window next to it, three times at most, then on the group of 4
+  // buckets that an exact histogram gives.
+  U128 need{0ull, 0ull}, above;
+  int nc = 0, nsub = 0, ss = -1;
+  auto sub_of = [&](uint64_t key) {
+    const float x = from_orderable(~(uint32_t)(key >> 32));
+    return min(max(subbucket_of(ypos(x, vmax, kb)) - kSub * lo, 0), nsub - 1);
+  };
+  bool group = false;  // [lo, hi] holds the cut
+  for (int tries = 0;; ++tries) {
+    U128 Z;
+    collect(lo, hi, Z, above);
+    if (all) break;
+    if (tries == 0) {
+      need = u128_ceil((double)top_p * u128_to_f64(Z));
+      if (need.lo == 0ull && need.hi == 0ull) need.lo = 1ull;
     }
-    if (nc > kMaxCand || !u128_lt(above, need) || u128_lt(u128_add(above, wmass), need)) {
-      // the window missed the cut or overflowed the list: exact histogram
-      // over groups of 4 buckets, then the exact pass over that group
+    nc = sh.ncand;
+    const bool below = !u128_lt(above, need), over = nc > kMaxCand;
+    if (!below && !over) {
+      // exact histogram of the list over sub-buckets of the window
+      nsub = kSub * (hi - lo + 1);
+      sh.u.c.sa[t] = 0ull;
+      sh.u.c.sb[t] = 0ull;
+      sh.u.c.scnt[t] = 0u;
+      if (t == 0) sh.bsel = -1;
       __syncthreads();
+      for (int i = t; i < nc; i += kSThreads) {
+        const int s = sub_of(sh.u.c.key[i]);
+        const uint64_t w = sh.u.c.e[i];
+        atomicAdd(reinterpret_cast<unsigned long long*>(&sh.u.c.sa[s]), (unsigned long long)part_a(w));
+        atomicAdd(reinterpret_cast<unsigned long long*>(&sh.u.c.sb[s]), (unsigned long long)part_b(w));
+        atomicAdd(&sh.u.c.scnt[s], 1u);
+      }
+      __syncthreads();
+      const U128 st = u128_join(sh.u.c.sa[t], sh.u.c.sb[t]);
+      U128 tot;
+      const U128 sx = u128_add(above, block_exscan_u128(st, sh, &tot));
+      if (t < nsub && u128_lt(sx, need) && !u128_lt(u128_add(sx, st), need)) {
+        sh.bsel = t;
+        sh.above = sx;
+      }
+      __syncthreads();
+      ss = sh.bsel;  // -1: the cut lies past the window
+      if (ss >= 0) break;
+    }
+    if (group) break;
+    __syncthreads();
+    if (tries < 3 && below && lo > 0) {
+      hi = lo - 1;
+      lo = max(0, lo - 2);
+    } else if (tries < 3 && !below && over && hi > lo) {
+      --hi;
+    } else if (tries < 3 && !below && !over && hi < kBuckets - 1) {
+      lo = hi + 1;
+      hi = min(hi + 2, kBuckets - 1);
+    } else {
+      group = true;
       for (int b = t; b < kCoarse + 64; b += kSThreads) {
         sh.u.h.a[b] = 0ull;
         sh.u.h.b[b] = 0ull;
       }
-      if (t == 0) {
-        sh.bsel = -1;
-        sh.ncand = 0;
-      }
-      sh.seg_a[t] = 0ull;
-      sh.seg_b[t] = 0ull;
+      if (t == 0) sh.bsel = -1;
       __syncthreads();
-      for_chunks<VEC>(row, n, NC, [&](int, int, const float (&x)[4], const bool (&v)[4]) {
+      for_chunks(row, n, NC, [&](int, int p, const float (&x)[4]) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const Fix w = fix(x[e]);
+          const uint64_t w = fix(x[e]);
           int b = bucket_of(ypos(x[e], vmax, kb)) >> 2;
-          if (!v[e] || b == kCoarse - 1) b = kCoarse + lane;
-          atomicAdd(reinterpret_cast<unsigned long long*>(&sh.u.h.a[b]),
-                    (unsigned long long)(v[e] ? w.a : 0u));
-          atomicAdd(reinterpret_cast<unsigned long long*>(&sh.u.h.b[b]),
-                    (unsigned long long)(v[e] ? w.b : 0u));
+          if (b == kCoarse - 1) b = kCoarse + lane;
+          atomicAdd(reinterpret_cast<unsigned long long*>(&sh.u.h.a[b]), (unsigned long long)part_a(w));
+          atomicAdd(reinterpret_cast<unsigned long long*>(&sh.u.h.b[b]), (unsigned long long)part_b(w));
         }
       });
       __syncthreads();
@@ -676,42 +737,15 @@ __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(6))) 
       const int cg = max(sh.bsel, 0);
       lo = 4 * cg;
       hi = 4 * cg + 3;
-      __syncthreads();
-      collect(lo, hi);
-      above = block_sum_u128(u128_join(sh.seg_a[t], sh.seg_b[t]), sh);
-      nc = sh.ncand;
     }
-
+    if (t == 0) sh.ncand = 0;
+    sh.seg_a[t] = 0ull;
+    sh.seg_b[t] = 0ull;
+    __syncthreads();
+  }
+  if (!all) {
     if (nc <= kMaxCand) {
-      // exact histogram of the list over sub-buckets of the window
-      const int nsub = kSub * (hi - lo + 1);
-      sh.u.c.sa[t] = 0ull;
-      sh.u.c.sb[t] = 0ull;
-      sh.u.c.scnt[t] = 0u;
-      if (t == 0) sh.bsel = -1;
-      __syncthreads();
-      auto sub_of = [&](uint64_t key) {
-        const float x = from_orderable(~(uint32_t)(key >> 32));
-        return min(max(subbucket_of(ypos(x, vmax, kb)) - kSub * lo, 0), nsub - 1);
-      };
-      for (int i = t; i < nc; i += kSThreads) {
-        const int s = sub_of(sh.u.c.key[i]);
-        atomicAdd(reinterpret_cast<unsigned long long*>(&sh.u.c.sa[s]),
-                  (unsigned long long)sh.u.c.a[i]);
-        atomicAdd(reinterpret_cast<unsigned long long*>(&sh.u.c.sb[s]),
-                  (unsigned long long)sh.u.c.b[i]);
-        atomicAdd(&sh.u.c.scnt[s], 1u);
-      }
-      __syncthreads();
-      const U128 st = u128_join(sh.u.c.sa[t], sh.u.c.sb[t]);
-      U128 tot;
-      const U128 sx = u128_add(above, block_exscan_u128(st, sh, &tot));
-      if (t < nsub && u128_lt(sx, need) && !u128_lt(u128_add(sx, st), need)) {
-        sh.bsel = t;
-        sh.above = sx;
-      }
-      __syncthreads();
-      const int ss = max(sh.bsel, 0);
+      ss = max(ss, 0);
       const U128 as = sh.above;
       const uint32_t cs = sh.u.c.scnt[ss];
       if (cs <= 64u) {
@@ -725,8 +759,7 @@ __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(6))) 
             if (in) {
               const int slot = got + __popcll(bal & ((1ull << lane) - 1ull));
               sh.wkey[slot] = sh.u.c.key[i];
-              sh.wa[slot] = sh.u.c.a[i];
-              sh.wb[slot] = sh.u.c.b[i];
+              sh.we[slot] = sh.u.c.e[i];
             }
             got += __popcll(bal);
           }
@@ -735,14 +768,10 @@ __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(6))) 
           __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
           if (lane < got) {
             const uint64_t kj = sh.wkey[lane];
-            uint64_t A = 0ull, B = 0ull;
-            for (int i = 0; i < got; ++i) {
-              const bool before = sh.wkey[i] < kj;
-              A += before ? sh.wa[i] : 0ull;
-              B += before ? sh.wb[i] : 0ull;
-            }
-            const U128 ex = u128_add(as, u128_join(A, B));
-            const U128 in = u128_add(ex, u128_join(sh.wa[lane], sh.wb[lane]));
+            uint64_t A = 0ull;  // at most 64 weights
+            for (int i = 0; i < got; ++i) A += sh.wkey[i] < kj ? sh.we[i] : 0ull;
+            const U128 ex = u128_add(as, U128{A, 0ull});
+            const U128 in = u128_add(ex, U128{sh.we[lane], 0ull});
             if (u128_lt(ex, need) && !u128_lt(in, need)) {
               sh.T = ~(uint32_t)(kj >> 32);
               sh.cut_pos = (int)(uint32_t)kj;
@@ -758,9 +787,9 @@ __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(6))) 
           if (s < ss || (s == ss && key <= kc)) {
             const int pos = (int)(uint32_t)key;
             atomicAdd(reinterpret_cast<unsigned long long*>(&sh.seg_a[pos / G]),
-                      (unsigned long long)sh.u.c.a[i]);
+                      (unsigned long long)part_a(sh.u.c.e[i]));
             atomicAdd(reinterpret_cast<unsigned long long*>(&sh.seg_b[pos / G]),
-                      (unsigned long long)sh.u.c.b[i]);
+                      (unsigned long long)part_b(sh.u.c.e[i]));
           }
         }
       } else {
@@ -769,8 +798,7 @@ __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(6))) 
         while (P < nc) P <<= 1;
         for (int i = nc + t; i < P; i += kSThreads) {
           sh.u.c.key[i] = ~0ull;
-          sh.u.c.a[i] = 0ull;
-          sh.u.c.b[i] = 0ull;
+          sh.u.c.e[i] = 0ull;
         }
         __syncthreads();
         for (int k = 2; k <= P; k <<= 1) {
@@ -782,19 +810,17 @@ __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(6))) 
               if ((ki > kl) == ((i & k) == 0)) {
                 sh.u.c.key[i] = kl;
                 sh.u.c.key[l] = ki;
-                const uint64_t ai = sh.u.c.a[i], bi = sh.u.c.b[i];
-                sh.u.c.a[i] = sh.u.c.a[l];
-                sh.u.c.b[i] = sh.u.c.b[l];
-                sh.u.c.a[l] = ai;
-                sh.u.c.b[l] = bi;
+                const uint64_t ei = sh.u.c.e[i];
+                sh.u.c.e[i] = sh.u.c.e[l];
+                sh.u.c.e[l] = ei;
               }
             }
             __syncthreads();
           }
         }
         const int i0 = 2 * t, i1 = 2 * t + 1;
-        const U128 e0 = i0 < nc ? u128_join(sh.u.c.a[i0], sh.u.c.b[i0]) : U128{0ull, 0ull};
-        const U128 e1 = i1 < nc ? u128_join(sh.u.c.a[i1], sh.u.c.b[i1]) : U128{0ull, 0ull};
+        const U128 e0{i0 < nc ? sh.u.c.e[i0] : 0ull, 0ull};
+        const U128 e1{i1 < nc ? sh.u.c.e[i1] : 0ull, 0ull};
         U128 tot2;
         const U128 ex0 = u128_add(above, block_exscan_u128(u128_add(e0, e1), sh, &tot2));
         const U128 ex1 = u128_add(ex0, e0);
@@ -805,9 +831,9 @@ __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(6))) 
         for (int i = t; i <= jc; i += kSThreads) {
           const int pos = (int)(uint32_t)sh.u.c.key[i];
           atomicAdd(reinterpret_cast<unsigned long long*>(&sh.seg_a[pos / G]),
-                    (unsigned long long)sh.u.c.a[i]);
+                    (unsigned long long)part_a(sh.u.c.e[i]));
           atomicAdd(reinterpret_cast<unsigned long long*>(&sh.seg_b[pos / G]),
-                    (unsigned long long)sh.u.c.b[i]);
+                    (unsigned long long)part_b(sh.u.c.e[i]));
         }
         if (t == 0 && jc >= 0) {
           sh.T = ~(uint32_t)(sh.u.c.key[jc] >> 32);
@@ -831,17 +857,15 @@ __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(6))) 
         }
         if (t == 0) sh.bsel = -1;
         __syncthreads();
-        for_chunks<VEC>(row, n, NC, [&](int, int, const float (&x)[4], const bool (&v)[4]) {
+        for_chunks(row, n, NC, [&](int, int p, const float (&x)[4]) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             const uint32_t key = orderable(x[e]);
-            if (v[e] && in_window(x[e]) && (key & kmask) == Tk) {
+            if (p + e < n && in_window(x[e]) && (key & kmask) == Tk) {
               const int b = (int)((key >> shift) & 255u);
-              const Fix w = fix(x[e]);
-              atomicAdd(reinterpret_cast<unsigned long long*>(&sh.u.h.a[b]),
-                        (unsigned long long)w.a);
-              atomicAdd(reinterpret_cast<unsigned long long*>(&sh.u.h.b[b]),
-                        (unsigned long long)w.b);
+              const uint64_t w = fix(x[e]);
+              atomicAdd(reinterpret_cast<unsigned long long*>(&sh.u.h.a[b]), (unsigned long long)part_a(w));
+              atomicAdd(reinterpret_cast<unsigned long long*>(&sh.u.h.b[b]), (unsigned long long)part_b(w));
               atomicAdd(&sh.u.h.cnt[b], 1u);
             }
           }
@@ -865,17 +889,16 @@ __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(6))) 
       }
       // the c-th element tied at Tk in id order completes the nucleus:
       // smallest c >= 1 with ab + c * E(Tk) >= need
-      const Fix wt = fix(from_orderable(Tk));
-      const U128 WT = u128_join(wt.a, wt.b);
+      const U128 WT{fix(from_orderable(Tk)), 0ull};
       const double cd = ceil(u128_to_f64(u128_sub(need, ab)) / u128_to_f64(WT));
       uint32_t c = cd < 1.0 ? 1u : (cd > (double)nt ? nt : (uint32_t)cd);
       while (c > 1u && !u128_lt(u128_add(ab, u128_mul32(WT, c - 1u)), need)) --c;
       while (c < nt && u128_lt(u128_add(ab, u128_mul32(WT, c)), need)) ++c;
       // ties per segment, then the segment and the lane holding the c-th
-      for_chunks<VEC>(row, n, NC, [&](int q, int, const float (&x)[4], const bool (&v)[4]) {
+      for_chunks(row, n, NC, [&](int q, int p, const float (&x)[4]) {
         uint32_t ties = 0u;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) ties += (v[e] && orderable(x[e]) == Tk) ? 1u : 0u;
+        for (int e = 0; e < 4; ++e) ties += (p + e < n && orderable(x[e]) == Tk) ? 1u : 0u;
         ties = (uint32_t)wave_sum_u64(ties);
         if (lane == 0 && ties) atomicAdd(&sh.seg_t[q * kChunk / G], ties);
       });
@@ -895,16 +918,15 @@ __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(6))) 
         for (int cb = sg * G; cb < end; cb += kChunk) {
           const int p = cb + 4 * lane;
           float x[4];
-          bool v[4];
-          load4<VEC>(row, n, p, x, v);
+          load4(row, n, p, x);
           bool tie[4];
           uint32_t lt = 0u;
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            tie[e] = v[e] && orderable(x[e]) == Tk;
+            tie[e] = p + e < n && orderable(x[e]) == Tk;
             lt += tie[e] ? 1u : 0u;
           }
-          const uint32_t inc = wave_inscan_u32(lt);
+          const uint32_t inc = wave_inscan(lt);
           uint32_t seen = run + inc - lt;
           int hit = -1;
 #pragma unroll
@@ -919,21 +941,21 @@ __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(6))) 
             }
             break;
           }
-          run += __shfl(inc, 63, 64);
+          run += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
         }
       }
       __syncthreads();
       // members of the window
       const uint32_t Tw = sh.T;
       const int cw = sh.cut_pos;
-      for_chunks<VEC>(row, n, NC, [&](int q, int p, const float (&x)[4], const bool (&v)[4]) {
+      for_chunks(row, n, NC, [&](int q, int p, const float (&x)[4]) {
         uint64_t A = 0ull, B = 0ull;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          if (v[e] && in_window(x[e]) && member(x[e], p + e, Tw, cw)) {
-            const Fix w = fix(x[e]);
-            A += w.a;
-            B += w.b;
+          if (p + e < n && in_window(x[e]) && member(x[e], p + e, Tw, cw)) {
+            const uint64_t w = fix(x[e]);
+            A += part_a(w);
+            B += part_b(w);
           }
         }
         A = wave_sum_u64(A);
@@ -969,48 +991,55 @@ __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(6))) 
     if (sg >= 0) {
       U128 run = sh.claim_base;
       const int end = min(n, (sg + 1) * G);
-      // the segment's chunks in groups of kSegChunks, a group's loads issued
-      // together
+      // the segment's chunks in groups of kSegChunks: a group's loads and
+      // sums side by side, then the elements of the chunk that is claimed
       for (int cg = sg * G; cg < end && pick < 0; cg += kSegChunks * kChunk) {
-      float xg[kSegChunks][4];
-      bool vg[kSegChunks][4];
+        U128 inc[kSegChunks], l[kSegChunks];
 #pragma unroll
-      for (int c = 0; c < kSegChunks; ++c) load4<VEC>(row, n, cg + c * kChunk + 4 * lane, xg[c], vg[c]);
+        for (int c = 0; c < kSegChunks; ++c) {
+          const int p = cg + c * kChunk + 4 * lane;
+          float x[4];
+          load4(row, n, p, x);
+          l[c] = U128{0ull, 0ull};
 #pragma unroll
-      for (int c = 0; c < kSegChunks; ++c) {
-        const int cb = cg + c * kChunk;
-        if (cb >= end || pick >= 0) break;
-        const int p = cb + 4 * lane;
-        float x[4];
-        bool v[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          x[e] = xg[c][e];
-          v[e] = vg[c][e];
-        }
-        U128 li[4];
-        U128 l{0ull, 0ull};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          if (v[e] && member(x[e], p + e, T, cut)) {
-            const Fix w = fix(x[e]);
-            l = u128_add(l, u128_join(w.a, w.b));
+          for (int e = 0; e < 4; ++e) {
+            if (p + e < n && member(x[e], p + e, T, cut)) {
+              l[c] = u128_add(l[c], U128{fix(x[e]), 0ull});
+            }
           }
-          li[e] = l;
+          inc[c] = wave_inscan(l[c]);
         }
-        const U128 inc = wave_inscan_u128(l);
-        const U128 lb = u128_add(run, u128_sub(inc, l));
-        int hit = -1;
+        int cc = -1;
+        U128 before = run, li{0ull, 0ull};
 #pragma unroll
-        for (int e = 3; e >= 0; --e)
-          if (u128_lt(target, u128_shl24(u128_add(lb, li[e])))) hit = e;
-        const uint64_t bal = __ballot(hit >= 0);
-        if (bal) {
-          const int src = __ffsll((unsigned long long)bal) - 1;
-          pick = cb + 4 * src + __shfl(hit, src, 64);
+        for (int c = 0; c < kSegChunks; ++c) {
+          if (cc < 0 && cg + c * kChunk < end) {
+            const U128 after = u128_add(run, U128{readlane_u64(inc[c].lo, 63), readlane_u64(inc[c].hi, 63)});
+            if (u128_lt(target, u128_shl24(after))) {
+              cc = c;
+              before = u128_add(run, u128_sub(inc[c], l[c]));  // mass before the lane's positions
+            }
+            run = after;
+          }
         }
-        run = u128_add(run, U128{shfl_u64(inc.lo, 63), shfl_u64(inc.hi, 63)});
-      }
+        if (cc >= 0) {
+          const int cb = cg + cc * kChunk, p = cb + 4 * lane;
+          float x[4];
+          load4(row, n, p, x);
+          int hit = -1;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            if (p + e < n && member(x[e], p + e, T, cut)) {
+              li = u128_add(li, U128{fix(x[e]), 0ull});
+            }
+            if (hit < 0 && u128_lt(target, u128_shl24(u128_add(before, li)))) hit = e;
+          }
+          const uint64_t bal = __ballot(hit >= 0);
+          if (bal) {
+            const int src = __ffsll((unsigned long long)bal) - 1;
+            pick = cb + 4 * src + __shfl(hit, src, 64);
+          }
+        }
       }
     }
     if (lane == 0) tokens[m] = ids[pick >= 0 ? pick : 0];
@@ -1049,13 +1078,8 @@ hipError_t launch_sample(const float* f, int M, int n, const unsigned long long*
   if ((int64_t)(n + kChunk * kMaxSeg - 1) / (kChunk * kMaxSeg) * kChunk * kMaxSeg >= (1ll << 31))
     return hipErrorInvalidValue;
   const uint32_t lo = (uint32_t)seed, hi = (uint32_t)(seed >> 32);
-  const bool vec = n % 4 == 0 && (reinterpret_cast<uintptr_t>(f) & 15u) == 0;
-  if (vec)
-    launch_kernel(k_sample<true>, dim3(M), dim3(kSThreads), 0, s, f, n, best, nblk, ids, R,
-                       temperature, top_p, lo, hi, tokens);
-  else
-    launch_kernel(k_sample<false>, dim3(M), dim3(kSThreads), 0, s, f, n, best, nblk, ids, R,
-                       temperature, top_p, lo, hi, tokens);
+  launch_kernel(k_sample, dim3(M), dim3(kSThreads), 0, s, f, n, best, nblk, ids, R, temperature, top_p, lo, hi,
+                tokens);
   return hipGetLastError();
 }
 
