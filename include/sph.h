@@ -110,7 +110,11 @@ void sph_subset_destroy(sph_subset subset);
  * The cloud workspace holds the fp32 partial logits (unless z_out is given,
  * the region is still reserved) and per-block row maxima; the fuse
  * workspace holds per-block argmax candidates and, for SPH_SAMPLE, the fused
- * fp32 logits.  Returns 0 for M == 0.
+ * fp32 logits.  Returns 0 for M == 0.  For SPH_SAMPLE on few long rows the
+ * size includes optional scratch of the sampler (up to 0.2 MB per row): a
+ * smaller workspace of align256(M * 16384) + align256(M * n_sub * 4) bytes
+ * (plus the widened hidden codes of sph_fuse_verify_hq) is accepted too and
+ * gives the same tokens, with one workgroup per row.
  */
 size_t sph_cloud_partial_workspace(int64_t M, sph_subset subset);
 size_t sph_fuse_verify_workspace(int64_t M, sph_subset subset, int mode);

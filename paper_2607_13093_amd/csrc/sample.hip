@@ -55,6 +55,8 @@
 //      nucleus member in id order whose running mass M has
 //      M * 2^24 > u24 * mass(nucleus): a scan over segment masses picks the
 //      segment, one wave scans inside it.
+#include <algorithm>
+
 #include "sph_internal.h"
 
 namespace sph {
@@ -335,6 +337,7 @@ struct SampleShared {
   double dred[kSWaves];
   uint64_t kred[kSWaves];
   uint32_t ured[kSWaves];
+  uint32_t off[64];
   U128 above, claim_base;
   uint32_t tie_base, T;
   int32_t bsel, lo, hi, ncand, cut_idx, cut_pos, claim_seg, tie_seg;
@@ -467,10 +470,214 @@ __device__ __forceinline__ void for_chunks_contig(const float* __restrict__ row,
   walk_chunks<UN>(row, n, wave * per, min(NC, (wave + 1) * per), 1, fn);
 }
 
+// ---------------------------------------------------------------------------
+// Few rows: the passes over a row are spread over several blocks (launch_sample
+// chooses), with the rest of the selection in one block per row as ever.
+//   k_sample_count  pass 1 over 1/p1 of a row: its bucket counts, and the
+//                   estimated masses of its 64 groups of 64 buckets
+//   k_sample_mass   the window from those of all parts (a group, then a
+//                   bucket), then the exact pass over spp segments of the row
+//   k_sample<true>  takes the parts' sums and lists in place of its own passes
+
+constexpr int kMaxParts = 32;    // parts of the exact pass
+constexpr int kPartCand = 128;   // window elements a part can list
+constexpr int kMassThreads = 256;
+
+struct SplitScratch {
+  float* coarse;    // [M][p1][64]
+  uint32_t* count;  // [M][p1][kBuckets]
+  int32_t* win;     // [M][2]: window
+  uint64_t* part;   // [M][p2][4]: total (a, b), mass below the window (a, b)
+  uint32_t* cnt;    // [M][p2]: window elements
+  uint64_t* seg;    // [M][kMaxSeg][2]
+  uint64_t* list;   // [M][p2][kPartCand][2]: key, weight
+  int p1, p2, spp;
+};
+
+constexpr float kBucketStep = kYSpan / kBuckets;
+// error of the estimated masses, of their total: the spread inside the buckets
+constexpr double kSlack = 1e-4;
+
+template <int NT>
+__device__ __forceinline__ float row_max(const unsigned long long* __restrict__ keys, int nblk,
+                                         uint64_t (&red)[NT / 64]) {
+  uint64_t k = 0ull;
+  for (int i = threadIdx.x; i < nblk; i += NT) k = max(k, (uint64_t)keys[i]);
+  k = wave_max_u64(k);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = k;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < NT / 64; ++w) k = max(k, red[w]);
+  return from_orderable((uint32_t)(k >> 32));
+}
+
+__global__ __launch_bounds__(kSThreads) void k_sample_count(const float* __restrict__ f, int n,
+                                                            const unsigned long long* __restrict__ best,
+                                                            int nblk, float temperature, SplitScratch sc) {
+  __shared__ uint32_t hf[kBuckets + 64];
+  __shared__ uint64_t red[kSWaves];
+  const int m = blockIdx.y, part = blockIdx.x, t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const float* row = f + (int64_t)m * n;
+  for (int b = t; b < kBuckets + 64; b += kSThreads) hf[b] = 0u;
+  const float vmax = row_max<kSThreads>(best + (int64_t)m * kMaxBlocks, nblk, red);  // and the zeros
+  const float kb = (float)kBuckets / (kYSpan * temperature);
+  const int NC = (n + kChunk - 1) / kChunk;
+  const int q0 = (int)((int64_t)NC * part / sc.p1), q1 = (int)((int64_t)NC * (part + 1) / sc.p1);
+  walk_chunks<4>(row, n, q0 + wave, q1, kSWaves, [&](int, int, const float (&x)[4]) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      int b = bucket_of(ypos(x[e], vmax, kb));
+      if (b == kBuckets - 1) b = kBuckets + lane;
+      atomicAdd(&hf[b], 1u);
+    }
+  });
+  __syncthreads();
+  const int64_t at = (int64_t)m * sc.p1 + part;
+  float d = 0.0f;
+  uint32_t c[kBPT];
+#pragma unroll
+  for (int i = 0; i < kBPT; ++i) {
+    c[i] = hf[kBPT * t + i];
+    d += (float)c[i] * __expf(-kBucketStep * ((float)(kBPT * t + i) + 0.5f));
+  }
+#pragma unroll
+  for (int i = 0; i < kBPT; i += 4)
+    *reinterpret_cast<uint4*>(sc.count + at * kBuckets + kBPT * t + i) = make_uint4(c[i], c[i + 1], c[i + 2], c[i + 3]);
+  d += __shfl_xor(d, 1, 64);
+  d += __shfl_xor(d, 2, 64);
+  d += __shfl_xor(d, 4, 64);
+  static_assert(kBPT * 8 == 64, "eight threads per group");
+  if ((t & 7) == 0) sc.coarse[at * 64 + (t >> 3)] = d;
+}
+
+__global__ __launch_bounds__(kMassThreads) void k_sample_mass(const float* __restrict__ f, int n,
+                                                              const unsigned long long* __restrict__ best,
+                                                              int nblk, float temperature, float top_p,
+                                                              SplitScratch sc) {
+  constexpr int NWV = kMassThreads / 64;
+  __shared__ double tab[kTab];
+  __shared__ uint64_t red[NWV];
+  __shared__ uint64_t sums[NWV][4];
+  __shared__ int32_t s_win[2];
+  __shared__ uint32_t s_cnt;
+  const int m = blockIdx.y, part = blockIdx.x, t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const float* row = f + (int64_t)m * n;
+  const int G = kChunk * max(kSegChunks, (n + kChunk * kMaxSeg - 1) / (kChunk * kMaxSeg));
+  const int NS = (n + G - 1) / G;
+  static_assert(kTab == kMassThreads, "one entry per thread");
+  tab[t] = exp2((double)t * (1.0 / kTab));
+  if (t == 0) s_cnt = 0u;
+  int lo = kBuckets, hi = kBuckets - 1;  // top_p 1: every bucket below lo, no window
+  if (top_p < 1.0f && wave == 0) {
+    double c = 0.0;
+    for (int i = 0; i < sc.p1; ++i) c += (double)sc.coarse[((int64_t)m * sc.p1 + i) * 64 + lane];
+    const double inc = wave_inscan(c);
+    auto lane_f64 = [](double v, int l) {
+      return __longlong_as_double((long long)readlane_u64((uint64_t)__double_as_longlong(v), l));
+    };
+    const double ztot = lane_f64(inc, 63), need_a = (double)top_p * ztot, slack = kSlack * ztot;
+    const uint64_t hit = __ballot(inc - c < need_a && inc >= need_a);
+    lo = kBuckets - 2;
+    if (hit) {
+      const int g = __ffsll((unsigned long long)hit) - 1;
+      uint32_t k = 0u;
+      for (int i = 0; i < sc.p1; ++i) k += sc.count[((int64_t)m * sc.p1 + i) * kBuckets + g * 64 + lane];
+      const double d = (double)((float)k * __expf(-kBucketStep * ((float)(g * 64 + lane) + 0.5f)));
+      const double in2 = lane_f64(inc - c, g) + wave_inscan(d);
+      const uint64_t hit2 = __ballot(in2 >= need_a);
+      const int l = hit2 ? __ffsll((unsigned long long)hit2) - 1 : 63;  // (63: rounding of the group's sum)
+      const int b = g * 64 + l;
+      lo = lane_f64(in2 - d, l) >= need_a - slack && b > 0 ? b - 1 : b;
+      hi = lane_f64(in2, l) <= need_a + slack && b < kBuckets - 1 ? b + 1 : b;
+    }
+  }
+  if (wave == 0 && lane == 0) {
+    s_win[0] = lo;
+    s_win[1] = hi;
+    if (part == 0) {
+      sc.win[2 * m] = lo;
+      sc.win[2 * m + 1] = hi;
+    }
+  }
+  const float vmax = row_max<kMassThreads>(best + (int64_t)m * kMaxBlocks, nblk, red);  // and the table
+  lo = s_win[0];
+  hi = s_win[1];
+  const double kk = (double)kTab / (kLn2 * (double)temperature);
+  const double c0 = -(double)vmax * kk;
+  const float kb = (float)kBuckets / (kYSpan * temperature);
+  const float ylo = (float)lo, yhi = (float)(hi + 1);
+  const bool window = lo <= hi, last = hi >= kBuckets - 1;
+  const int64_t at = (int64_t)m * sc.p2 + part;
+  uint64_t* list = sc.list + at * kPartCand * 2;
+  uint64_t za = 0ull, zb = 0ull, ma = 0ull, mb = 0ull;
+  const int s1 = min(NS, (part + 1) * sc.spp);
+  for (int sg = part * sc.spp + wave; sg < s1; sg += NWV) {
+    uint64_t sz = 0ull, sm = 0ull;  // at most 128 weights a lane
+    walk_chunks<4>(row, n, sg * (G / kChunk), min((sg + 1) * (G / kChunk), (n + kChunk - 1) / kChunk), 1,
+                   [&](int, int p, const float (&x)[4]) {
+      uint64_t w[4];
+      bool cand[4], anyc = false;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        w[e] = weight56(x[e], kk, c0, tab);
+        const float y = ypos(x[e], vmax, kb);
+        const bool mem = y < ylo || !window;
+        sz += w[e];
+        sm += mem ? w[e] : 0ull;
+        cand[e] = !mem && (last || y < yhi);
+        anyc |= cand[e];
+      }
+      if (__ballot(anyc)) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          if (cand[e] && p + e < n) {
+            const uint32_t slot = atomicAdd(&s_cnt, 1u);
+            if (slot < (uint32_t)kPartCand) {
+              list[2 * slot] = ((uint64_t)(~orderable(x[e])) << 32) | (uint32_t)(p + e);
+              list[2 * slot + 1] = w[e];
+            }
+          }
+        }
+      }
+    });
+    za += part_a(sz);
+    zb += part_b(sz);
+    ma += part_a(sm);
+    mb += part_b(sm);
+    const uint64_t A = wave_sum_u64(part_a(sm)), B = wave_sum_u64(part_b(sm));
+    if (lane == 0) {
+      sc.seg[((int64_t)m * kMaxSeg + sg) * 2] = A;
+      sc.seg[((int64_t)m * kMaxSeg + sg) * 2 + 1] = B;
+    }
+  }
+  za = wave_sum_u64(za);
+  zb = wave_sum_u64(zb);
+  ma = wave_sum_u64(ma);
+  mb = wave_sum_u64(mb);
+  if (lane == 0) {
+    sums[wave][0] = za;
+    sums[wave][1] = zb;
+    sums[wave][2] = ma;
+    sums[wave][3] = mb;
+  }
+  __syncthreads();
+  if (t < 4) {
+    uint64_t v = 0ull;
+#pragma unroll
+    for (int w = 0; w < NWV; ++w) v += sums[w][t];
+    sc.part[at * 4 + t] = v;
+  }
+  if (t == 0) sc.cnt[at] = s_cnt;
+}
+
+// SPLIT: the passes of the first window were made by the kernels above.
+template <bool SPLIT>
 __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(6))) void k_sample(
     const float* __restrict__ f, int n, const unsigned long long* __restrict__ best, int nblk,
     const int32_t* __restrict__ ids, int R, float temperature, float top_p, uint32_t seed_lo,
-    uint32_t seed_hi, int32_t* __restrict__ tokens) {
+    uint32_t seed_hi, int32_t* __restrict__ tokens, const SplitScratch sc) {
   __shared__ SampleShared sh;
   const int m = blockIdx.x;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -581,9 +788,47 @@ __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(6))) 
     // barriers: segments and list complete
     block_sum2_u128(u128_join(za, zb), u128_join(ma, mb), sh, Z, above);
   };
+  // The same from the parts that k_sample_mass wrote.
+  auto gather = [&](U128& Z, U128& above) {
+    const uint64_t* pt = sc.part + (int64_t)m * sc.p2 * 4;
+    U128 z{0ull, 0ull}, a{0ull, 0ull};
+    uint32_t c = 0u;
+    if (t < sc.p2) {
+      z = u128_join(pt[4 * t], pt[4 * t + 1]);
+      a = u128_join(pt[4 * t + 2], pt[4 * t + 3]);
+      c = sc.cnt[(int64_t)m * sc.p2 + t];
+    }
+    if (t < NS) {
+      sh.seg_a[t] = sc.seg[((int64_t)m * kMaxSeg + t) * 2];
+      sh.seg_b[t] = sc.seg[((int64_t)m * kMaxSeg + t) * 2 + 1];
+    }
+    if (wave == 0) {
+      static_assert(kMaxParts < 64, "a wave scans the parts");
+      const uint32_t inc = wave_inscan(c);
+      const bool fits = __ballot(c > (uint32_t)kPartCand) == 0ull;
+      if (lane <= sc.p2) sh.off[lane] = inc - c;  // (lane p2: the total)
+      if (lane == 0) sh.ncand = fits ? (int)__builtin_amdgcn_readlane((int)inc, 63) : kMaxCand + 1;
+    }
+    block_sum2_u128(z, a, sh, Z, above);  // (and its barriers)
+    if (sh.ncand <= kMaxCand) {
+      for (int i = t; i < sc.p2 * kPartCand; i += kSThreads) {
+        const int p = i / kPartCand, e = i % kPartCand;
+        const uint32_t o = sh.off[p] + e;
+        if (o < sh.off[p + 1]) {
+          const uint64_t* src = sc.list + ((int64_t)m * sc.p2 * kPartCand + i) * 2;
+          sh.u.c.key[o] = src[0];
+          sh.u.c.e[o] = src[1];
+        }
+      }
+    }
+    __syncthreads();
+  };
   const bool all = !(top_p < 1.0f);
   int lo = kBuckets, hi = kBuckets - 1;  // all: every bucket below lo, no window
-  if (!all) {
+  if constexpr (SPLIT) {
+    lo = sc.win[2 * m];
+    hi = sc.win[2 * m + 1];
+  } else if (!all) {
     // 1. histogram of element counts -> window
     for (int b = t; b < kBuckets + 64; b += kSThreads) sh.u.hf[b] = 0u;
     __syncthreads();
@@ -603,9 +848,8 @@ __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(6))) 
     double dl = 0.0;
     {
       // weight of the middle of thread t's first bucket, then from bucket to bucket
-      constexpr float kStep = kYSpan / kBuckets;
-      float w = __expf(-kStep * ((float)(kBPT * t) + 0.5f));
-      constexpr float kRatio = 0.994157758f;  // exp(-kStep)
+      float w = __expf(-kBucketStep * ((float)(kBPT * t) + 0.5f));
+      constexpr float kRatio = 0.994157758f;  // exp(-kBucketStep)
 #pragma unroll
       for (int i = 0; i < kBPT; ++i) {
         d[i] = (float)sh.u.hf[kBPT * t + i] * w;
@@ -616,8 +860,7 @@ __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(6))) 
     double ztot;
     double acc = block_exscan_f64(dl, sh, &ztot);
     const double need_a = (double)top_p * ztot;
-    // error of the estimate: the elements' spread inside their buckets
-    const double slack = 1e-4 * ztot;
+    const double slack = kSlack * ztot;
 #pragma unroll
     for (int i = 0; i < kBPT; ++i) {
       if (acc < need_a && acc + (double)d[i] >= need_a) {
@@ -653,7 +896,8 @@ __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(6))) 
   bool group = false;  // [lo, hi] holds the cut
   for (int tries = 0;; ++tries) {
     U128 Z;
-    collect(lo, hi, Z, above);
+    if (SPLIT && tries == 0) gather(Z, above);
+    else collect(lo, hi, Z, above);
     if (all) break;
     if (tries == 0) {
       need = u128_ceil((double)top_p * u128_to_f64(Z));
@@ -985,65 +1229,51 @@ __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(6))) 
     sh.claim_base = sb;
   }
   __syncthreads();
-  if (wave == 0) {
-    const int sg = sh.claim_seg;
-    int pick = -1;
-    if (sg >= 0) {
-      U128 run = sh.claim_base;
-      const int end = min(n, (sg + 1) * G);
-      // the segment's chunks in groups of kSegChunks: a group's loads and
-      // sums side by side, then the elements of the chunk that is claimed
-      for (int cg = sg * G; cg < end && pick < 0; cg += kSegChunks * kChunk) {
-        U128 inc[kSegChunks], l[kSegChunks];
+  // the claimed segment in groups of kSegChunks chunks, a wave each: the wave
+  // whose chunk holds the target finds the position
+  const int sg = sh.claim_seg;
+  bool done = false;
+  if (sg >= 0) {
+    U128 run = sh.claim_base;
+    const int end = min(n, (sg + 1) * G);
+    for (int cg = sg * G; cg < end && !done; cg += kSegChunks * kChunk) {
+      const int p = cg + wave * kChunk + 4 * lane;
+      uint64_t li[4];  // the lane's mass up to each of its positions
+      U128 inc{0ull, 0ull};
+      if (wave < kSegChunks) {
+        float x[4];
+        load4(row, p < end ? n : 0, p, x);
+        uint64_t l = 0ull;
 #pragma unroll
-        for (int c = 0; c < kSegChunks; ++c) {
-          const int p = cg + c * kChunk + 4 * lane;
-          float x[4];
-          load4(row, n, p, x);
-          l[c] = U128{0ull, 0ull};
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            if (p + e < n && member(x[e], p + e, T, cut)) {
-              l[c] = u128_add(l[c], U128{fix(x[e]), 0ull});
-            }
-          }
-          inc[c] = wave_inscan(l[c]);
+        for (int e = 0; e < 4; ++e) {
+          if (p + e < end && member(x[e], p + e, T, cut)) l += fix(x[e]);
+          li[e] = l;
         }
-        int cc = -1;
-        U128 before = run, li{0ull, 0ull};
-#pragma unroll
-        for (int c = 0; c < kSegChunks; ++c) {
-          if (cc < 0 && cg + c * kChunk < end) {
-            const U128 after = u128_add(run, U128{readlane_u64(inc[c].lo, 63), readlane_u64(inc[c].hi, 63)});
-            if (u128_lt(target, u128_shl24(after))) {
-              cc = c;
-              before = u128_add(run, u128_sub(inc[c], l[c]));  // mass before the lane's positions
-            }
-            run = after;
-          }
-        }
-        if (cc >= 0) {
-          const int cb = cg + cc * kChunk, p = cb + 4 * lane;
-          float x[4];
-          load4(row, n, p, x);
-          int hit = -1;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            if (p + e < n && member(x[e], p + e, T, cut)) {
-              li = u128_add(li, U128{fix(x[e]), 0ull});
-            }
-            if (hit < 0 && u128_lt(target, u128_shl24(u128_add(before, li)))) hit = e;
-          }
-          const uint64_t bal = __ballot(hit >= 0);
-          if (bal) {
-            const int src = __ffsll((unsigned long long)bal) - 1;
-            pick = cb + 4 * src + __shfl(hit, src, 64);
-          }
-        }
+        inc = wave_inscan(U128{l, 0ull});
+        if (lane == 63) sh.xred[wave] = inc;
       }
+      __syncthreads();
+      U128 before = run;
+#pragma unroll
+      for (int c = 0; c < kSegChunks; ++c) {
+        if (c < wave) before = u128_add(before, sh.xred[c]);
+        run = u128_add(run, sh.xred[c]);
+      }
+      if (wave < kSegChunks && !u128_lt(target, u128_shl24(before)) &&
+          u128_lt(target, u128_shl24(u128_add(before, sh.xred[wave])))) {
+        const U128 lb = u128_add(before, u128_sub(inc, U128{li[3], 0ull}));
+        int hit = -1;
+#pragma unroll
+        for (int e = 3; e >= 0; --e)
+          if (u128_lt(target, u128_shl24(u128_add(lb, U128{li[e], 0ull})))) hit = e;
+        const uint64_t bal = __ballot(hit >= 0);
+        if (lane == __ffsll((unsigned long long)bal) - 1) tokens[m] = ids[p + hit];
+      }
+      done = u128_lt(target, u128_shl24(run));
+      __syncthreads();  // before the next group's sums
     }
-    if (lane == 0) tokens[m] = ids[pick >= 0 ? pick : 0];
   }
+  if (!done && t == 0) tokens[m] = ids[0];
 }
 
 __global__ void k_accept(const int32_t* __restrict__ tokens, const int32_t* __restrict__ drafts,
@@ -1071,15 +1301,76 @@ __global__ void k_accept(const int32_t* __restrict__ tokens, const int32_t* __re
   accept[s] = a;
 }
 
+// Whether the passes are spread over several blocks: two more launches, for
+// rows that keep one block busy longer than that.  Measured (one block / spread,
+// tau 0.7, top_p 0.9): 5 rows x 16384 22.0 / 27.5 us, x 32768 31.8 / 28.6,
+// x 65536 51.8 / 32.2; 64 rows x 32768 32.4 / 32.0; 128 rows x 32768 33.5 /
+// 38.3, x 65536 56.0 / 51.8, x 150000 119 / 80.
+static bool split_rows(int64_t M, int64_t n) {
+  return M > 0 && M <= 128 && n >= std::max<int64_t>(32768, 512 * M) && n <= 0x7FFFFFFF;
+}
+
+struct SplitPlan {
+  int p1, p2, spp;
+};
+static SplitPlan split_plan(int M, int n) {
+  const int NC = (n + kChunk - 1) / kChunk;
+  const int G = kChunk * std::max(kSegChunks, (n + kChunk * kMaxSeg - 1) / (kChunk * kMaxSeg));
+  const int NS = (n + G - 1) / G;
+  SplitPlan p;
+  p.p1 = std::min(8, (NC + 31) / 32);
+  p.spp = 4 * ((NS + 4 * kMaxParts - 1) / (4 * kMaxParts));
+  p.p2 = (NS + p.spp - 1) / p.spp;
+  return p;
+}
+
+static size_t take(uint8_t* base, size_t& at, size_t bytes, void** out) {
+  if (out) *out = base + at;
+  at += (bytes + 255) & ~(size_t)255;
+  return at;
+}
+
+static size_t split_layout(int M, const SplitPlan& p, uint8_t* base, SplitScratch* sc) {
+  size_t at = 0;
+  void* q[7];
+  take(base, at, (size_t)M * p.p1 * 64 * 4, &q[0]);
+  take(base, at, (size_t)M * p.p1 * kBuckets * 4, &q[1]);
+  take(base, at, (size_t)M * 8, &q[2]);
+  take(base, at, (size_t)M * p.p2 * 32, &q[3]);
+  take(base, at, (size_t)M * p.p2 * 4, &q[4]);
+  take(base, at, (size_t)M * kMaxSeg * 16, &q[5]);
+  take(base, at, (size_t)M * p.p2 * kPartCand * 16, &q[6]);
+  if (sc)
+    *sc = SplitScratch{(float*)q[0], (uint32_t*)q[1], (int32_t*)q[2], (uint64_t*)q[3],
+                       (uint32_t*)q[4], (uint64_t*)q[5], (uint64_t*)q[6], p.p1, p.p2, p.spp};
+  return at;
+}
+
+size_t sample_scratch_bytes(int64_t M, int64_t n) {
+  if (!split_rows(M, n)) return 0;
+  return split_layout((int)M, split_plan((int)M, (int)n), nullptr, nullptr);
+}
+
 hipError_t launch_sample(const float* f, int M, int n, const unsigned long long* best, int nblk,
                          const int32_t* ids, int R, float temperature, float top_p, uint64_t seed,
-                         int32_t* tokens, hipStream_t s) {
+                         int32_t* tokens, void* scratch, hipStream_t s) {
   if (n < 1 || nblk < 1 || nblk > kMaxBlocks) return hipErrorInvalidValue;
   if ((int64_t)(n + kChunk * kMaxSeg - 1) / (kChunk * kMaxSeg) * kChunk * kMaxSeg >= (1ll << 31))
     return hipErrorInvalidValue;
   const uint32_t lo = (uint32_t)seed, hi = (uint32_t)(seed >> 32);
-  launch_kernel(k_sample, dim3(M), dim3(kSThreads), 0, s, f, n, best, nblk, ids, R, temperature, top_p, lo, hi,
-                tokens);
+  SplitScratch sc{};
+  if (!scratch || !split_rows(M, n)) {
+    launch_kernel(k_sample<false>, dim3(M), dim3(kSThreads), 0, s, f, n, best, nblk, ids, R, temperature,
+                  top_p, lo, hi, tokens, sc);
+    return hipGetLastError();
+  }
+  const SplitPlan p = split_plan(M, n);
+  split_layout(M, p, static_cast<uint8_t*>(scratch), &sc);
+  if (top_p < 1.0f)
+    launch_kernel(k_sample_count, dim3(p.p1, M), dim3(kSThreads), 0, s, f, n, best, nblk, temperature, sc);
+  launch_kernel(k_sample_mass, dim3(p.p2, M), dim3(kMassThreads), 0, s, f, n, best, nblk, temperature, top_p, sc);
+  launch_kernel(k_sample<true>, dim3(M), dim3(kSThreads), 0, s, f, n, best, nblk, ids, R, temperature,
+                top_p, lo, hi, tokens, sc);
   return hipGetLastError();
 }
 

@@ -196,6 +196,12 @@ size_t fuse_ws(int64_t M, int64_t n, int mode) {
   return b;
 }
 
+// The sampler's optional scratch comes last: a workspace without it is
+// accepted, and one block then takes a whole row.
+size_t sample_ws(int64_t M, int64_t n, int mode) {
+  return mode == SPH_SAMPLE ? align256(sph::sample_scratch_bytes(M, n)) : 0;
+}
+
 // int8 hidden-state codes of more rows than the skinny projection takes are
 // widened to bf16 operands [M, round_up(d_end, 8)] after the fuse workspace.
 size_t widen_ws(int64_t M, int64_t d_end) {
@@ -309,12 +315,12 @@ size_t sph_cloud_partial_workspace(int64_t M, sph_subset subset) {
 
 size_t sph_fuse_verify_workspace(int64_t M, sph_subset subset, int mode) {
   if (!subset || M < 0) return 0;
-  return fuse_ws(M, subset->n, mode);
+  return fuse_ws(M, subset->n, mode) + sample_ws(M, subset->n, mode);
 }
 
 size_t sph_fuse_verify_hq_workspace(int64_t M, int64_t d_end, sph_subset subset, int mode) {
   if (!subset || M < 0 || d_end < 0) return 0;
-  return fuse_ws(M, subset->n, mode) + widen_ws(M, d_end);
+  return fuse_ws(M, subset->n, mode) + widen_ws(M, d_end) + sample_ws(M, subset->n, mode);
 }
 
 int sph_hidden_quantize(const void* h, int64_t ldh, int64_t M, int64_t d, int8_t* q_out,
@@ -657,11 +663,13 @@ int fuse_verify_impl(const char* fn, bool codes, const void* q, const float* sca
     }
   }
   if (mode == SPH_SAMPLE) {
+    const size_t extra = sample_ws(M, n, mode);
+    void* scratch = extra > 0 && ws_bytes >= need + extra ? ws + need : nullptr;
     hipError_t e = traced("fuse_sample", s, [&] {
       return sph::launch_sample(fused, (int)M, (int)n,
                                 reinterpret_cast<const unsigned long long*>(best), nblk,
                                 subset->d_ids, (int)rows_per_session, temperature, top_p, seed,
-                                tokens_out, s);
+                                tokens_out, scratch, s);
     });
     if (e != hipSuccess) return hip_fail(e, "sampling launch");
     e = traced("fuse_accept", s, [&] {

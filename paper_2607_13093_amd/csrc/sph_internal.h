@@ -150,7 +150,11 @@ hipError_t launch_quantize(const float* z, const float* amax_part, int nblk, int
 // (row stride kMaxBlocks), whose maximum gives the row's largest logit.
 hipError_t launch_sample(const float* f, int M, int n, const unsigned long long* best, int nblk,
                          const int32_t* ids, int R, float temperature, float top_p, uint64_t seed,
-                         int32_t* tokens, hipStream_t s);
+                         int32_t* tokens, void* scratch, hipStream_t s);
+// Device scratch (256-byte aligned) that lets launch_sample spread the passes
+// over few long rows over several blocks; 0 where it would not.  Without it
+// (scratch null) one block takes a row.
+size_t sample_scratch_bytes(int64_t M, int64_t n);
 hipError_t launch_accept(const int32_t* tokens, const int32_t* drafts, int n_sessions, int R,
                          int32_t* accept, hipStream_t s);
 

@@ -64,3 +64,58 @@ def test_streaming_cloud_projection(shape, wtype):
     # one session of a large case stands for its row tile's first and last rows
     sessions = None if S * R * n < 1_000_000 else [0, S - 1]
     run_format_case(make_workload(cfg), 8, 0, f"stream {shape} {wtype}", sessions=sessions)
+
+
+# (sessions, R, n, tau, top_p): rows whose passes are spread over several
+# blocks, at the edges of the rule, with every mass below the cut, with one
+# part listing too much (tau large) and with a nucleus of a few ids
+LONG_ROWS = [
+    (1, 5, 32768, 0.7, 0.9),
+    (1, 1, 40001, 0.7, 1.0),
+    (2, 3, 70003, 3.0, 0.95),
+    (1, 2, 33027, 0.25, 0.5),
+    (64, 1, 32769, 0.9, 0.8),
+    (32, 4, 65537, 0.6, 0.9),
+]
+
+
+@pytest.mark.parametrize("shape", LONG_ROWS, ids=[f"S{s}R{r}n{n}t{t}p{p}" for s, r, n, t, p in LONG_ROWS])
+def test_sampling_few_long_rows(shape):
+    import numpy as np
+    import torch
+
+    from paper_2607_13093_amd import api as sph
+    from test_gpu_sampling import run_sample_case
+
+    S, R, n, tau, top_p = shape
+    cfg = Config("long_rows", 700 + S + R, d=192, d_end=64, vocab=n + 50, n_sub=n, subset_kind="choice",
+                 sessions=S, rows_per_session=R, mode="sample", temperature=tau, top_p=top_p,
+                 philox_seed=0xABCDEF12345 + n)
+    if S * R <= 8:
+        run_sample_case(make_workload(cfg), tag=f"long rows {shape}")
+    # the same tokens from a workspace without the optional scratch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    M = S * R
+    q = (torch.randn((M, n), generator=g, device="cuda") * 30).round().clamp(-127, 127).to(torch.int8)
+    sc = torch.rand((M,), generator=g, device="cuda") * 0.05 + 0.01
+    ids = np.sort(np.random.default_rng(n).choice(n + 50, n, replace=False)).astype(np.int32)
+    sub = sph.Subset(ids, vocab=n + 50)
+    drafts = torch.zeros((S, R - 1), dtype=torch.int32, device="cuda") if R > 1 else None
+    full = sph.fuse_verify_workspace(M, sub, sph.SAMPLE)
+    base = (M * 16384 + 255) // 256 * 256 + (M * n * 4 + 255) // 256 * 256
+    assert full > base
+    got = []
+    for size in (full, base):
+        ws = torch.full((size,), 0xA5, dtype=torch.uint8, device="cuda")
+        tok, acc, _ = sph.fuse_verify(q, sc, None, None, sub, S, R, drafts, mode=sph.SAMPLE,
+                                      temperature=tau, top_p=top_p, seed=n, workspace=ws)
+        torch.cuda.synchronize()
+        got.append((tok.cpu().numpy(), acc.cpu().numpy()))
+    np.testing.assert_array_equal(got[0][0], got[1][0])
+    np.testing.assert_array_equal(got[0][1], got[1][1])
+    with pytest.raises(sph.SphError):
+        sph.fuse_verify(q, sc, None, None, sub, S, R, drafts, mode=sph.SAMPLE, temperature=tau,
+                        top_p=top_p, seed=n,
+                        workspace=torch.empty((base - 256,), dtype=torch.uint8, device="cuda"))
+    sub.close()
