@@ -1,17 +1,17 @@
 // Dense gathered projection for many rows of h (MFMA path).
 //
-//   C[m, j] = sum_k h[m, k] * W[S_j, k]      (eq. 12 / eq. 11 on the subset S)
+//   C[m, j] = sum_k h[m, k] * W[S_j, k]      (eq. 12 on the subset S)
 //
 // With hundreds of rows the contraction is dense enough for the matrix
 // cores: a block computes a BM x BN tile of C with v_mfma_f32_32x32x16_bf16
 // (bf16 inputs, fp32 accumulation).  Both operands are K-contiguous in
-// memory (h is [M, K] row-major, the weight rows are vocab-major), so both
-// tiles are staged in LDS as [rows][BK] with a 16-byte row pad, which makes
-// every operand fetch a conflict-free ds_read_b128.  The B tile is gathered:
-// tile column j is weight row S[n0 + j]; fp8 E4M3 rows are widened to bf16
-// (exactly) on their way into LDS and their per-row scale is applied in the
-// epilogue.  Global loads of the next K step are issued into registers
-// before the MFMAs of the current step.
+// memory (h is [M, K] row-major, the weight rows are vocab-major), and both
+// tiles are copied global-to-LDS as [rows][BK].  The B tile is gathered: tile
+// column j is weight row S[n0 + j]; fp8 E4M3 rows are widened to bf16
+// (exactly) in registers and their per-row scale is applied in the epilogue.
+// Any K that is whole 16-byte chunks takes these kernels: staging partial
+// steps through registers instead ran 3 to 5 times slower (268 rows x 15360 x
+// 4048 columns 172 us, see TAIL).
 //
 // Operand layouts of the 32x32x16 instruction (checked on the hardware):
 //   A: lane l supplies A[l % 32][8 * (l / 32) + e], e = 0..7
@@ -45,6 +45,26 @@ __device__ __forceinline__ float cloud_value(float dot, const MfmaArgs& a, int i
   return zv;
 }
 
+// Descriptor of `rows` rows of z from the tile's first one (at most 320 rows of
+// 2^19 positions, below 2^30 bytes), an offset past any tile's, and the
+// non-temporal store of one value.
+__device__ __forceinline__ auto tile_rsrc(float* z, int rows, int n) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(scalar_ptr(z)), 0,
+                                           (int)((uint32_t)rows * (uint32_t)n * 4u), 0x00020000);
+}
+constexpr uint32_t kPastTile = 0xC0000000u;  // (plus an offset inside the tile: no wrap)
+__device__ __forceinline__ void store_z(float v, __amdgpu_buffer_rsrc_t rsrc, uint32_t off) {
+  __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rsrc, (int)off, 0, 2);
+}
+
+// From the row of accumulator r - 1 (of the previous fragment for r = 0) to that
+// of r: the next row, or the fifth next.  The empty asm keeps one running
+// offset: all of them at once spilled 100 registers.
+__device__ __forceinline__ void next_row(uint32_t& off, int r, int n) {
+  off += (uint32_t)n * (r % 4 == 0 ? 20u : 4u);
+  asm volatile("" : "+v"(off));
+}
+
 template <int BM, int BN, int WM, int WN, int WT, int EPI, int FM, int FN>
 __device__ __forceinline__ void tile_epilogue(f32x16_t (&acc)[FM][FN], const MfmaArgs& a,
                                               const int32_t* s_ids, uint32_t* s_rmax, int m0,
@@ -58,82 +78,66 @@ __device__ __forceinline__ void tile_epilogue(f32x16_t (&acc)[FM][FN], const Mfm
   float red[P];
 #pragma unroll
   for (int t = FM * 16; t < P; ++t) red[t] = 0.0f;
-  auto fill = [&]() {
-#pragma unroll
-    for (int i = 0; i < FM; ++i) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int lrow = wm * TM + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        const int row = m0 + lrow;
-        float best = 0.0f;
-#pragma unroll
-        for (int j = 0; j < FN; ++j) {
-          const int lcol = wn * TN + j * 32 + (lane & 31);
-          const int col = n0 + lcol;
-          if (row < M && col < n) {
-            const float zv = cloud_value<WT>(acc[i][j][r], a, s_ids[lcol]);
-            if (EPI == kEpiCloud || a.z) __builtin_nontemporal_store(zv, a.z + (int64_t)row * n + col);
-            best = fmaxf(best, fabsf(fminf(fmaxf(zv, -a.clip), a.clip)));
-          }
-        }
-        red[i * 16 + r] = best;
-      }
-    }
-  };
-  // Cloud tiles wholly inside z: the same values and row maxima without a
-  // bounds test per element.  Each store is the scalar-base + 32-bit-offset
-  // form (the row's base is uniform, the lane adds its column and, for lanes
-  // 32..63, the four rows below), and max |clamp(z)| is taken as
-  // min(|z|, c), which is the same value for every z, NaN included.  The
-  // general form above compiled to two branches, a 64-bit address and a
-  // reload of the bias pointer per element: 13.6 us of a 210 us block on
-  // the dense 2048-row shape.
-  auto fill_full = [&](auto has_bias, auto store) {
-    constexpr bool HB = decltype(has_bias)::value, ST = decltype(store)::value;
+  // z goes out through a buffer descriptor of the tile's rows: a store past
+  // row M - 1 is dropped, so every tile inside the positions runs the same
+  // straight-line code, and in the last one the lanes past n store beyond the
+  // descriptor.  Rows past M and positions past n repeat a valid one, so they
+  // leave the maxima as they are; max |clamp(z)| is taken as min(|z|, c), which
+  // is the same value for every z, NaN included.  (A bounds test per element
+  // compiled to two branches, a 64-bit address and a reload of the bias
+  // pointer: 13.6 us of a 210 us block on the dense 2048-row shape, now 7, and
+  // every tile of a batch whose rows do not fill its row tiles.)
+  const auto rsrc = tile_rsrc(a.z ? a.z + (int64_t)m0 * n : nullptr, min(BM, M - m0), n);
+  const uint32_t lrow0 = (uint32_t)(wm * TM + 4 * (lane >> 5));
+  const uint32_t lcol0 = (uint32_t)(n0 + wn * TN + (lane & 31));
+  auto fill = [&](auto edge, auto has_bias, auto store) {
+    constexpr bool ED = decltype(edge)::value, HB = decltype(has_bias)::value, ST = decltype(store)::value;
     float cs[FN], cb[FN];
 #pragma unroll
     for (int j = 0; j < FN; ++j) {
       const int id = s_ids[wn * TN + j * 32 + (lane & 31)];
       cs[j] = WT == 1 ? a.wscale[id] : 1.0f;
-      cb[j] = HB ? a.bias[id] : 0.0f;
+      cb[j] = HB && a.bias ? a.bias[id] : 0.0f;
     }
-    uint32_t loff = ((uint32_t)(lane >> 5) * 4u * (uint32_t)n + (uint32_t)(lane & 31)) * 4u;
-    asm volatile("" : "+v"(loff));
+    const bool hb = a.bias != nullptr;
+    uint32_t oj[FN];
+#pragma unroll
+    for (int j = 0; j < FN; ++j) oj[j] = ED && lcol0 + 32u * j >= (uint32_t)n ? kPastTile : 128u * j;
     const float clip = a.clip;
-    const int row0 = __builtin_amdgcn_readfirstlane(m0 + wm * TM);  // first row of the wave's tile
+    uint32_t off = (lrow0 * (uint32_t)n + lcol0) * 4u;
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int row = row0 + i * 32 + 8 * (r >> 2) + (r & 3);  // the row of lanes 0..31
-        const uint8_t* rb = scalar_ptr(a.z + (int64_t)row * n + n0 + wn * TN);
+        if (i + r > 0) next_row(off, r, n);
         float best = 0.0f;
 #pragma unroll
         for (int j = 0; j < FN; ++j) {
           float zv = acc[i][j][r];
           if constexpr (WT == 1) zv = zv * cs[j];
-          if constexpr (HB) zv = zv + cb[j];
-          if constexpr (ST)
-            __builtin_nontemporal_store(zv, (__attribute__((address_space(1))) float*)(rb + loff + j * 128));
+          if constexpr (HB) zv = hb ? zv + cb[j] : zv;
+          if constexpr (ST) store_z(zv, rsrc, off + oj[j]);
           best = fmaxf(best, fminf(fabsf(zv), clip));
         }
         red[i * 16 + r] = best;
       }
     }
   };
-  bool done = false;
-  if (m0 + BM <= M && n0 + BN <= n && n <= (1 << 27)) {
-    const bool st = EPI == kEpiCloud || a.z != nullptr;
-    if (a.bias) {
-      if (st) fill_full(std::true_type{}, std::true_type{});
-      else fill_full(std::true_type{}, std::false_type{});
+  {
+    using T = std::true_type;
+    using F = std::false_type;
+    const bool st = EPI == kEpiCloud || a.z != nullptr, edge = n0 + BN > n;
+    if (!st) {
+      if (a.bias) fill(F{}, T{}, F{});
+      else fill(F{}, F{}, F{});
+    } else if (edge) {
+      fill(T{}, T{}, T{});
+    } else if (a.bias) {
+      fill(F{}, T{}, T{});
     } else {
-      if (st) fill_full(std::false_type{}, std::true_type{});
-      else fill_full(std::false_type{}, std::false_type{});
+      fill(F{}, F{}, T{});
     }
-    done = true;
   }
-  if (!done) fill();
   half_wave_max_transpose<P>(red, lane);
   constexpr int PER = P / 32;
 #pragma unroll
@@ -220,132 +224,9 @@ __device__ __forceinline__ void tile_epilogue(f32x16_t (&acc)[FM][FN], const Mfm
   }
 }
 
-// BM x BN tile per block, 4 waves in a 2 x 2 grid, wave tile (BM/2) x (BN/2).
-// LDS holds two K steps of both tiles; the global loads of step k+1 are in
-// flight (in registers) while step k's MFMAs run, then land in the other LDS
-// buffer, so each step needs a single barrier.
-template <int BM, int BN, int WT, int EPI>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_mfma(const MfmaArgs a) {
-  constexpr int NT = 256;
-  constexpr int TM = BM / 2, TN = BN / 2;    // wave tile
-  constexpr int FM = TM / 32, FN = TN / 32;  // 32x32 fragments per wave
-  constexpr int A_CH = BM * (kBK / 8) / NT;  // 16-byte A chunks per thread per step
-  constexpr int B_EPC = WT == 0 ? 8 : 16;    // weight elements per 16-byte chunk
-  constexpr int B_CH = BN * (kBK / B_EPC) / NT;
-  static_assert(A_CH * NT == BM * (kBK / 8) && B_CH * NT == BN * (kBK / B_EPC), "tile/threads");
-
-  extern __shared__ __align__(16) uint8_t smem[];
-  uint16_t* As = reinterpret_cast<uint16_t*>(smem);            // [2][BM][kLDK]
-  uint16_t* Bs = As + 2 * BM * kLDK;                             // [2][BN][kLDK]
-  int32_t* s_ids = reinterpret_cast<int32_t*>(Bs + 2 * BN * kLDK);
-  uint32_t* s_rmax = reinterpret_cast<uint32_t*>(s_ids + BN);
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  int mt, nt;
-  tile_of_block(blockIdx.x, a.m_tiles, a.n_tiles, mt, nt);
-  const int m0 = mt * BM, n0 = nt * BN;
-  const int M = a.M, K = a.K, n = a.n;
-
-  for (int i = tid; i < BN; i += NT) s_ids[i] = n0 + i < n ? a.ids[n0 + i] : -1;
-  for (int i = tid; i < BM; i += NT) s_rmax[i] = 0u;
-  __syncthreads();
-
-  u32x4_t ra[A_CH], rb[B_CH];
-  auto load = [&](int k0) {
-#pragma unroll
-    for (int i = 0; i < A_CH; ++i) {
-      const int c = tid + i * NT, row = c >> 3, kk = k0 + (c & 7) * 8;
-      const int gr = m0 + row;
-      ra[i] = (gr < M && kk < K) ? *reinterpret_cast<const u32x4_t*>(a.h + (int64_t)gr * a.ldh + kk)
-                                 : u32x4_t{0u, 0u, 0u, 0u};
-    }
-#pragma unroll
-    for (int i = 0; i < B_CH; ++i) {
-      const int c = tid + i * NT;
-      const int row = c / (kBK / B_EPC), kk = k0 + (c % (kBK / B_EPC)) * B_EPC;
-      const int id = s_ids[row];
-      rb[i] = (id >= 0 && kk < K)
-                  ? __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(
-                        a.w + (int64_t)id * a.ldw_bytes + (int64_t)kk * (WT == 0 ? 2 : 1)))
-                  : u32x4_t{0u, 0u, 0u, 0u};
-    }
-  };
-  auto store = [&](int buf) {
-    uint16_t* as = As + buf * BM * kLDK;
-    uint16_t* bs = Bs + buf * BN * kLDK;
-#pragma unroll
-    for (int i = 0; i < A_CH; ++i) {
-      const int c = tid + i * NT, row = c >> 3, kc = c & 7;
-      *reinterpret_cast<u32x4_t*>(as + row * kLDK + kc * 8) = ra[i];
-    }
-#pragma unroll
-    for (int i = 0; i < B_CH; ++i) {
-      const int c = tid + i * NT;
-      const int row = c / (kBK / B_EPC), kc = c % (kBK / B_EPC);
-      if constexpr (WT == 0) {
-        *reinterpret_cast<u32x4_t*>(bs + row * kLDK + kc * 8) = rb[i];
-      } else {
-        const uint32_t w4[4] = {rb[i].x, rb[i].y, rb[i].z, rb[i].w};
-        u32x4_t lo, hi;
-        lo.x = e4m3x2_to_bf16x2_m<false>(w4[0]); lo.y = e4m3x2_to_bf16x2_m<true>(w4[0]);
-        lo.z = e4m3x2_to_bf16x2_m<false>(w4[1]); lo.w = e4m3x2_to_bf16x2_m<true>(w4[1]);
-        hi.x = e4m3x2_to_bf16x2_m<false>(w4[2]); hi.y = e4m3x2_to_bf16x2_m<true>(w4[2]);
-        hi.z = e4m3x2_to_bf16x2_m<false>(w4[3]); hi.w = e4m3x2_to_bf16x2_m<true>(w4[3]);
-        *reinterpret_cast<u32x4_t*>(bs + row * kLDK + kc * 16) = lo;
-        *reinterpret_cast<u32x4_t*>(bs + row * kLDK + kc * 16 + 8) = hi;
-      }
-    }
-  };
-
-  f32x16_t acc[FM][FN];
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-
-  if (K > 0) {
-    load(0);
-    store(0);
-    __syncthreads();
-  }
-  int buf = 0;
-  for (int k0 = 0; k0 < K; k0 += kBK) {
-    const bool next = k0 + kBK < K;
-    if (next) load(k0 + kBK);
-    const uint16_t* as = As + buf * BM * kLDK;
-    const uint16_t* bs = Bs + buf * BN * kLDK;
-#pragma unroll
-    for (int kk = 0; kk < kBK / 16; ++kk) {
-      bf16x8_t af[FM], bfr[FN];
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-        af[i] = *reinterpret_cast<const bf16x8_t*>(
-            as + (wm * TM + i * 32 + (lane & 31)) * kLDK + kk * 16 + 8 * (lane >> 5));
-#pragma unroll
-      for (int j = 0; j < FN; ++j)
-        bfr[j] = *reinterpret_cast<const bf16x8_t*>(
-            bs + (wn * TN + j * 32 + (lane & 31)) * kLDK + kk * 16 + 8 * (lane >> 5));
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
-    }
-    // The other buffer was last read in the previous step, which every wave
-    // finished before the barrier that ended it.
-    if (next) store(buf ^ 1);
-    __syncthreads();
-    buf ^= 1;
-  }
-
-  tile_epilogue<BM, BN, 2, 2, WT, EPI>(acc, a, s_ids, s_rmax, m0, n0, nt, reinterpret_cast<int8_t*>(As));
-}
-
-
-// Direct-to-LDS variant (bf16 weights, K a multiple of 64).  gfx950's
+// Tiles of bf16 weights, K a multiple of 8 (TAIL: no multiple of the K step;
+// the missing chunks of the last step read its first chunk and are cleared in
+// LDS).  gfx950's
 // global_load_lds_dwordx4 writes a wave's 64 x 16 bytes straight into LDS
 // (lane l at base + 16*l), so tiles never pass through registers and no
 // ds_write is issued.  A wave instruction fills 8 rows x 128 bytes; rows are
@@ -357,7 +238,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 // shape this loop ran 1.2x faster than register staging.
 // Waves: WM x WN (wave tile (BM/WM) x (BN/WN)), two per SIMD, whose
 // accumulators live in the 256 registers each wave has.
-template <int BM, int BN, int WM, int WN, int EPI, bool O32>
+template <int BM, int BN, int WM, int WN, int EPI, bool O32, bool TAIL>
 __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(WM * WN / 4, WM * WN / 4)))
 void k_mfma_dma(const MfmaArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -413,10 +294,24 @@ void k_mfma_dma(const MfmaArgs a) {
     const int64_t step = (int64_t)k0 * 2;
     const uint8_t* ha = O32 ? scalar_ptr(hbase + step) : nullptr;
     const uint8_t* wb = O32 ? scalar_ptr(a.w + step) : nullptr;
+    if (!TAIL || K - k0 >= kBK) {
 #pragma unroll
-    for (int i = 0; i < A_INS; ++i) pa[i].copy(ha, step, (lds_void_t*)(as + (iw * A_INS + i) * 1024));
+      for (int i = 0; i < A_INS; ++i) pa[i].copy(ha, step, (lds_void_t*)(as + (iw * A_INS + i) * 1024));
 #pragma unroll
-    for (int i = 0; i < B_INS; ++i) pb[i].copy(wb, step, (lds_void_t*)(bs + (iw * B_INS + i) * 1024));
+      for (int i = 0; i < B_INS; ++i) pb[i].copy(wb, step, (lds_void_t*)(bs + (iw * B_INS + i) * 1024));
+    } else {
+      const int valid = K - k0;
+      auto back = [&](int r) {
+        const int c = (lane & 7) ^ swz8(r);
+        return c * 8 < valid ? 0u : (uint32_t)(c * 16);
+      };
+#pragma unroll
+      for (int i = 0; i < A_INS; ++i)
+        pa[i].copy_back(ha, step, (lds_void_t*)(as + (iw * A_INS + i) * 1024), back((iw * A_INS + i) * 8 + lr));
+#pragma unroll
+      for (int i = 0; i < B_INS; ++i)
+        pb[i].copy_back(wb, step, (lds_void_t*)(bs + (iw * B_INS + i) * 1024), back((iw * B_INS + i) * 8 + lr));
+    }
   };
 
   f32x16_t acc[FM][FN];
@@ -437,6 +332,11 @@ void k_mfma_dma(const MfmaArgs a) {
     // the other stage was last read in the previous step, finished by all
     // waves before that step's closing barrier
     if (k0 + kBK < K) issue(k0 + kBK, stage ^ 1);
+    if (TAIL && K - k0 < kBK) {
+      zero_tail<BM, NT>(As + stage * BM * kBK, K - k0);
+      zero_tail<BN, NT>(Bs + stage * BN * kBK, K - k0);
+      __syncthreads();
+    }
     const uint16_t* as = As + stage * BM * kBK;
     const uint16_t* bs = Bs + stage * BN * kBK;
 #pragma unroll
@@ -512,6 +412,9 @@ typedef __attribute__((address_space(3))) const char* lds_cptr_t;
 // Harness, dense_full / dense_sub: two stages 3300 / 996 us; three, weights
 // copied in the last sub-step three steps ahead, 3250 / 970 us; three with
 // the copies spread over the step 3290 -> 3257 / 1004 -> 961 us (A/B runs).
+// Odd or partial last steps run on k_mfma_dma (an epilogue for them here was no
+// faster: 1184 rows x 31038 x 4000 columns 400 against 390 us, 1999 x 32767 x
+// 4032 567 against 526).
 template <int EPI, int NB>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void k_mfma_w1(const MfmaArgs a) {
@@ -757,48 +660,36 @@ void k_mfma_w1(const MfmaArgs a) {
 #pragma unroll
   for (int t = 0; t < P; ++t) red[t] = 0.0f;
   const float clip = a.clip;
-  if (m0 + BM <= M && n0 + BN <= n && n <= (1 << 27) && !a.bias) {
-    uint32_t loff = ((uint32_t)(lane >> 5) * 4u * (uint32_t)n + (uint32_t)(lane & 31)) * 4u;
-    asm volatile("" : "+v"(loff));
-    const int row0 = __builtin_amdgcn_readfirstlane(m0 + wm * TM);
+  const auto rsrc = tile_rsrc(a.z + (int64_t)m0 * n, min(BM, M - m0), n);
+  const uint32_t lrow0 = (uint32_t)(wm * TM + 4 * (lane >> 5));
+  const uint32_t lcol0 = (uint32_t)(n0 + wn * TN + (lane & 31));
+  auto fill = [&](auto plain) {
+    constexpr bool PL = decltype(plain)::value;  // no bias, a tile inside the positions
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
 #pragma unroll
       for (int j = 0; j < FN; ++j) {
         f32x16_t v;
         asm volatile("; fragment out of the AGPRs" : "=v"(v) : "0"(acc[i][j]));
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int row = row0 + i * 32 + 8 * (r >> 2) + (r & 3);
-          const uint8_t* rb = scalar_ptr(a.z + (int64_t)row * n + n0 + wn * TN);
-          __builtin_nontemporal_store(v[r], (__attribute__((address_space(1))) float*)(rb + loff + j * 128));
-          red[i * 16 + r] = fmaxf(red[i * 16 + r], fminf(fabsf(v[r]), clip));
-        }
-      }
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < FM; ++i) {
-#pragma unroll
-      for (int j = 0; j < FN; ++j) {
-        f32x16_t v;
-        asm volatile("; fragment out of the AGPRs" : "=v"(v) : "0"(acc[i][j]));
-        const int lcol = wn * TN + j * 32 + (lane & 31);
-        const int col = n0 + lcol;
+        const uint32_t col = lcol0 + 32u * j;
+        uint32_t off = ((lrow0 + 32u * i) * (uint32_t)n + col) * 4u;
         float cb = 0.0f;
-        if (a.bias) cb = a.bias[NB == 2 ? s_ids[lcol] : (col < n ? a.ids[col] : last_id)];
+        if (!PL && a.bias) {
+          const int lcol = wn * TN + j * 32 + (lane & 31);
+          cb = a.bias[NB == 2 ? s_ids[lcol] : (col < (uint32_t)n ? a.ids[col] : last_id)];
+        }
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int row = m0 + wm * TM + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-          if (row < M && col < n) {
-            const float zv = a.bias ? v[r] + cb : v[r];
-            __builtin_nontemporal_store(zv, a.z + (int64_t)row * n + col);
-            red[i * 16 + r] = fmaxf(red[i * 16 + r], fabsf(fminf(fmaxf(zv, -clip), clip)));
-          }
+          const float zv = !PL && a.bias ? v[r] + cb : v[r];
+          if (r > 0) next_row(off, r, n);
+          store_z(zv, rsrc, !PL && col >= (uint32_t)n ? kPastTile : off);
+          red[i * 16 + r] = fmaxf(red[i * 16 + r], fminf(fabsf(zv), clip));
         }
       }
     }
-  }
+  };
+  if (n0 + BN <= n && !a.bias) fill(std::true_type{});
+  else fill(std::false_type{});
   half_wave_max_transpose<P>(red, lane);
   constexpr int PER = P / 32;
 #pragma unroll
@@ -814,7 +705,7 @@ void k_mfma_w1(const MfmaArgs a) {
 #endif
 }
 
-// Direct-to-LDS variant for fp8 E4M3 weights (K a multiple of 64).  The A
+// Tiles of fp8 E4M3 weights, K a multiple of 16 (TAIL as above).  The A
 // tile is staged as above; the B tile keeps its bytes: a weight row holds 64
 // codes per K step (64 bytes, four 16-byte chunks), and a wave instruction
 // fills 16 rows.  Chunks are XOR-swizzled with g(row) = (row >> 2) & 3, so
@@ -826,7 +717,7 @@ void k_mfma_w1(const MfmaArgs a) {
 // other wave covers the wait.
 __device__ __forceinline__ int swz4(int row) { return (row >> 2) & 3; }
 
-template <int BM, int BN, int WM, int WN, int EPI, bool O32>
+template <int BM, int BN, int WM, int WN, int EPI, bool O32, bool TAIL>
 __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(WM * WN / 4, WM * WN / 4)))
 void k_mfma_dma8(const MfmaArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -874,11 +765,27 @@ void k_mfma_dma8(const MfmaArgs a) {
     uint8_t* bs = Bs + stage * BN * kBK;
     const uint8_t* ha = O32 ? scalar_ptr(hbase + (int64_t)k0 * 2) : nullptr;
     const uint8_t* wb = O32 ? scalar_ptr(a.w + k0) : nullptr;
+    if (!TAIL || K - k0 >= kBK) {
 #pragma unroll
-    for (int i = 0; i < A_INS; ++i)
-      pa[i].copy(ha, (int64_t)k0 * 2, (lds_void_t*)(as + (iw * A_INS + i) * 1024));
+      for (int i = 0; i < A_INS; ++i)
+        pa[i].copy(ha, (int64_t)k0 * 2, (lds_void_t*)(as + (iw * A_INS + i) * 1024));
 #pragma unroll
-    for (int i = 0; i < B_INS; ++i) pb[i].copy(wb, k0, (lds_void_t*)(bs + (iw * B_INS + i) * 1024));
+      for (int i = 0; i < B_INS; ++i) pb[i].copy(wb, k0, (lds_void_t*)(bs + (iw * B_INS + i) * 1024));
+    } else {
+      const int valid = K - k0;
+#pragma unroll
+      for (int i = 0; i < A_INS; ++i) {
+        const int c = (lane & 7) ^ swz8((iw * A_INS + i) * 8 + (lane >> 3));
+        pa[i].copy_back(ha, (int64_t)k0 * 2, (lds_void_t*)(as + (iw * A_INS + i) * 1024),
+                        c * 8 < valid ? 0u : (uint32_t)(c * 16));
+      }
+#pragma unroll
+      for (int i = 0; i < B_INS; ++i) {
+        const int c = (lane & 3) ^ swz4((iw * B_INS + i) * 16 + (lane >> 2));
+        pb[i].copy_back(wb, k0, (lds_void_t*)(bs + (iw * B_INS + i) * 1024),
+                        c * 16 < valid ? 0u : (uint32_t)(c * 16));
+      }
+    }
   };
 
   f32x16_t acc[FM][FN];
@@ -898,6 +805,17 @@ void k_mfma_dma8(const MfmaArgs a) {
   for (int k0 = 0; k0 < K; k0 += kBK) {
     const uint16_t* as = As + stage * BM * kBK;
     const uint8_t* bs = Bs + stage * BN * kBK;
+    if (TAIL && K - k0 < kBK) {
+      const int valid = K - k0;
+      zero_tail<BM, NT>(As + stage * BM * kBK, valid);
+      for (int i = tid; i < BN * 4; i += NT) {
+        const int row = i >> 2, c = i & 3;
+        if (c * 16 >= valid)
+          *reinterpret_cast<u32x4_t*>(Bs + stage * BN * kBK + row * kBK + ((c ^ swz4(row)) << 4)) =
+              u32x4_t{0u, 0u, 0u, 0u};
+      }
+      __syncthreads();
+    }
     // The step's fp8 codes (8 bytes per fragment and sub-step, 16 VGPRs)
     // are read before the next stage's copies go out.  The compiler makes
     // an LDS read behind pending copies wait for them where it cannot
@@ -948,11 +866,6 @@ void k_mfma_dma8(const MfmaArgs a) {
 }
 
 template <int BM, int BN>
-constexpr size_t mfma_lds_bytes() {
-  return (size_t)2 * (BM + BN) * kLDK * 2 + (size_t)BN * 4 + (size_t)BM * 4;
-}
-
-template <int BM, int BN>
 constexpr size_t mfma_dma_lds_bytes() {
   return (size_t)2 * (BM + BN) * kBK * 2 + (size_t)BN * 4 + (size_t)BM * 4;
 }
@@ -969,89 +882,79 @@ constexpr size_t mfma_dma8_lds_bytes() {
 // tile 128 x 128).
 constexpr int kTileWM = 2, kTileWN = 4;
 
+template <int BM, int BN, int WT, int EPI, bool O32, bool TAIL>
+static hipError_t launch_dma(const MfmaArgs& a, hipStream_t s) {
+  static std::atomic<uint64_t> lds_set{0};
+  constexpr int WM = kTileWM, WN = kTileWN;
+  auto k = [] {
+    if constexpr (WT == 0) return k_mfma_dma<BM, BN, WM, WN, EPI, O32, TAIL>;
+    else return k_mfma_dma8<BM, BN, WM, WN, EPI, O32, TAIL>;
+  }();
+  constexpr size_t lds = WT == 0 ? mfma_dma_lds_bytes<BM, BN>() : mfma_dma8_lds_bytes<BM, BN>();
+  hipError_t e = set_lds_limit_once(lds_set, reinterpret_cast<const void*>(k), lds);
+  if (e != hipSuccess) return e;
+  launch_kernel(k, dim3(a.m_tiles * a.n_tiles), dim3(64 * WM * WN), lds, s, a);
+  return hipGetLastError();
+}
+
+template <int NB>
+static hipError_t launch_w1(const MfmaArgs& a, size_t lds, hipStream_t s) {
+  static std::atomic<uint64_t> lds_set{0};
+  auto k = k_mfma_w1<kEpiCloud, NB>;
+  hipError_t e = set_lds_limit_once(lds_set, reinterpret_cast<const void*>(k), lds);
+  if (e != hipSuccess) return e;
+  launch_kernel(k, dim3(a.m_tiles * a.n_tiles), dim3(256), lds, s, a);
+  return hipGetLastError();
+}
+
 template <int BM, int BN, int WT, int EPI>
 static hipError_t launch_tile(MfmaArgs a, hipStream_t s) {
-  static std::atomic<uint64_t> lds_set_dma{0}, lds_set_dma64{0}, lds_set_reg{0};
-  constexpr int WM = kTileWM, WN = kTileWN, NT = 64 * WM * WN;
   a.m_tiles = (a.M + BM - 1) / BM;
   a.n_tiles = (a.n + BN - 1) / BN;
-  if (a.n_tiles > kMaxBlocks) return hipErrorInvalidValue;
-  const bool o32 = copy_offsets_fit(a);
-  if (a.K % kBK == 0) {
-    if constexpr (BM == 256 && WT == 0 && EPI == kEpiCloud) {
-      // (the one-wave kernels copy their first steps unconditionally: they
-      // need at least 6 or 2 steps; a zero-width slice takes the kernel below)
-      if (o32 && a.K >= 6 * kBK && (a.K / kBK) % 6 == 0) {
-        // one wave per SIMD, three weight stages (all 160 KB of LDS)
-        static std::atomic<uint64_t> lds_set_w3{0};
-        constexpr size_t lds_w = (size_t)5 * BM * kBK * 2;
-        hipError_t e = set_lds_limit_once(lds_set_w3, reinterpret_cast<const void*>(k_mfma_w1<EPI, 3>), lds_w);
-        if (e != hipSuccess) return e;
-        launch_kernel(k_mfma_w1<EPI, 3>, dim3(a.m_tiles * a.n_tiles), dim3(256), lds_w, s, a);
-        return hipGetLastError();
-      }
-      if (o32 && a.K >= 2 * kBK && (a.K / kBK) % 2 == 0) {
-        // one wave per SIMD (an even number of K steps)
-        static std::atomic<uint64_t> lds_set_w1{0};
-        constexpr size_t lds_w = mfma_dma_lds_bytes<BM, BN>();
-        hipError_t e = set_lds_limit_once(lds_set_w1, reinterpret_cast<const void*>(k_mfma_w1<EPI, 2>), lds_w);
-        if (e != hipSuccess) return e;
-        launch_kernel(k_mfma_w1<EPI, 2>, dim3(a.m_tiles * a.n_tiles), dim3(256), lds_w, s, a);
-        return hipGetLastError();
-      }
-    }
-    auto kd = WT == 0 ? (o32 ? k_mfma_dma<BM, BN, WM, WN, EPI, true> : k_mfma_dma<BM, BN, WM, WN, EPI, false>)
-                      : (o32 ? k_mfma_dma8<BM, BN, WM, WN, EPI, true> : k_mfma_dma8<BM, BN, WM, WN, EPI, false>);
-    constexpr size_t lds_d = WT == 0 ? mfma_dma_lds_bytes<BM, BN>() : mfma_dma8_lds_bytes<BM, BN>();
-    hipError_t e = set_lds_limit_once(o32 ? lds_set_dma : lds_set_dma64, reinterpret_cast<const void*>(kd), lds_d);
-    if (e != hipSuccess) return e;
-    launch_kernel(kd, dim3(a.m_tiles * a.n_tiles), dim3(NT), lds_d, s, a);
-    return hipGetLastError();
+  if (a.n_tiles > kMaxBlocks || a.K % (WT == 0 ? 8 : 16) != 0) return hipErrorInvalidValue;
+  const bool o32 = copy_offsets_fit(a), tail = a.K % kBK != 0;
+  if constexpr (BM == 256 && WT == 0 && EPI == kEpiCloud) {
+    // (the one-wave kernels copy their first steps unconditionally: they
+    // need at least 6 or 2 steps; fewer take the kernel below)
+    if (!tail && o32 && a.K >= 6 * kBK && (a.K / kBK) % 6 == 0)  // all 160 KB of LDS
+      return launch_w1<3>(a, (size_t)5 * BM * kBK * 2, s);
+    if (!tail && o32 && a.K >= 2 * kBK && (a.K / kBK) % 2 == 0)
+      return launch_w1<2>(a, mfma_dma_lds_bytes<BM, BN>(), s);
   }
-  // K not a multiple of the K step: the register-staged kernel (2 x 2 waves),
-  // which exists for 256-row tiles (the tile rule picks no other then)
-  if constexpr (BM == 256 && EPI != kEpiCloudQ) {
-    auto kern = k_mfma<BM, BN, WT, EPI>;
-    constexpr size_t lds = mfma_lds_bytes<BM, BN>();
-    hipError_t e = set_lds_limit_once(lds_set_reg, reinterpret_cast<const void*>(kern), lds);
-    if (e != hipSuccess) return e;
-    launch_kernel(kern, dim3(a.m_tiles * a.n_tiles), dim3(256), lds, s, a);
-    return hipGetLastError();
-  }
-  return hipErrorInvalidValue;
+  if (o32)
+    return tail ? launch_dma<BM, BN, WT, EPI, true, true>(a, s) : launch_dma<BM, BN, WT, EPI, true, false>(a, s);
+  return tail ? launch_dma<BM, BN, WT, EPI, false, true>(a, s) : launch_dma<BM, BN, WT, EPI, false, false>(a, s);
 }
 
 // Row tile for M rows (more than kStreamMaxRows): whichever of 256 and 320
-// pads M less (320-row tiles need K a multiple of the K step).  Measured on
+// pads M less.  Measured on
 // the batched shape (M = 320, 60000 ids): 320-row tiles, one per 256 ids,
 // 156 us against 265 us for 256-row tiles; M = 640 with fp8 weights: 460 us
 // against 537 us for 256-row tiles.
-static int mfma_bm(int M, int K) {
+static int mfma_bm(int M) {
   const int pad256 = (M + 255) / 256 * 256 - M;
   const int pad320 = (M + 319) / 320 * 320 - M;
-  return (K % kBK == 0 && pad320 < pad256) ? 320 : 256;
+  return pad320 < pad256 ? 320 : 256;
 }
 
 int mfma_n_tiles(int n) { return (n + kMfmaBN - 1) / kMfmaBN; }
 
 template <int WT, int EPI>
 static hipError_t launch_bm(const MfmaArgs& a, hipStream_t s) {
-  return mfma_bm(a.M, a.K) == 320 ? launch_tile<320, kMfmaBN, WT, EPI>(a, s)
+  return mfma_bm(a.M) == 320 ? launch_tile<320, kMfmaBN, WT, EPI>(a, s)
                                   : launch_tile<256, kMfmaBN, WT, EPI>(a, s);
 }
 
 // Cloud projection with the block quantiser in the epilogue, for the row
 // tile whose accumulators and row maxima fit in the registers together
-// (256 rows, K a multiple of the K step).  Where the tile rule picks
+// (256 rows).  Where the tile rule picks
 // 320 rows the separate quantiser is used: on 640 rows, 256-row tiles with
 // the fused quantiser ran 598 us against 428 + 43 us.
-bool mfma_quantises_in_epilogue(int M, int K) {
-  return K % kBK == 0 && mfma_bm(M, K) != 320;
-}
+bool mfma_quantises_in_epilogue(int M) { return mfma_bm(M) != 320; }
 
 template <int WT>
 static hipError_t launch_bm_q(const MfmaArgs& a, hipStream_t s) {
-  if (!mfma_quantises_in_epilogue(a.M, a.K)) return hipErrorInvalidValue;
+  if (!mfma_quantises_in_epilogue(a.M)) return hipErrorInvalidValue;
   return launch_tile<256, kMfmaBN, WT, kEpiCloudQ>(a, s);
 }
 

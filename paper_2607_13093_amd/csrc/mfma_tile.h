@@ -27,7 +27,6 @@ __device__ __forceinline__ unsigned long long argmax_key_m(float v, int pos) {
 }
 
 constexpr int kBK = 64;          // K elements per staged step
-constexpr int kLDK = kBK + 8;    // padded LDS row, bf16 elements (144 bytes)
 constexpr int kGM = 8;           // m-tiles grouped per n-tile in the tile order
 
 __device__ __forceinline__ void tile_of_block(int b, int m_tiles, int n_tiles, int& mt, int& nt) {

@@ -432,7 +432,7 @@ int sph_cloud_partial_fmt(const void* h_cloud, int64_t ldh, int64_t M, int64_t d
     a.bias = bias;
     a.clip = clip_c;
     const bool few = M <= sph::kStreamMaxRows;
-    if (!few && block == sph::kMfmaBN && sph::mfma_quantises_in_epilogue((int)M, (int)d_cloud)) {
+    if (!few && block == sph::kMfmaBN && sph::mfma_quantises_in_epilogue((int)M)) {
       // a scale block is one 256-position tile: the projection's epilogue
       // quantises from its accumulators, z is written only on request
       a.z = z_out;

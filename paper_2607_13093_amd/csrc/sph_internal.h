@@ -135,7 +135,7 @@ int stream_width(int n);
 hipError_t launch_stream(int wtype, MfmaArgs a, hipStream_t s);
 hipError_t launch_fuse_mfma(const MfmaArgs& a, hipStream_t s);
 // true where the cloud projection can quantise blocks of 256 positions in its epilogue
-bool mfma_quantises_in_epilogue(int M, int K);
+bool mfma_quantises_in_epilogue(int M);
 int mfma_n_tiles(int n);
 
 // Clip + quantise z [M, n] to b-bit codes (bits 8 or 4; 4-bit codes two per

@@ -119,3 +119,28 @@ def test_sampling_few_long_rows(shape):
                         top_p=top_p, seed=n,
                         workspace=torch.empty((base - 256,), dtype=torch.uint8, device="cuda"))
     sub.close()
+
+
+# (sessions, R, d_cloud, n): partial K steps and ragged edges of the 256- and
+# 320-row tiles (193 rows and more), one chunk to a few steps
+TILES = [
+    (193, 1, 8, 300),
+    (64, 4, 72, 513),     # 256 rows, every row of the tile
+    (52, 5, 200, 255),    # 260 rows: 320-row tile
+    (64, 5, 312, 1025),   # 320 rows, one position past the tiles
+    (57, 9, 456, 770),    # 513 rows: 640 by 320-row tiles
+    (37, 7, 1000, 256),   # 259 rows, one whole tile of positions
+]
+
+
+@pytest.mark.parametrize("fmt", [(8, 0), (4, 256)], ids=["b8", "b4blk256"])
+@pytest.mark.parametrize("wtype", ["bf16", "fp8"])
+@pytest.mark.parametrize("shape", TILES, ids=[f"S{s}R{r}dc{c}n{n}" for s, r, c, n in TILES])
+def test_tiled_cloud_projection_partial_steps(shape, wtype, fmt):
+    S, R, dc, n = shape
+    if wtype == "fp8":
+        dc = -(-dc // 16) * 16
+    cfg = Config("tiles", 800 + sum(shape) % 1000, d=dc + 8, d_end=8, vocab=n + 33, n_sub=n,
+                 subset_kind="choice", sessions=S, rows_per_session=R, wtype=wtype,
+                 with_bias=S % 2 == 1)
+    run_format_case(make_workload(cfg), fmt[0], fmt[1], f"tiles {shape} {wtype} {fmt}")
