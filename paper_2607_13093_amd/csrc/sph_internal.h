@@ -173,16 +173,17 @@ hipError_t launch_widen_codes(const int8_t* hq, int64_t ldhq, int M, int K, int 
 // AES-GCM of payload rows (gcm.hip).  A key's device image holds the T0
 // table (1 KB), the S-box (256 B), the round keys (at kGcmRkOffset), the
 // powers H^0 .. H^kGcmMaxPow of the hash key (16 B each, at kGcmPowOffset)
-// and, at kGcmTabOffset, the product by G = H^kGcmStride as 32 nibble
-// tables: entry [p][v] (16 B) is G times the block whose nibble p (from the
-// most significant end) is v and whose other bits are zero.
+// and, at kGcmTabOffset, the product by H^64 as 32 nibble tables: entry [p][v]
+// (16 B) is H^64 times the block whose nibble p (from the most significant
+// end) is v and whose other bits are zero.
 constexpr int kGcmMaxPow = 16384;  // AAD + ciphertext + length blocks of one message
 constexpr int kGcmRkOffset = 1280;
 constexpr int kGcmPowOffset = 1536;
-constexpr int kGcmStride = 256;    // blocks between the terms one thread chains
-constexpr int kGcmMaxChain = 16;   // blocks one thread chains at most
+constexpr int kGcmStride = 256;    // a partial sum covers kGcmStride * gcm_chain blocks of a row
+constexpr int kGcmMaxChain = 16;
 constexpr size_t kGcmTabOffset = (size_t)kGcmPowOffset + (size_t)(kGcmMaxPow + 1) * 16;
-constexpr size_t kGcmImageBytes = kGcmTabOffset + 32 * 16 * 16;
+constexpr size_t kGcmTabBytes = 32 * 16 * 16;
+constexpr size_t kGcmImageBytes = kGcmTabOffset + kGcmTabBytes;
 bool gcm_key_setup(const uint8_t* key, int key_bytes, std::vector<uint8_t>& dev_image, int& nr);
 // A message row is the concatenation of up to kGcmMaxSegs segments: bytes
 // [end[k-1], end[k]) of row r come from in[k] + r * ld_in[k] and go to
@@ -198,19 +199,18 @@ struct GcmSegs {
   int nseg;
 };
 constexpr int kGcmMaxAad = 1024;  // bytes of associated data per message
-// Blocks each thread chains for a batch of rows messages of n data blocks:
-// 1 while the batch has few blocks (parallelism first), up to kGcmMaxChain
-// for large batches.
+// Partial sums of a batch of rows messages of n data blocks: one for each
+// kGcmStride * gcm_chain blocks of a row, so that their number stays near 128
+// (and the workspace small) up to large batches.
 inline int gcm_chain(int64_t rows, int64_t n) {
   const int64_t k = (rows * n + 32767) / 32768;
   return (int)(k < 1 ? 1 : (k > kGcmMaxChain ? kGcmMaxChain : k));
 }
-// Workgroups (of kGcmStride threads) per message of n data blocks and na
-// AAD blocks.  The last na + 2 threads of workgroup *extra_part take the
-// AAD blocks, the length block and E_K(J0): the last data workgroup, unless
-// threads chain single blocks (a latency-bound batch) and it has fewer than
-// na + 2 threads without a block; then one more workgroup.  (Adding a
-// workgroup per row to a large batch would double its grid.)
+// Partial sums per message of n data blocks and na AAD blocks.  The AAD blocks,
+// the length block and E_K(J0) go to sum *extra_part: the last one of data,
+// unless a sum covers kGcmStride blocks only (a latency-bound batch) and the
+// last covers more than kGcmStride - na - 2; then one more.  (A sum more per row
+// of a large batch would double their number.)
 inline int gcm_parts(int64_t n, int64_t na, int chain, int* extra_part = nullptr) {
   const int64_t per = (int64_t)kGcmStride * chain;
   const int64_t nd = (n + per - 1) / per;

@@ -4,8 +4,12 @@ subsets that end one position into a tile, and payload rows at every
 alignment, through the staged checks of tests/parity.py against the oracle.
 """
 
+import numpy as np
 import pytest
+import torch
 
+import paper_2607_13093_amd as sph
+from oracle import gcm as ogcm
 from synth import Config, make_workload
 
 from test_gpu_payload import run_format_case
@@ -144,3 +148,49 @@ def test_tiled_cloud_projection_partial_steps(shape, wtype, fmt):
                  subset_kind="choice", sessions=S, rows_per_session=R, wtype=wtype,
                  with_bias=S % 2 == 1)
     run_format_case(make_workload(cfg), fmt[0], fmt[1], f"tiles {shape} {wtype} {fmt}")
+
+
+# (key bytes, rows, segment bytes, aad bytes): batches whose lanes chain blocks
+# (the last piece of a row full, one block, a few), short rows in large numbers,
+# blocks over two and three segments, and sums whose workgroup has no thread
+# left for the other terms
+SEALED = [
+    (32, 520, (5, 2, 3), 7),       # 520 rows of one block over three segments
+    (16, 520, (0,), 33),           # no data
+    (32, 130, (16381, 4), 20),     # 1025 blocks a row, chained
+    (16, 33, (65535, 9), 0),       # 4097
+    (16, 41, (30007, 20008), 16),  # a boundary inside a block, a ragged end
+    (32, 24, (49153, 4), 1024),    # 768 threads, the largest AAD beside one block
+    (16, 40, (49136,), 1024),      # 1024 threads, 1023 blocks in the last sum: a second pass
+]
+
+
+@pytest.mark.parametrize("case", SEALED, ids=[f"k{k}r{r}L{'_'.join(map(str, b))}a{a}" for k, r, b, a in SEALED])
+def test_sealed_batches(case):
+    """A batch's rows equal the same rows sealed one at a time (and the oracle),
+    and open; a changed byte fails its row alone."""
+    klen, rows, seg, la = case
+    rng = np.random.default_rng(rows + sum(seg) + la)
+    key = sph.GcmKey(k := rng.bytes(klen))
+    x = [rng.integers(0, 256, (rows, b), dtype=np.uint8) for b in seg]
+    iv = rng.integers(0, 256, (rows, 12), dtype=np.uint8)
+    aad = rng.integers(0, 256, (rows, la), dtype=np.uint8)
+    dx, div = [torch.from_numpy(a).cuda() for a in x], torch.from_numpy(iv).cuda()
+    daad = torch.from_numpy(aad).cuda() if la else None
+    ct, tag = sph.gcm_seal_segments(key, dx, div, daad)
+    for r in sorted({0, 1, rows // 2, rows - 1}):
+        one, t1 = sph.gcm_seal_segments(key, [a[r:r + 1] for a in dx], div[r:r + 1], daad[r:r + 1] if la else None)
+        assert torch.equal(t1, tag[r:r + 1]), r
+        for a, b in zip(one, ct):
+            assert torch.equal(a, b[r:r + 1]), r
+    ref, tref = ogcm.seal_rows(k, np.concatenate([a[-1:] for a in x], 1), iv[-1:], aad[-1:])
+    np.testing.assert_array_equal(torch.cat(list(ct), 1)[-1:].cpu().numpy(), ref)
+    np.testing.assert_array_equal(tag[-1:].cpu().numpy(), tref)
+    bad = rows // 3
+    tag[bad, 5] ^= 1
+    pt, ok = sph.gcm_open_segments(key, ct, div, tag, daad)
+    for a, b in zip(pt, dx):
+        assert torch.equal(a, b)
+    want = torch.ones_like(ok)
+    want[bad] = 0
+    assert torch.equal(ok, want)
