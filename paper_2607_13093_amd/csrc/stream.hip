@@ -159,7 +159,8 @@ void k_mfma_stream(const MfmaArgs a) {
   constexpr int NW = stream_waves(BM), NT = 64 * NW;
   constexpr int FR = BM / 32;  // row fragments, over as many waves as divide them
   constexpr int WN = BN == 64 ? 2 : BN == 128 ? 4 : (NW == 8 && FR % 2) ? 8 : 4;
-  constexpr int WM = FR % (NW / WN) == 0 ? NW / WN : FR % 2 == 0 && NW / WN >= 2 ? 2 : 1;
+  constexpr int WX = NW / WN;
+  constexpr int WM = FR % WX == 0 ? WX : FR % 3 == 0 && WX > 3 ? 3 : FR % 2 == 0 && WX > 2 ? 2 : 1;
   constexpr int WROWS = BM / WM, WCOLS = BN / WN;        // rows and positions of a wave
   constexpr int BK = WT == 0 ? 64 : 128;                 // columns per stage
   constexpr int FM = WROWS / 32, FN = WCOLS / 32;
@@ -477,25 +478,30 @@ static hipError_t launch_stream_bm(const MfmaArgs& a, hipStream_t s) {
   }
 }
 
+// Blocks of at most 128 positions have more than one row of waves: 3 and 5
+// row fragments, which it does not divide, run as 4 and 6 (but 3 over four
+// rows of waves, at most 64 positions).  155 rows x 16000 x 3584 columns 85 ->
+// 54 us, x 30000 x 4000 102 -> 78; 90 x 30000 x 3584 64 -> 56.
+template <int WT>
+static hipError_t launch_stream_rows(const MfmaArgs& a, hipStream_t s) {
+  int fr = (a.M + 31) / 32;
+  if (a.width <= 128 && (fr == 5 || (fr == 3 && a.width > 64))) ++fr;
+  switch (fr) {
+    case 1: return launch_stream_bm<32, WT>(a, s);
+    case 2: return launch_stream_bm<64, WT>(a, s);
+    case 3: return launch_stream_bm<96, WT>(a, s);
+    case 4: return launch_stream_bm<128, WT>(a, s);
+    case 5: return launch_stream_bm<160, WT>(a, s);
+    default: return launch_stream_bm<192, WT>(a, s);
+  }
+}
+
 hipError_t launch_stream(int wtype, MfmaArgs a, hipStream_t s) {
   a.width = stream_width(a.n);
   const int blocks = (a.n + a.width - 1) / a.width;
   if (a.M < 1 || a.M > kStreamMaxRows || blocks > kMaxBlocks || a.K % (wtype == 0 ? 8 : 16) != 0)
     return hipErrorInvalidValue;
-  if (wtype == 0) {
-    if (a.M <= 32) return launch_stream_bm<32, 0>(a, s);
-    if (a.M <= 64) return launch_stream_bm<64, 0>(a, s);
-    if (a.M <= 96) return launch_stream_bm<96, 0>(a, s);
-    if (a.M <= 128) return launch_stream_bm<128, 0>(a, s);
-    if (a.M <= 160) return launch_stream_bm<160, 0>(a, s);
-    return launch_stream_bm<192, 0>(a, s);
-  }
-  if (a.M <= 32) return launch_stream_bm<32, 1>(a, s);
-  if (a.M <= 64) return launch_stream_bm<64, 1>(a, s);
-  if (a.M <= 96) return launch_stream_bm<96, 1>(a, s);
-  if (a.M <= 128) return launch_stream_bm<128, 1>(a, s);
-  if (a.M <= 160) return launch_stream_bm<160, 1>(a, s);
-  return launch_stream_bm<192, 1>(a, s);
+  return wtype == 0 ? launch_stream_rows<0>(a, s) : launch_stream_rows<1>(a, s);
 }
 
 }  // namespace sph

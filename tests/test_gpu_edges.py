@@ -53,6 +53,10 @@ STREAM = [
     (32, 5, 960, 65537),  # 160 rows, two rounds
     (23, 7, 152, 45001),  # 161 rows
     (24, 8, 64, 300),     # 192 rows, one whole step
+    (19, 5, 264, 24000),  # 95 rows, 94 positions per block
+    (23, 4, 200, 9001),   # 92 rows, 36
+    (31, 5, 136, 31000),  # 155 rows, 122
+    (35, 5, 328, 14000),  # 175 rows, 55
 ]
 
 
