@@ -938,6 +938,7 @@ static int mfma_bm(int M) {
 }
 
 int mfma_n_tiles(int n) { return (n + kMfmaBN - 1) / kMfmaBN; }
+int mfma_tiles(int M, int n) { return (M + mfma_bm(M) - 1) / mfma_bm(M) * mfma_n_tiles(n); }
 
 template <int WT, int EPI>
 static hipError_t launch_bm(const MfmaArgs& a, hipStream_t s) {

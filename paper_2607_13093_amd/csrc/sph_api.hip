@@ -431,7 +431,7 @@ int sph_cloud_partial_fmt(const void* h_cloud, int64_t ldh, int64_t M, int64_t d
     a.n = (int)n;
     a.bias = bias;
     a.clip = clip_c;
-    const bool few = M <= sph::kStreamMaxRows;
+    const bool few = sph::stream_groups((int)M, (int)n) > 0;
     if (!few && block == sph::kMfmaBN && sph::mfma_quantises_in_epilogue((int)M)) {
       // a scale block is one 256-position tile: the projection's epilogue
       // quantises from its accumulators, z is written only on request
@@ -451,7 +451,7 @@ int sph_cloud_partial_fmt(const void* h_cloud, int64_t ldh, int64_t M, int64_t d
       return few ? sph::launch_stream(wtype, a, s) : sph::launch_mfma(sph::kEpiCloud, wtype, a, s);
     });
     if (e != hipSuccess) return hip_fail(e, "cloud projection launch");
-    const int w = sph::stream_width((int)n);
+    const int w = sph::stream_width((int)M, (int)n);
     nblk = few ? (int)((n + w - 1) / w) : sph::mfma_n_tiles((int)n);
   } else {
     int mr = sph::kGemvMaxRows;

@@ -89,7 +89,7 @@ struct MfmaArgs {
   const float* wscale;    // fp32 [V] for fp8 weights, else null
   const int32_t* ids;     // subset ids [n]
   int n;
-  int m_tiles, n_tiles;   // set by the launcher
+  int m_tiles, n_tiles;   // set by the launcher (streaming kernel: m_tiles row groups)
   int width;              // streaming kernel: positions per block, set by its launcher
   // cloud epilogue
   const float* bias;
@@ -129,14 +129,17 @@ constexpr int kCUs = 256;             // compute units of an MI355X
 // x 3840 columns: 192 rows 124 us against 142 for a 256-row tile, 256 rows 149
 // against 135.
 constexpr int kStreamMaxRows = 192;
-// Few rows (kGemvMaxRows < M <= kStreamMaxRows): row maxima go to slot j /
-// stream_width(n), one per block of positions.
-int stream_width(int n);
+// Row groups of the streaming kernel for M > kGemvMaxRows rows and n positions
+// (1 up to kStreamMaxRows; 0: launch_mfma).  Row maxima go to slot j /
+// stream_width(M, n), one per block of positions.
+int stream_groups(int M, int n);
+int stream_width(int M, int n);
 hipError_t launch_stream(int wtype, MfmaArgs a, hipStream_t s);
 hipError_t launch_fuse_mfma(const MfmaArgs& a, hipStream_t s);
 // true where the cloud projection can quantise blocks of 256 positions in its epilogue
 bool mfma_quantises_in_epilogue(int M);
 int mfma_n_tiles(int n);
+int mfma_tiles(int M, int n);  // all tiles of the cloud projection
 
 // Clip + quantise z [M, n] to b-bit codes (bits 8 or 4; 4-bit codes two per
 // byte, low nibble first) with one scale per row (qshift < 0: from the

@@ -1,4 +1,5 @@
-// Cloud projection of 9 to 192 rows (MFMA path, HBM bound).
+// Cloud projection of 9 to 192 rows (MFMA path, HBM bound), and of up to 1024
+// over few positions in groups of at most 192 (stream_groups).
 //
 //   C[m, j] = sum_k h[m, k] * W[S_j, k]      (eq. 12 on the subset S)
 //
@@ -175,8 +176,18 @@ void k_mfma_stream(const MfmaArgs a) {
   uint32_t* s_rmax = reinterpret_cast<uint32_t*>(smem);  // once the stages are read
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int nt = blockIdx.x, n0 = nt * a.width, w = min(a.width, a.n - n0);
-  const int M = a.M, K = a.K, n = a.n;
+  // the row groups of a share of positions run next to each other on one XCD
+  int nt = blockIdx.x, m0 = 0, M = a.M;
+  const int K = a.K, n = a.n;
+  if (a.m_tiles > 1) {
+    const int c = nt / (8 * a.m_tiles), r = nt - c * 8 * a.m_tiles, shares = (n + a.width - 1) / a.width;
+    const int in = min(8, shares - c * 8), per = (M + a.m_tiles - 1) / a.m_tiles;
+    nt = c * 8 + r % in;
+    m0 = r / in * per;
+    M = min(per, M - m0);
+  }
+  const uint16_t* h = a.h + (int64_t)m0 * a.ldh;
+  const int n0 = nt * a.width, w = min(a.width, n - n0);
   const int nsteps = (K + BK - 1) / BK;
   const int kch = K / (WT == 0 ? 8 : 16);  // 16-byte chunks of a weight row
   // rows start on a line, or stages t and t + 1 hold the columns of step t
@@ -207,7 +218,7 @@ void k_mfma_stream(const MfmaArgs a) {
 #pragma unroll
   for (int i = 0; i < A_INS; ++i) {
     const int g = acp(i) * 8, r = g % BM + lr, p = g / BM;
-    pa[i] = reinterpret_cast<const uint8_t*>(a.h) + (int64_t)min(r, M - 1) * a.ldh * 2 + p * 128 + chunk_of(r) * 16;
+    pa[i] = reinterpret_cast<const uint8_t*>(h) + (int64_t)min(r, M - 1) * a.ldh * 2 + p * 128 + chunk_of(r) * 16;
   }
   // h of a step / line of the weights into a stage; lanes without a chunk
   // there (before the row's start, at or past its end) read the nearest one
@@ -393,7 +404,7 @@ void k_mfma_stream(const MfmaArgs a) {
 #pragma unroll
     for (int t = 0; t < P; ++t) red[t] = 0.0f;
     const float clip = a.clip;
-    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(scalar_ptr(a.z)), 0,
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(scalar_ptr(a.z + (int64_t)m0 * n)), 0,
                                                         (int)((uint32_t)M * (uint32_t)n * 4u), 0x00020000);
 #pragma unroll
     for (int j = 0; j < FN; ++j) {
@@ -430,7 +441,7 @@ void k_mfma_stream(const MfmaArgs a) {
   }
   __syncthreads();
   for (int i = tid; i < BM; i += NT)
-    if (i < M) a.amax_part[(int64_t)i * kMaxBlocks + nt] = __uint_as_float(s_rmax[i]);
+    if (i < M) a.amax_part[(int64_t)(m0 + i) * kMaxBlocks + nt] = __uint_as_float(s_rmax[i]);
 #endif
 }
 
@@ -444,15 +455,31 @@ static hipError_t launch_stream_tile(const MfmaArgs& a, hipStream_t s) {
   auto k = k_mfma_stream<BM, BN, WT, RA, RW>;
   hipError_t e = set_lds_limit_once(lds_set, reinterpret_cast<const void*>(k), most);
   if (e != hipSuccess) return e;
-  launch_kernel(k, dim3((a.n + a.width - 1) / a.width), dim3(64 * stream_waves(BM)), lds, s, a);
+  launch_kernel(k, dim3((a.n + a.width - 1) / a.width * a.m_tiles), dim3(64 * stream_waves(BM)), lds, s, a);
   return hipGetLastError();
 }
 
-// Positions per block: an equal share for every CU, in as many rounds as 256
-// positions per block need, at least 32 (a fragment).
-int stream_width(int n) {
-  const int rounds = (n + kCUs * 256 - 1) / (kCUs * 256);
-  const int w = (n + kCUs * rounds - 1) / (kCUs * rounds);
+// Row groups of the streaming kernel, 0 where the tiles of launch_mfma are the
+// faster way.  More than kStreamMaxRows rows are split into 2, 4 or 8 groups
+// (the CUs divide evenly) where 256-position tiles would leave half of the CUs
+// or more without work and the groups' shares fit one round.  (us, tiles /
+// groups, K 3584 ... 4032: 256 rows x 8000 69 / 42, 320 x 15000 99 / 65, 320 x
+// 30000 103 / 93, 400 x 16000 85 / 75, 640 x 8000 88 / 64, 640 x 16000 107 /
+// 100, 1024 x 8000 83 / 76, E4M3 268 x 30000 116 / 93, 512 x 8000 83 / 47; past
+// the rule 384 x 32000 105 / 111, 768 x 16000 95 / 103, 1280 x 6000 78 / 85.)
+int stream_groups(int M, int n) {
+  if (M <= kStreamMaxRows) return 1;
+  int g = 2;
+  while (g * kStreamMaxRows < M) g *= 2;
+  return M <= 1024 && mfma_tiles(M, n) <= kCUs / 2 && (int64_t)n * g <= kCUs * 256 ? g : 0;
+}
+
+// Positions per block: an equal share for every CU of a row group, in as many
+// rounds as 256 positions per block need, at least 32 (a fragment).
+int stream_width(int M, int n) {
+  const int cus = kCUs / std::max(1, stream_groups(M, n));
+  const int rounds = (n + cus * 256 - 1) / (cus * 256);
+  const int w = (n + cus * rounds - 1) / (cus * rounds);
   return w < 32 ? 32 : w;
 }
 
@@ -484,7 +511,7 @@ static hipError_t launch_stream_bm(const MfmaArgs& a, hipStream_t s) {
 // 54 us, x 30000 x 4000 102 -> 78; 90 x 30000 x 3584 64 -> 56.
 template <int WT>
 static hipError_t launch_stream_rows(const MfmaArgs& a, hipStream_t s) {
-  int fr = (a.M + 31) / 32;
+  int fr = ((a.M + a.m_tiles - 1) / a.m_tiles + 31) / 32;
   if (a.width <= 128 && (fr == 5 || (fr == 3 && a.width > 64))) ++fr;
   switch (fr) {
     case 1: return launch_stream_bm<32, WT>(a, s);
@@ -497,9 +524,10 @@ static hipError_t launch_stream_rows(const MfmaArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_stream(int wtype, MfmaArgs a, hipStream_t s) {
-  a.width = stream_width(a.n);
+  a.width = stream_width(a.M, a.n);
+  a.m_tiles = stream_groups(a.M, a.n);
   const int blocks = (a.n + a.width - 1) / a.width;
-  if (a.M < 1 || a.M > kStreamMaxRows || blocks > kMaxBlocks || a.K % (wtype == 0 ? 8 : 16) != 0)
+  if (a.M < 1 || a.m_tiles < 1 || blocks > kMaxBlocks || a.K % (wtype == 0 ? 8 : 16) != 0)
     return hipErrorInvalidValue;
   return wtype == 0 ? launch_stream_rows<0>(a, s) : launch_stream_rows<1>(a, s);
 }

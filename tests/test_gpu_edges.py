@@ -129,15 +129,27 @@ def test_sampling_few_long_rows(shape):
     sub.close()
 
 
-# (sessions, R, d_cloud, n): partial K steps and ragged edges of the 256- and
-# 320-row tiles (193 rows and more), one chunk to a few steps
+# (sessions, R, d_cloud, n): partial K steps and ragged edges, first of the row
+# groups of the streaming kernel (193 to 1024 rows over few positions), then of
+# the 256- and 320-row tiles
 TILES = [
-    (193, 1, 8, 300),
-    (64, 4, 72, 513),     # 256 rows, every row of the tile
-    (52, 5, 200, 255),    # 260 rows: 320-row tile
-    (64, 5, 312, 1025),   # 320 rows, one position past the tiles
-    (57, 9, 456, 770),    # 513 rows: 640 by 320-row tiles
-    (37, 7, 1000, 256),   # 259 rows, one whole tile of positions
+    (193, 1, 8, 300),      # groups of 97 and 96 rows, 32 positions per block
+    (64, 4, 72, 513),      # two groups of 128
+    (52, 5, 200, 255),     # 260 rows, fewer shares than one XCD group
+    (64, 5, 312, 1025),
+    (57, 9, 456, 770),     # 513 rows: four groups
+    (37, 7, 1000, 256),    # 259 rows
+    (97, 4, 136, 16384),   # 388 rows: four groups, 256 positions per block
+    (205, 1, 88, 32768),   # 205 rows: two groups, the last positions of the rule
+    (1021, 1, 264, 333),   # eight groups, the last one short
+    (257, 4, 8, 300),      # 1028 rows: 256-row tiles, one chunk
+    (320, 4, 72, 513),     # 1280 rows, every row of the tiles
+    (260, 6, 200, 255),    # 1560 rows: 320-row tiles
+    (400, 4, 312, 1025),   # 1600 rows, one position past the tiles
+    (391, 4, 456, 770),    # 1564 rows: 320-row tiles
+    (257, 5, 1000, 256),   # 1285 rows, one whole tile of positions
+    (257, 4, 256, 300),    # two whole steps at a time
+    (258, 4, 384, 513),    # six
 ]
 
 
@@ -151,7 +163,8 @@ def test_tiled_cloud_projection_partial_steps(shape, wtype, fmt):
     cfg = Config("tiles", 800 + sum(shape) % 1000, d=dc + 8, d_end=8, vocab=n + 33, n_sub=n,
                  subset_kind="choice", sessions=S, rows_per_session=R, wtype=wtype,
                  with_bias=S % 2 == 1)
-    run_format_case(make_workload(cfg), fmt[0], fmt[1], f"tiles {shape} {wtype} {fmt}")
+    sessions = None if S * R * n < 2_000_000 else [0, S // 2, S - 1]
+    run_format_case(make_workload(cfg), fmt[0], fmt[1], f"tiles {shape} {wtype} {fmt}", sessions=sessions)
 
 
 # (key bytes, rows, segment bytes, aad bytes): batches whose lanes chain blocks
