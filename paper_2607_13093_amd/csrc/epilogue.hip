@@ -158,29 +158,33 @@ __device__ __forceinline__ unsigned long long shfl_xor_u64(unsigned long long x,
 constexpr int kMaxRowsPerSession = 1024;
 constexpr int kFinalWaves = 16;  // rows of a session reduced in parallel
 
-// One block per session, one wave per verification row: fold the row's
+// One block per session, WPR waves per verification row: fold the row's
 // per-block argmax keys (every lane loads its share of up to kMaxBlocks keys
 // at once) into the greedy token, ties to the lowest subset position = the
 // lowest id; then count the drafts that match the verification rows in
 // order (Section 5.5, Algorithm 1 verification step).
+template <int WPR>
 __global__ __launch_bounds__(64 * kFinalWaves) void k_final_greedy(
     const unsigned long long* __restrict__ best, int nblk, const int32_t* __restrict__ ids, int n,
     int R, const int32_t* __restrict__ drafts, int32_t* __restrict__ tokens,
     int32_t* __restrict__ accept) {
-  constexpr int PER_LANE = kMaxBlocks / 64;
+  constexpr int PER_LANE = kMaxBlocks / 64 / WPR, RP = kFinalWaves / WPR;
   const int s = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  __shared__ unsigned long long s_key[kMaxRowsPerSession];
   __shared__ int32_t s_tok[kMaxRowsPerSession];
   __shared__ int32_t s_draft[kMaxRowsPerSession];
   // the session's drafts are staged while the keys are read, so the prefix
   // match below reads LDS only
   for (int r = tid; r < R - 1; r += blockDim.x) s_draft[r] = drafts[(int64_t)s * (R - 1) + r];
-  for (int r = wave; r < R; r += kFinalWaves) {
+  for (int r = tid; r < R; r += blockDim.x) s_key[r] = 0ull;
+  __syncthreads();
+  for (int r = wave / WPR; r < R; r += RP) {
     const int64_t m = (int64_t)s * R + r;
     unsigned long long x[PER_LANE];
 #pragma unroll
     for (int t = 0; t < PER_LANE; ++t) {
-      const int i = lane + 64 * t;
+      const int i = (wave % WPR + WPR * t) * 64 + lane;
       x[t] = i < nblk ? best[m * kMaxBlocks + i] : 0ull;
     }
     unsigned long long k = x[0];
@@ -191,14 +195,16 @@ __global__ __launch_bounds__(64 * kFinalWaves) void k_final_greedy(
       const unsigned long long y = shfl_xor_u64(k, o);
       k = y > k ? y : k;
     }
-    if (lane == 0) {
-      // every position of the row produced a key, so pos < n; the clamp only
-      // keeps a corrupted key from reading outside the id table
-      const uint32_t pos = min(0xFFFFFFFFu - (uint32_t)k, (uint32_t)(n - 1));
-      const int32_t tok = ids[pos];
-      tokens[m] = tok;
-      s_tok[r] = tok;
-    }
+    if (lane == 0) atomicMax(&s_key[r], k);
+  }
+  __syncthreads();
+  for (int r = tid; r < R; r += blockDim.x) {
+    // every position of the row produced a key, so pos < n; the clamp only
+    // keeps a corrupted key from reading outside the id table
+    const uint32_t pos = min(0xFFFFFFFFu - (uint32_t)s_key[r], (uint32_t)(n - 1));
+    const int32_t tok = ids[pos];
+    tokens[(int64_t)s * R + r] = tok;
+    s_tok[r] = tok;
   }
   __syncthreads();
   if (tid == 0) {
@@ -213,10 +219,13 @@ hipError_t launch_final_greedy(const uint64_t* best_part, int nblk, const int32_
                                int n_sessions, int R, const int32_t* drafts, int32_t* tokens,
                                int32_t* accept, hipStream_t s) {
   if (R > kMaxRowsPerSession || n < 1 || nblk > kMaxBlocks) return hipErrorInvalidValue;
-  const int waves = R < kFinalWaves ? R : kFinalWaves;
-  launch_kernel(k_final_greedy, dim3(n_sessions), dim3(64 * waves), 0, s,
-                     reinterpret_cast<const unsigned long long*>(best_part), nblk, ids, n, R,
-                     drafts, tokens, accept);
+  // rows of few-row sessions take several waves each
+  const int wpr = R <= kFinalWaves / 4 ? 4 : R <= kFinalWaves / 2 ? 2 : 1;
+  const int waves = R * wpr < kFinalWaves ? R * wpr : kFinalWaves;
+  auto kern = wpr == 4 ? k_final_greedy<4> : wpr == 2 ? k_final_greedy<2> : k_final_greedy<1>;
+  launch_kernel(kern, dim3(n_sessions), dim3(64 * waves), 0, s,
+                reinterpret_cast<const unsigned long long*>(best_part), nblk, ids, n, R, drafts, tokens,
+                accept);
   return hipGetLastError();
 }
 

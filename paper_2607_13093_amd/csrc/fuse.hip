@@ -32,10 +32,10 @@ __device__ __forceinline__ u32x4_t load_chunk16(const uint8_t* p, int64_t left) 
 // order that puts subset position 16*(l/32) + r of the group in accumulator
 // r of lane l: a lane holds 16 consecutive positions of row j*32 + l%32 (in
 // the wave's tile) per fragment.  Operands are otherwise staged exactly as
-// in k_mfma_dma.  A BM x 256 tile runs WNN x WMM waves (WNN along the
+// in k_mfma_dma.  A BM x BN tile runs WNN x WMM waves (WNN along the
 // positions, WMM along the rows).
 //
-// Payload: the tile's codes (BM rows of 256 * qbits / 8 bytes) are staged
+// Payload: the tile's codes (BM rows of BN * qbits / 8 bytes) are staged
 // in LDS as 16-byte chunks, swizzled per row, so one 16-byte read gives a
 // lane its 16 8-bit codes (an 8-byte read its 16 4-bit codes) and the rows
 // a read touches spread over the banks.  With 8-bit codes on 16-byte
@@ -60,25 +60,24 @@ __device__ __forceinline__ u32x4_t load_chunk16(const uint8_t* p, int64_t left) 
 // with 8 K steps a tile's prologue and epilogue weigh more than the LDS
 // traffic the larger wave tiles save (dense_full 379-396 against 350-364 us,
 // dense_sub 87 against 76).
-template <int BM, int WNN, int WMM>
+template <int BM, int BN>
 constexpr size_t fuse_dma_lds_bytes() {
-  return (size_t)2 * (BM + kMfmaBN) * kBK * 2 + (size_t)kMfmaBN * 4 + (size_t)2 * BM * 4 +
-         (size_t)BM * 8;
+  return (size_t)2 * (BM + BN) * kBK * 2 + (size_t)BN * 4 + (size_t)2 * BM * 4 + (size_t)BM * 8;
 }
 
-template <int BM, int WNN, int WMM, bool O32, bool TAIL>
+template <int BM, int BN, int WNN, int WMM, int BPC, bool O32, bool TAIL>
 __global__ __launch_bounds__(64 * WNN * WMM)
-__attribute__((amdgpu_waves_per_eu(WNN * WMM / 4, WNN * WMM / 4)))
+__attribute__((amdgpu_waves_per_eu(WNN * WMM / 4 * BPC, WNN * WMM / 4 * BPC)))
 void k_fuse_dma(const MfmaArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  constexpr int BN = kMfmaBN, NT = 64 * WNN * WMM;
+  constexpr int NT = 64 * WNN * WMM;
   constexpr int FI = BN / WNN / 32, FJ = BM / WMM / 32;  // position / row fragments per wave
   static_assert(FI * WNN * 32 == BN && FJ * WMM * 32 == BM, "wave grid");
   constexpr int IW = 4;  // waves issuing the operand copies (one per SIMD)
   constexpr int A_INS = BM / 8 / IW, B_INS = BN / 8 / IW;
   static_assert(A_INS * 8 * IW == BM && B_INS * 8 * IW == BN, "copy instructions");
   constexpr int STAGE_B = (BM + BN) * kBK * 2;  // bytes of one operand stage
-  constexpr bool kLastStep = BM * BN <= STAGE_B && BM <= BN;  // 8-bit tile fits in one stage
+  constexpr bool kLastStep = BM <= 256;  // an 8-bit tile's halves fit the two buffers of a stage
   extern __shared__ __align__(16) uint8_t smem[];
   uint16_t* As = reinterpret_cast<uint16_t*>(smem);                 // [2][BM][64]
   uint16_t* Bs = As + 2 * BM * kBK;                                  // [2][BN][64]
@@ -157,9 +156,12 @@ void k_fuse_dma(const MfmaArgs a) {
   const int64_t rowbytes = ((int64_t)n * qb + 7) / 8;
   const bool vec_q = (a.qstride & 15) == 0 && (reinterpret_cast<uintptr_t>(a.q) & 15) == 0;
   const bool dma_q = qb == 8 && vec_q;
-  // chunk swizzle of payload row r: 16 chunks of 8-bit codes, 8 of 4-bit
-  // codes (by r / 2, so that the 8-byte reads of 32 rows spread over the banks)
-  auto qswz = [&](int r) { return qb == 8 ? (r & 15) : ((r >> 1) & 7); };
+  // chunk swizzle of payload row r: 16 (BN = 256) or 8 chunks of 8-bit codes, 8
+  // or 4 of 4-bit codes (by r / 2 or r / 4, so that the 8-byte reads of 32 rows
+  // spread over the banks)
+  auto qswz8 = [](int r) { return BN == 256 ? (r & 15) : swz8(r); };
+  auto qswz4 = [](int r) { return BN == 256 ? ((r >> 1) & 7) : ((r >> 2) & 3); };
+  auto qswz = [&](int r) { return qb == 8 ? qswz8(r) : qswz4(r); };
   // payload row r: staged in the last K step, rows [0, BM/2) in the idle
   // stage's A buffer and [BM/2, BM) in its B buffer; staged after the
   // loop, consecutive rows from the start of LDS
@@ -169,16 +171,17 @@ void k_fuse_dma(const MfmaArgs a) {
                       : reinterpret_cast<uint8_t*>(Bs + st * BN * kBK) + (r - BM / 2) * TB;
   };
   // global-to-LDS copies of an 8-bit payload tile: a wave instruction fills
-  // 4 rows (1 KB, contiguous in either placement); rows past M read row
+  // 1 KB (RP rows, contiguous in either placement); rows past M read row
   // M-1 and chunks past the row's end read the tile's first chunk (their
   // positions are never selected)
   auto stage_payload_dma = [&](bool in_stage, int st) {
-    for (int t = wave; t < BM / 4; t += WNN * WMM) {
-      const int r = t * 4 + (lane >> 4);
-      const int k = (lane & 15) ^ (r & 15);
+    constexpr int RP = 1024 / BN, CP = BN / 16;
+    for (int t = wave; t < BM / RP; t += WNN * WMM) {
+      const int r = t * RP + lane / CP;
+      const int k = (lane & (CP - 1)) ^ qswz8(r);
       const int64_t col = c0 + k * 16 < rowbytes ? c0 + k * 16 : c0;
       __builtin_amdgcn_global_load_lds(a.q + (int64_t)min(m0 + r, M - 1) * a.qstride + col,
-                                       (lds_void_t*)prow(in_stage, st, t * 4), 16, 0, 0);
+                                       (lds_void_t*)prow(in_stage, st, t * RP), 16, 0, 0);
     }
   };
 
@@ -193,7 +196,7 @@ void k_fuse_dma(const MfmaArgs a) {
   constexpr int QT = BM * (BN / 16) / NT;  // 8-bit chunks per thread (4-bit: half of them)
   u32x4_t qv[QT];
   auto load_payload = [&]() {
-    const int ksh = qb == 8 ? 4 : 3;  // log2 CPR
+    const int ksh = (BN == 256 ? 4 : 3) - (qb == 8 ? 0 : 1);  // log2 CPR
 #pragma unroll
     for (int t = 0; t < QT; ++t) {
       const int c = tid + t * NT, r = c >> ksh;
@@ -204,7 +207,7 @@ void k_fuse_dma(const MfmaArgs a) {
     }
   };
   auto store_payload = [&]() {
-    const int ksh = qb == 8 ? 4 : 3;
+    const int ksh = (BN == 256 ? 4 : 3) - (qb == 8 ? 0 : 1);
 #pragma unroll
     for (int t = 0; t < QT; ++t) {
       const int c = tid + t * NT, r = c >> ksh, k = c & (CPR - 1);
@@ -297,10 +300,10 @@ void k_fuse_dma(const MfmaArgs a) {
       for (int i = 0; i < FI; ++i) {
         const int nl0 = wn * (BN / WNN) + i * 32 + 16 * hh;
         if (qb == 8) {
-          cq[i] = *reinterpret_cast<const u32x4_t*>(qrow + (((nl0 >> 4) ^ (ml & 15)) << 4));
+          cq[i] = *reinterpret_cast<const u32x4_t*>(qrow + (((nl0 >> 4) ^ qswz8(ml)) << 4));
         } else {
           const int bo = nl0 >> 1;
-          const uint2 h2 = *reinterpret_cast<const uint2*>(qrow + ((((bo >> 4) ^ ((ml >> 1) & 7)) << 4) | (bo & 15)));
+          const uint2 h2 = *reinterpret_cast<const uint2*>(qrow + ((((bo >> 4) ^ qswz4(ml)) << 4) | (bo & 15)));
 #pragma unroll
           for (int g = 0; g < 4; ++g) {
             const uint32_t h = ((g < 2 ? h2.x : h2.y) >> (16 * (g & 1))) & 0xFFFFu;
@@ -393,31 +396,50 @@ void k_fuse_dma(const MfmaArgs a) {
 }
 
 
-template <int BM, int WNN, int WMM>
+template <int BM, int BN, int WNN, int WMM, int BPC>
 static hipError_t launch_fuse_tile(MfmaArgs a, hipStream_t s) {
   static std::atomic<uint64_t> lds_set[4];
   a.m_tiles = (a.M + BM - 1) / BM;
-  a.n_tiles = (a.n + kMfmaBN - 1) / kMfmaBN;
+  a.n_tiles = (a.n + BN - 1) / BN;
   if (a.n_tiles > kMaxBlocks || a.K % 8 != 0) return hipErrorInvalidValue;
   const bool o32 = copy_offsets_fit(a);
   const bool tail = a.K % kBK != 0;
-  auto kf = o32 ? (tail ? k_fuse_dma<BM, WNN, WMM, true, true> : k_fuse_dma<BM, WNN, WMM, true, false>)
-                : (tail ? k_fuse_dma<BM, WNN, WMM, false, true> : k_fuse_dma<BM, WNN, WMM, false, false>);
-  constexpr size_t lds = fuse_dma_lds_bytes<BM, WNN, WMM>();
+  auto kf = o32 ? (tail ? k_fuse_dma<BM, BN, WNN, WMM, BPC, true, true> : k_fuse_dma<BM, BN, WNN, WMM, BPC, true, false>)
+                : (tail ? k_fuse_dma<BM, BN, WNN, WMM, BPC, false, true> : k_fuse_dma<BM, BN, WNN, WMM, BPC, false, false>);
+  constexpr size_t lds = fuse_dma_lds_bytes<BM, BN>();
   hipError_t e = set_lds_limit_once(lds_set[2 * o32 + tail], reinterpret_cast<const void*>(kf), lds);
   if (e != hipSuccess) return e;
   launch_kernel(kf, dim3(a.m_tiles * a.n_tiles), dim3(64 * WNN * WMM), lds, s, a);
   return hipGetLastError();
 }
 
-// Row tile for M rows: 32 up to 32 rows, 128 up to 128, else whichever of
-// 256 and 320 pads M less.
+// Tiles of 64 (32 up to 32 rows) x 128, three blocks on a CU, or of 256 or 320
+// rows (whichever pads M less) x 256, one block.  With few K steps a block is
+// mostly waits (ids, first copies, payload), which only other blocks on its CU
+// can cover; the large tiles copy less per product.  The small ones up to 128
+// rows; where the large ones would leave half of the CUs or more without work;
+// and up to 192 rows for short K.  (us, before / small: 18 rows x 45001
+// positions x 96 columns 9.2 / 8.2, 60 x 60000 x 512 21.8 / 15.0, 80 x 78720 x
+// 512 39 / 29, 128 x 30000 x 256 13.2 / 8.7, 155 x 60000 x 96 15.6 / 13.5, 205 x
+// 28982 x 256 4-bit 25 / 16, 320 x 15000 x 512 40 / 15; not taken: 155 x 60000 x
+// 512 26.2 / 27.9, 320 x 60000 x 96 17 / 21, x 512 28 / 41, 882 x 29504 x 512
+// 50.6 / 50.8, 2048 x 8000 x 512 24 / 27.)
+static int fuse_bm_large(int M) { return (M + 319) / 320 * 320 < (M + 255) / 256 * 256 ? 320 : 256; }
+
+static bool fuse_small_tiles(int M, int n, int K) {
+  if ((n + 127) / 128 > kMaxBlocks) return false;
+  const int bm = fuse_bm_large(M);
+  return M <= 128 || (M <= 192 && K <= 256) || (int64_t)((M + bm - 1) / bm) * ((n + 255) / 256) <= kCUs / 2;
+}
+
+int fuse_n_tiles(int M, int n, int K) { return fuse_small_tiles(M, n, K) ? (n + 127) / 128 : (n + 255) / 256; }
+
 hipError_t launch_fuse_mfma(const MfmaArgs& a, hipStream_t s) {
-  if (a.M <= 32) return launch_fuse_tile<32, 4, 1>(a, s);
-  if (a.M <= 128) return launch_fuse_tile<128, 2, 2>(a, s);
-  const int pad256 = (a.M + 255) / 256 * 256 - a.M;
-  const int pad320 = (a.M + 319) / 320 * 320 - a.M;
-  return pad320 < pad256 ? launch_fuse_tile<320, 4, 2>(a, s) : launch_fuse_tile<256, 2, 4>(a, s);
+  if (fuse_small_tiles(a.M, a.n, a.K))
+    return a.M <= 32 ? launch_fuse_tile<32, 128, 4, 1, 3>(a, s) : launch_fuse_tile<64, 128, 4, 1, 3>(a, s);
+  if (a.M <= 128) return launch_fuse_tile<64, 256, 4, 1, 2>(a, s);  // more than 262144 positions
+  return fuse_bm_large(a.M) == 320 ? launch_fuse_tile<320, 256, 4, 2, 1>(a, s)
+                                   : launch_fuse_tile<256, 256, 2, 4, 1>(a, s);
 }
 
 }  // namespace sph

@@ -625,7 +625,7 @@ int fuse_verify_impl(const char* fn, bool codes, const void* q, const float* sca
     a.best_part = best;
     hipError_t e = traced("fuse_mfma", s, [&] { return sph::launch_mfma(sph::kEpiFuse, 0, a, s); });
     if (e != hipSuccess) return hip_fail(e, "endpoint projection launch");
-    nblk = sph::mfma_n_tiles((int)n);
+    nblk = sph::fuse_n_tiles((int)M, (int)n, (int)d_end);
   } else {
     int mr = sph::kGemvMaxRows;
     if (Kp > 0) mr = (int)std::min<int64_t>(mr, sph::kGemvLdsBytes / (Kp * 2));

@@ -136,6 +136,8 @@ int stream_groups(int M, int n);
 int stream_width(int M, int n);
 hipError_t launch_stream(int wtype, MfmaArgs a, hipStream_t s);
 hipError_t launch_fuse_mfma(const MfmaArgs& a, hipStream_t s);
+// its argmax keys go to slot j / tile, fuse_n_tiles of them
+int fuse_n_tiles(int M, int n, int K);
 // true where the cloud projection can quantise blocks of 256 positions in its epilogue
 bool mfma_quantises_in_epilogue(int M);
 int mfma_n_tiles(int n);

@@ -17,14 +17,19 @@ from test_gpu_payload import run_format_case
 pytestmark = pytest.mark.gpu
 
 ENDPOINT = [
-    # (sessions, R, d_end, n): every row tile of the endpoint projection
+    # (sessions, R, d_end, n): the small tiles of the endpoint projection
     (3, 3, 8, 257),      # 9 rows, one 8-column step, a tile of one position
     (4, 8, 48, 1535),    # 32 rows, one partial step
     (11, 3, 72, 519),    # 33 rows, a whole and an 8-column step
     (32, 4, 120, 1009),  # 128 rows
-    (43, 3, 96, 770),    # 129 rows: 256-row tile
+    (43, 3, 96, 770),    # 129 rows
     (64, 4, 56, 513),    # 256 rows
-    (53, 6, 184, 1031),  # 318 rows: 320-row tile
+    (53, 6, 184, 1031),  # 318 rows
+    # the large ones (many positions; long K up to 192 rows)
+    (31, 5, 264, 33057),  # 155 rows of the 256-row tile
+    (64, 4, 56, 33025),   # 256 rows, a tile of one position
+    (80, 4, 72, 33000),   # 320 rows
+    (2, 5, 8, 262145),    # few rows, more positions than the small tiles have slots for
 ]
 
 
@@ -34,7 +39,8 @@ def test_endpoint_partial_steps_and_unaligned_rows(shape, fmt):
     S, R, de, n = shape
     cfg = Config("edge", 400 + sum(shape) + fmt[0], d=de + 128, d_end=de, vocab=n + 300, n_sub=n,
                  subset_kind="choice", sessions=S, rows_per_session=R)
-    run_format_case(make_workload(cfg), fmt[0], fmt[1], f"endpoint edge {shape} {fmt}")
+    sessions = None if S * R * n < 2_000_000 else [0, S - 1]
+    run_format_case(make_workload(cfg), fmt[0], fmt[1], f"endpoint edge {shape} {fmt}", sessions=sessions)
 
 
 # (sessions, R, d_cloud, n): every row tile of the streaming cloud projection
