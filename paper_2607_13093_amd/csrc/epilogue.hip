@@ -26,7 +26,7 @@ __device__ __forceinline__ int quantize_one(float z, float clip, float s, float 
 template <int BITS>
 __global__ __launch_bounds__(256) void k_quantize(const float* __restrict__ z,
                                                   const float* __restrict__ amax_part, int nblk,
-                                                  int n, int vec, float clip, int qshift,
+                                                  int n, float clip, int qshift,
                                                   uint8_t* __restrict__ q, int64_t qstride,
                                                   float* __restrict__ scale, int qnb) {
   constexpr float kQmax = BITS == 8 ? 127.0f : 7.0f;
@@ -47,8 +47,8 @@ __global__ __launch_bounds__(256) void k_quantize(const float* __restrict__ z,
 #pragma unroll
   for (int t = 0; t < VT; ++t) {
     const int j = j0 + tid * 4 + 1024 * t;
-    if (vec) {
-      v[t] = j < j1 ? *reinterpret_cast<const float4*>(z + zrow + j) : make_float4(0.f, 0.f, 0.f, 0.f);
+    if (j + 4 <= j1) {  // one load at any alignment
+      __builtin_memcpy(&v[t], z + zrow + j, 16);
     } else {
       v[t].x = j < j1 ? z[zrow + j] : 0.f;
       v[t].y = j + 1 < j1 ? z[zrow + j + 1] : 0.f;
@@ -107,13 +107,13 @@ __global__ __launch_bounds__(256) void k_quantize(const float* __restrict__ z,
     const int c0 = quantize_one(v[t].x, clip, s, kQmax), c1 = quantize_one(v[t].y, clip, s, kQmax);
     const int c2 = quantize_one(v[t].z, clip, s, kQmax), c3 = quantize_one(v[t].w, clip, s, kQmax);
     if constexpr (BITS == 8) {
-      if (vec) {
+      if (j + 4 <= j1) {  // one store at any alignment
         char4 o;
         o.x = (signed char)c0;
         o.y = (signed char)c1;
         o.z = (signed char)c2;
         o.w = (signed char)c3;
-        *reinterpret_cast<char4*>(qrow + j) = o;
+        __builtin_memcpy(qrow + j, &o, 4);
       } else {
         const int c[4] = {c0, c1, c2, c3};
 #pragma unroll
@@ -125,8 +125,9 @@ __global__ __launch_bounds__(256) void k_quantize(const float* __restrict__ z,
       // nibble of an odd row
       const uint8_t b0 = (uint8_t)((c0 & 15) | ((c1 & 15) << 4));
       const uint8_t b1 = (uint8_t)((c2 & 15) | ((c3 & 15) << 4));
-      qrow[j >> 1] = b0;
-      if (j + 2 < j1) qrow[(j >> 1) + 1] = b1;
+      const uint8_t o[2] = {b0, b1};
+      if (j + 2 < j1) __builtin_memcpy(qrow + (j >> 1), o, 2);
+      else qrow[j >> 1] = b0;
     }
   }
 }
@@ -137,14 +138,11 @@ hipError_t launch_quantize(const float* z, const float* amax_part, int nblk, int
   const int chunks = (n + kQuantChunk - 1) / kQuantChunk;
   if (chunks > 65535 || (bits != 8 && bits != 4)) return hipErrorInvalidValue;
   if (qshift >= 0 && (qshift < 8 || (1 << qshift) > kQuantChunk)) return hipErrorInvalidValue;
-  // float4 / char4 accesses need whole, aligned groups of four columns
-  const int vec = (n % 4 == 0) && (reinterpret_cast<uintptr_t>(z) % 16 == 0) &&
-                  (reinterpret_cast<uintptr_t>(q) % 4 == 0) && qstride % 4 == 0;
   if (bits == 8)
-    launch_kernel(k_quantize<8>, dim3(M, chunks), dim3(256), 0, s, z, amax_part, nblk, n, vec,
+    launch_kernel(k_quantize<8>, dim3(M, chunks), dim3(256), 0, s, z, amax_part, nblk, n,
                   clip, qshift, q, qstride, scale, qnb);
   else
-    launch_kernel(k_quantize<4>, dim3(M, chunks), dim3(256), 0, s, z, amax_part, nblk, n, vec,
+    launch_kernel(k_quantize<4>, dim3(M, chunks), dim3(256), 0, s, z, amax_part, nblk, n,
                   clip, qshift, q, qstride, scale, qnb);
   return hipGetLastError();
 }
