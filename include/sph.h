@@ -114,7 +114,10 @@ void sph_subset_destroy(sph_subset subset);
  * size includes optional scratch of the sampler (up to 0.2 MB per row): a
  * smaller workspace of align256(M * 16384) + align256(M * n_sub * 4) bytes
  * (plus the widened hidden codes of sph_fuse_verify_hq) is accepted too and
- * gives the same tokens, with one workgroup per row.
+ * gives the same tokens, with one workgroup per row.  The cloud size has the
+ * rows of partial logits start on 128-byte lines (n_sub rounded up to 32
+ * positions); align256(M * n_sub * 4) + align256(M * 8192) bytes are accepted
+ * too and give the same payload.
  */
 size_t sph_cloud_partial_workspace(int64_t M, sph_subset subset);
 size_t sph_fuse_verify_workspace(int64_t M, sph_subset subset, int mode);
@@ -227,8 +230,8 @@ int sph_cloud_partial_fmt(const void* h_cloud, int64_t ldh, int64_t M, int64_t d
  * that every GPU the library runs on holds until the process ends; the
  * call allocates nothing, frees nothing and calls no allocating routine.
  * Inputs, outputs, results and errors are those of sph_cloud_partial_fmt,
- * plus SPH_E_WORKSPACE (nothing enqueued) when
- * sph_cloud_partial_workspace(M, subset) exceeds the scratch size, e.g.
+ * plus SPH_E_WORKSPACE (nothing enqueued) when the least workspace that call
+ * accepts exceeds the scratch size, e.g.
  * 5 rows x 49152 ids need about 1 MB, 20 rows x 190000 ids about 15 MB.
  * The scratch keeps the last call's contents and no kernel depends on
  * its initial contents.  Every call on one GPU shares that GPU's scratch:

@@ -24,7 +24,7 @@ __device__ __forceinline__ int quantize_one(float z, float clip, float s, float 
 // The division is correctly rounded.  8-bit codes are bytes; 4-bit codes go
 // two per byte, the even position in the low nibble (two's complement).
 template <int BITS>
-__global__ __launch_bounds__(256) void k_quantize(const float* __restrict__ z,
+__global__ __launch_bounds__(256) void k_quantize(const float* __restrict__ z, int ldz,
                                                   const float* __restrict__ amax_part, int nblk,
                                                   int n, float clip, int qshift,
                                                   uint8_t* __restrict__ q, int64_t qstride,
@@ -34,7 +34,7 @@ __global__ __launch_bounds__(256) void k_quantize(const float* __restrict__ z,
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   __shared__ float s_red[4];
   __shared__ uint32_t s_bmax[kQuantChunk / 256];  // |y| maxima of the chunk's blocks
-  const int64_t zrow = (int64_t)m * n;
+  const int64_t zrow = (int64_t)m * ldz;
   const int j0 = blockIdx.y * kQuantChunk;
   const int j1 = min(n, j0 + kQuantChunk);
   const bool per_row = qshift < 0;
@@ -132,17 +132,17 @@ __global__ __launch_bounds__(256) void k_quantize(const float* __restrict__ z,
   }
 }
 
-hipError_t launch_quantize(const float* z, const float* amax_part, int nblk, int M, int n,
+hipError_t launch_quantize(const float* z, int ldz, const float* amax_part, int nblk, int M, int n,
                            float clip, int bits, int qshift, uint8_t* q, int64_t qstride,
                            float* scale, int qnb, hipStream_t s) {
   const int chunks = (n + kQuantChunk - 1) / kQuantChunk;
   if (chunks > 65535 || (bits != 8 && bits != 4)) return hipErrorInvalidValue;
   if (qshift >= 0 && (qshift < 8 || (1 << qshift) > kQuantChunk)) return hipErrorInvalidValue;
   if (bits == 8)
-    launch_kernel(k_quantize<8>, dim3(M, chunks), dim3(256), 0, s, z, amax_part, nblk, n,
+    launch_kernel(k_quantize<8>, dim3(M, chunks), dim3(256), 0, s, z, ldz, amax_part, nblk, n,
                   clip, qshift, q, qstride, scale, qnb);
   else
-    launch_kernel(k_quantize<4>, dim3(M, chunks), dim3(256), 0, s, z, amax_part, nblk, n,
+    launch_kernel(k_quantize<4>, dim3(M, chunks), dim3(256), 0, s, z, ldz, amax_part, nblk, n,
                   clip, qshift, q, qstride, scale, qnb);
   return hipGetLastError();
 }

@@ -48,9 +48,9 @@ __device__ __forceinline__ float cloud_value(float dot, const MfmaArgs& a, int i
 // Descriptor of `rows` rows of z from the tile's first one (at most 320 rows of
 // 2^19 positions, below 2^30 bytes), an offset past any tile's, and the
 // non-temporal store of one value.
-__device__ __forceinline__ auto tile_rsrc(float* z, int rows, int n) {
+__device__ __forceinline__ auto tile_rsrc(float* z, int rows, int ldz) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(scalar_ptr(z)), 0,
-                                           (int)((uint32_t)rows * (uint32_t)n * 4u), 0x00020000);
+                                           (int)((uint32_t)rows * (uint32_t)ldz * 4u), 0x00020000);
 }
 constexpr uint32_t kPastTile = 0xC0000000u;  // (plus an offset inside the tile: no wrap)
 __device__ __forceinline__ void store_z(float v, __amdgpu_buffer_rsrc_t rsrc, uint32_t off) {
@@ -60,8 +60,8 @@ __device__ __forceinline__ void store_z(float v, __amdgpu_buffer_rsrc_t rsrc, ui
 // From the row of accumulator r - 1 (of the previous fragment for r = 0) to that
 // of r: the next row, or the fifth next.  The empty asm keeps one running
 // offset: all of them at once spilled 100 registers.
-__device__ __forceinline__ void next_row(uint32_t& off, int r, int n) {
-  off += (uint32_t)n * (r % 4 == 0 ? 20u : 4u);
+__device__ __forceinline__ void next_row(uint32_t& off, int r, int ldz) {
+  off += (uint32_t)ldz * (r % 4 == 0 ? 20u : 4u);
   asm volatile("" : "+v"(off));
 }
 
@@ -74,7 +74,7 @@ __device__ __forceinline__ void tile_epilogue(f32x16_t (&acc)[FM][FN], const Mfm
   constexpr int P = (FM * 16 + 31) / 32 * 32;  // row values per lane, padded for the butterfly
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WN, wn = wave % WN;
-  const int M = a.M, n = a.n;
+  const int M = a.M, n = a.n, ldz = a.ldz;
   float red[P];
 #pragma unroll
   for (int t = FM * 16; t < P; ++t) red[t] = 0.0f;
@@ -87,7 +87,7 @@ __device__ __forceinline__ void tile_epilogue(f32x16_t (&acc)[FM][FN], const Mfm
   // compiled to two branches, a 64-bit address and a reload of the bias
   // pointer: 13.6 us of a 210 us block on the dense 2048-row shape, now 7, and
   // every tile of a batch whose rows do not fill its row tiles.)
-  const auto rsrc = tile_rsrc(a.z ? a.z + (int64_t)m0 * n : nullptr, min(BM, M - m0), n);
+  const auto rsrc = tile_rsrc(a.z ? a.z + (int64_t)m0 * ldz : nullptr, min(BM, M - m0), ldz);
   const uint32_t lrow0 = (uint32_t)(wm * TM + 4 * (lane >> 5));
   const uint32_t lcol0 = (uint32_t)(n0 + wn * TN + (lane & 31));
   auto fill = [&](auto edge, auto has_bias, auto store) {
@@ -104,12 +104,12 @@ __device__ __forceinline__ void tile_epilogue(f32x16_t (&acc)[FM][FN], const Mfm
 #pragma unroll
     for (int j = 0; j < FN; ++j) oj[j] = ED && lcol0 + 32u * j >= (uint32_t)n ? kPastTile : 128u * j;
     const float clip = a.clip;
-    uint32_t off = (lrow0 * (uint32_t)n + lcol0) * 4u;
+    uint32_t off = (lrow0 * (uint32_t)ldz + lcol0) * 4u;
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        if (i + r > 0) next_row(off, r, n);
+        if (i + r > 0) next_row(off, r, ldz);
         float best = 0.0f;
 #pragma unroll
         for (int j = 0; j < FN; ++j) {
@@ -660,7 +660,8 @@ void k_mfma_w1(const MfmaArgs a) {
 #pragma unroll
   for (int t = 0; t < P; ++t) red[t] = 0.0f;
   const float clip = a.clip;
-  const auto rsrc = tile_rsrc(a.z + (int64_t)m0 * n, min(BM, M - m0), n);
+  const int ldz = a.ldz;
+  const auto rsrc = tile_rsrc(a.z + (int64_t)m0 * ldz, min(BM, M - m0), ldz);
   const uint32_t lrow0 = (uint32_t)(wm * TM + 4 * (lane >> 5));
   const uint32_t lcol0 = (uint32_t)(n0 + wn * TN + (lane & 31));
   auto fill = [&](auto plain) {
@@ -672,7 +673,7 @@ void k_mfma_w1(const MfmaArgs a) {
         f32x16_t v;
         asm volatile("; fragment out of the AGPRs" : "=v"(v) : "0"(acc[i][j]));
         const uint32_t col = lcol0 + 32u * j;
-        uint32_t off = ((lrow0 + 32u * i) * (uint32_t)n + col) * 4u;
+        uint32_t off = ((lrow0 + 32u * i) * (uint32_t)ldz + col) * 4u;
         float cb = 0.0f;
         if (!PL && a.bias) {
           const int lcol = wn * TN + j * 32 + (lane & 31);
@@ -681,7 +682,7 @@ void k_mfma_w1(const MfmaArgs a) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const float zv = !PL && a.bias ? v[r] + cb : v[r];
-          if (r > 0) next_row(off, r, n);
+          if (r > 0) next_row(off, r, ldz);
           store_z(zv, rsrc, !PL && col >= (uint32_t)n ? kPastTile : off);
           red[i * 16 + r] = fmaxf(red[i * 16 + r], fminf(fabsf(zv), clip));
         }

@@ -182,11 +182,16 @@ int make_plan(const int32_t* host_ids, int64_t n, int64_t vocab, hipStream_t str
   return ok();
 }
 
-// Cloud workspace: [fp32 z : M x n][fp32 row-max partials : M x kMaxBlocks]
-size_t cloud_ws(int64_t M, int64_t n) {
+// Cloud workspace: [fp32 z : M rows ldz apart][fp32 row-max partials : M x
+// kMaxBlocks].  With ldz a whole number of 128-byte lines the projections'
+// stores of z fill lines (1999 rows x 32767 positions x 256 columns 230 -> 120
+// us, 320 x 60001 41 -> 27); a workspace too small for that is accepted with
+// rows n apart.
+size_t cloud_ws(int64_t M, int64_t ldz) {
   if (M <= 0) return 0;
-  return align256((size_t)M * n * 4) + align256((size_t)M * sph::kMaxBlocks * 4);
+  return align256((size_t)M * ldz * 4) + align256((size_t)M * sph::kMaxBlocks * 4);
 }
+int64_t whole_lines(int64_t n) { return round_up(n, 32); }
 
 // Fuse workspace: [argmax keys : M x kMaxBlocks][sample: fp32 f : M x n]
 size_t fuse_ws(int64_t M, int64_t n, int mode) {
@@ -310,7 +315,7 @@ void sph_subset_destroy(sph_subset subset) {
 
 size_t sph_cloud_partial_workspace(int64_t M, sph_subset subset) {
   if (!subset || M < 0) return 0;
-  return cloud_ws(M, subset->n);
+  return cloud_ws(M, whole_lines(subset->n));
 }
 
 size_t sph_fuse_verify_workspace(int64_t M, sph_subset subset, int mode) {
@@ -410,7 +415,9 @@ int sph_cloud_partial_fmt(const void* h_cloud, int64_t ldh, int64_t M, int64_t d
   hipStream_t s = (hipStream_t)stream;
   uint8_t* ws = static_cast<uint8_t*>(workspace);
   float* z = z_out ? z_out : reinterpret_cast<float*>(ws);
-  float* amax = reinterpret_cast<float*>(ws + align256((size_t)M * n * 4));
+  const int64_t ldw_z = ws_bytes >= cloud_ws(M, whole_lines(n)) ? whole_lines(n) : n;
+  float* amax = reinterpret_cast<float*>(ws + align256((size_t)M * ldw_z * 4));
+  int64_t ldz = n;
 
   // Dense path: more rows than one skinny launch covers, 16-byte aligned h rows.
   const bool h_vec = (reinterpret_cast<uintptr_t>(h_cloud) & 15) == 0 && ldh % 8 == 0;
@@ -436,6 +443,7 @@ int sph_cloud_partial_fmt(const void* h_cloud, int64_t ldh, int64_t M, int64_t d
       // a scale block is one 256-position tile: the projection's epilogue
       // quantises from its accumulators, z is written only on request
       a.z = z_out;
+      a.ldz = (int)n;
       a.qout = static_cast<uint8_t*>(q_out);
       a.qout_stride = qstride;
       a.qout_scale = scale_out;
@@ -445,7 +453,9 @@ int sph_cloud_partial_fmt(const void* h_cloud, int64_t ldh, int64_t M, int64_t d
       if (e != hipSuccess) return hip_fail(e, "cloud projection launch");
       return ok();
     }
+    if (!z_out) ldz = ldw_z;
     a.z = z;
+    a.ldz = (int)ldz;
     a.amax_part = amax;
     hipError_t e = traced("cloud_mfma", s, [&] {
       return few ? sph::launch_stream(wtype, a, s) : sph::launch_mfma(sph::kEpiCloud, wtype, a, s);
@@ -482,7 +492,7 @@ int sph_cloud_partial_fmt(const void* h_cloud, int64_t ldh, int64_t M, int64_t d
     }
   }
   hipError_t e = traced("cloud_quantize", s, [&] {
-    return sph::launch_quantize(z, amax, nblk, (int)M, (int)n, clip_c, bits, qshift,
+    return sph::launch_quantize(z, (int)ldz, amax, nblk, (int)M, (int)n, clip_c, bits, qshift,
                                 static_cast<uint8_t*>(q_out), qstride, scale_out, qnb, s);
   });
   if (e != hipSuccess) return hip_fail(e, "quantiser launch");

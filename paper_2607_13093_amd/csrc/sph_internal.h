@@ -94,7 +94,8 @@ struct MfmaArgs {
   // cloud epilogue
   const float* bias;
   float clip;
-  float* z;               // fp32 [M, n]
+  float* z;               // fp32 [M, n], rows ldz apart
+  int ldz;
   float* amax_part;       // fp32 [M, kMaxBlocks], slot = n-tile
   // fuse epilogue: the payload in format (qbits, block of 2^qshift >= 256
   // positions or one per row when qshift < 0)
@@ -147,7 +148,7 @@ int mfma_tiles(int M, int n);  // all tiles of the cloud projection
 // byte, low nibble first) with one scale per row (qshift < 0: from the
 // projection's per-block maxima amax_part) or per row and block of 2^qshift
 // positions (8 <= qshift <= 12).  q rows are qstride bytes, scale rows qnb.
-hipError_t launch_quantize(const float* z, const float* amax_part, int nblk, int M, int n,
+hipError_t launch_quantize(const float* z, int ldz, const float* amax_part, int nblk, int M, int n,
                            float clip, int bits, int qshift, uint8_t* q, int64_t qstride,
                            float* scale, int qnb, hipStream_t s);
 

@@ -404,8 +404,8 @@ void k_mfma_stream(const MfmaArgs a) {
 #pragma unroll
     for (int t = 0; t < P; ++t) red[t] = 0.0f;
     const float clip = a.clip;
-    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(scalar_ptr(a.z + (int64_t)m0 * n)), 0,
-                                                        (int)((uint32_t)M * (uint32_t)n * 4u), 0x00020000);
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(scalar_ptr(a.z + (int64_t)m0 * a.ldz)), 0,
+                                                        (int)((uint32_t)M * (uint32_t)a.ldz * 4u), 0x00020000);
 #pragma unroll
     for (int j = 0; j < FN; ++j) {
       const int rel = wn * WCOLS + j * 32 + (lane & 31);
@@ -423,7 +423,7 @@ void k_mfma_stream(const MfmaArgs a) {
           if constexpr (WT == 1) zv = zv * cs;
           zv = hb ? zv + cb : zv;
           const uint32_t row = (uint32_t)(wm * WROWS + i * 32 + 8 * (r >> 2) + 4 * hh + (r & 3));
-          const uint32_t off = rel < w ? (row * (uint32_t)n + (uint32_t)col) * 4u : 0xF0000000u;
+          const uint32_t off = rel < w ? (row * (uint32_t)a.ldz + (uint32_t)col) * 4u : 0xF0000000u;
           __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(zv), rsrc, (int)off, 0, 0);
           red[i * 16 + r] = fmaxf(red[i * 16 + r], rel < w ? fminf(fabsf(zv), clip) : 0.0f);
         }

@@ -217,3 +217,26 @@ def test_sealed_batches(case):
     want = torch.ones_like(ok)
     want[bad] = 0
     assert torch.equal(ok, want)
+
+
+@pytest.mark.parametrize("M,n", [(37, 1001), (300, 33025), (1030, 259)], ids=["stream", "tiles320", "tiles256"])
+def test_payload_with_and_without_padded_rows(M, n):
+    """The partial logits' row stride (whole lines in a workspace of the queried
+    size, n in the smallest one accepted or in z_out) changes no payload bit."""
+    g = torch.Generator(device="cuda").manual_seed(M)
+    h = torch.randn((M, 72), device="cuda", generator=g).to(torch.bfloat16)
+    w = torch.randn((n, 72), device="cuda", generator=g).to(torch.bfloat16)
+    sub = sph.Subset(vocab=n, full=True)
+    full = sph.cloud_partial_workspace(M, sub)
+    least = (M * n * 4 + 255) // 256 * 256 + (M * 8192 + 255) // 256 * 256
+    assert least < full
+    got = [sph.cloud_partial(h, w, sub, 8.0, workspace=torch.full((size,), 0x7F, dtype=torch.uint8, device="cuda"),
+                             want_z=want)
+           for size, want in ((full, False), (least, False), (full, True))]
+    for q, s, _ in got[1:]:
+        assert torch.equal(q, got[0][0]) and torch.equal(s, got[0][1])
+    assert torch.equal(got[2][2].abs().clamp(max=8.0).amax(1) / 127.0, got[2][1])
+    with pytest.raises(sph.SphError):
+        sph.cloud_partial(h, w, sub, 8.0, workspace=torch.empty((least - 256,), dtype=torch.uint8, device="cuda"),
+                          want_z=False)
+    sub.close()
