@@ -167,7 +167,7 @@ struct GemvShape {
 template <int MR, int LPR, int UNR, int WT, int EPI>
 constexpr int gemv_waves() {
   if (UNR == 4) return MR <= 4 ? 6 : 4;
-  if (MR <= (EPI == kEpiFuse ? 1 : 2)) return 6;
+  if (MR <= (EPI == kEpiFuse || (WT == 1 && LPR == 8) ? 1 : 2)) return 6;
   return (LPR == 64 && WT == 0 && EPI == kEpiCloud && MR <= 5) ? 6 : 4;
 }
 
@@ -315,7 +315,13 @@ void k_gemv(const GemvArgs a) {
     s_amax[tid] = 0u;
     s_best[tid] = 0ull;
   }
-  // Stage h[0:MR, 0:K] into LDS, zero padded to Kp, and this block's ids.
+  // Stage h[0:MR, 0:K] into LDS, zero padded to Kp, and this block's ids.  For
+  // E4M3 weights a lane needs the 16 elements of its chunk, two 16-byte reads:
+  // the first 8 of every chunk lie in the row's first half and the others in
+  // its second, so that a wave's read is 1 KB without gaps (elements in order
+  // had it touch every other 16 bytes: 5 rows x 65536 x 4800 columns 68.7 -> 66.0
+  // us, 6 rows 70.8 -> 67.7).
+  auto h_place = [&](int k) { return WT == 0 ? k : ((k >> 3) & 1) * (Kp >> 1) + (k >> 4) * 8 + (k & 7); };
   // int8 hidden-state codes are staged as bf16 (exact: at most 8 significant
   // bits) and their row scales applied to the dot products in the epilogue.
   if (EPI == kEpiFuse && a.hq) {
@@ -331,12 +337,12 @@ void k_gemv(const GemvArgs a) {
       const int m = idx / vpr, c = idx - m * vpr;
       u32x4_t val = {0u, 0u, 0u, 0u};
       if (c * 8 < a.K) val = *reinterpret_cast<const u32x4_t*>(a.h + (int64_t)m * a.ldh + c * 8);
-      *reinterpret_cast<u32x4_t*>(hs + m * Kp + c * 8) = val;
+      *reinterpret_cast<u32x4_t*>(hs + m * Kp + h_place(c * 8)) = val;
     }
   } else {
     for (int idx = tid; idx < MR * Kp; idx += kBS) {
       const int m = idx / Kp, k = idx - m * Kp;
-      hs[idx] = k < a.K ? a.h[(int64_t)m * a.ldh + k] : (uint16_t)0;
+      hs[m * Kp + h_place(k)] = k < a.K ? a.h[(int64_t)m * a.ldh + k] : (uint16_t)0;
     }
   }
   for (int j = r0 + tid; j < r1; j += kBS) s_ids[j - r0] = a.ids[j];
@@ -358,11 +364,11 @@ void k_gemv(const GemvArgs a) {
   auto products = [&](int u, const uint16_t* hp0) {
 #pragma unroll
     for (int m = 0; m < MR; ++m) {
-      const uint32_t* hp = reinterpret_cast<const uint32_t*>(hp0 + m * Kp + u * LPR * EPC);
+      const uint16_t* hp = hp0 + m * Kp + u * LPR * 8;
       uint32_t hw[HW];
 #pragma unroll
       for (int e = 0; e < HW; e += 4) {
-        const u32x4_t x = *reinterpret_cast<const u32x4_t*>(hp + e);
+        const u32x4_t x = *reinterpret_cast<const u32x4_t*>(hp + (e > 0 ? Kp >> 1 : 0));
         hw[e] = x.x; hw[e + 1] = x.y; hw[e + 2] = x.z; hw[e + 3] = x.w;
       }
       float s = acc[m];
@@ -430,7 +436,7 @@ void k_gemv(const GemvArgs a) {
     const int nit = npass == 0 ? it + 1 : it;
     const int nid = s_ids[pos_of(nit) - r0];
     const auto nrow = row_of(nid);
-    const uint16_t* hp0 = hs + (cl + pass * UNR * LPR) * EPC;
+    const uint16_t* hp0 = hs + (cl + pass * UNR * LPR) * 8;
     const int c0 = cl + pass * UNR * LPR;
     if (passes > 1) set_coff(npass);
     Epi enext = ecur;
@@ -446,7 +452,7 @@ void k_gemv(const GemvArgs a) {
     pass = npass;
   }
   if (T > 0) {
-    const uint16_t* hp0 = hs + (cl + pass * UNR * LPR) * EPC;
+    const uint16_t* hp0 = hs + (cl + pass * UNR * LPR) * 8;
     const int c0 = cl + pass * UNR * LPR;
 #pragma unroll
     for (int u = 0; u < UNR; ++u)
@@ -501,7 +507,12 @@ static int gemv_unr(int K, int wtype, int lpr) {
 template <int MR, int LPR, int UNR, int WT, int EPI>
 static hipError_t launch_one(GemvArgs a, hipStream_t s) {
   auto kern = k_gemv<MR, LPR, UNR, WT, EPI>;
+  static std::atomic<uint64_t> lds_set{0};
   const size_t hbytes = (size_t)MR * a.Kp * 2;
+  if (hbytes > (size_t)kGemvLdsBytes) return hipErrorInvalidValue;
+  hipError_t e = set_lds_limit_once(lds_set, reinterpret_cast<const void*>(kern),
+                                    (size_t)kGemvLdsBytes + kGemvMaxIdsPerBlock * 4);
+  if (e != hipSuccess) return e;
   constexpr int rpi = GemvShape<LPR>::RPI;
   const int iters = (a.n + rpi - 1) / rpi;
   // One round of resident blocks where possible: each block takes an equal

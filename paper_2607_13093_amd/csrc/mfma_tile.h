@@ -189,20 +189,6 @@ __device__ __forceinline__ void zero_tail(uint16_t* tile, int valid) {
   }
 }
 
-// The dynamic-LDS limit of a kernel is raised once per device (a host call,
-// kept out of every launch so that launches can be captured in a graph).
-// `done` is one instantiation's mask of devices already set.
-inline hipError_t set_lds_limit_once(std::atomic<uint64_t>& done, const void* kern, size_t bytes) {
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  const uint64_t bit = dev < 64 ? (uint64_t(1) << dev) : 0;
-  if (bit && (done.load(std::memory_order_acquire) & bit)) return hipSuccess;
-  e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-  if (e == hipSuccess && bit) done.fetch_or(bit, std::memory_order_release);
-  return e;
-}
-
 // 32-bit copy offsets (LaneAddr<true>) when every row the copies address
 // lies below 4 GiB of its operand's base.
 inline bool copy_offsets_fit(const MfmaArgs& a) {

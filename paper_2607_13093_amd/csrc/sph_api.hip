@@ -466,7 +466,7 @@ int sph_cloud_partial_fmt(const void* h_cloud, int64_t ldh, int64_t M, int64_t d
   } else {
     int mr = sph::kGemvMaxRows;
     if (Kp > 0) mr = (int)std::min<int64_t>(mr, sph::kGemvLdsBytes / (Kp * 2));
-    if (mr < 1) return fail(SPH_E_UNSUPPORTED, "%s: d_cloud=%lld too large", fn, (long long)d_cloud);
+    if (Kp * 2 > sph::kGemvRowBytes) return fail(SPH_E_UNSUPPORTED, "%s: d_cloud=%lld too large", fn, (long long)d_cloud);
     const int lpr = sph::gemv_lpr((int)d_cloud, wtype);
     const int rpi = sph::gemv_rows_per_iter(lpr);
     nblk = (int)std::min<int64_t>((n + rpi - 1) / rpi, sph::kMaxBlocks);
@@ -639,7 +639,7 @@ int fuse_verify_impl(const char* fn, bool codes, const void* q, const float* sca
   } else {
     int mr = sph::kGemvMaxRows;
     if (Kp > 0) mr = (int)std::min<int64_t>(mr, sph::kGemvLdsBytes / (Kp * 2));
-    if (mr < 1) return fail(SPH_E_UNSUPPORTED, "%s: d_end=%lld too large", fn, (long long)d_end);
+    if (Kp * 2 > sph::kGemvRowBytes) return fail(SPH_E_UNSUPPORTED, "%s: d_end=%lld too large", fn, (long long)d_end);
     const int lpr = sph::gemv_lpr((int)d_end, 0);
     const int rpi = sph::gemv_rows_per_iter(lpr);
     nblk = (int)std::min<int64_t>((n + rpi - 1) / rpi, sph::kMaxBlocks);

@@ -3,6 +3,8 @@
 
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
+
+#include <atomic>
 #include <vector>
 #include <stddef.h>
 #include <stdint.h>
@@ -32,11 +34,31 @@ inline void launch_kernel(K kernel, dim3 grid, dim3 block, uint32_t lds, hipStre
   }
 }
 
+// The dynamic-LDS limit of a kernel is raised once per device (a host call,
+// kept out of every launch so that launches can be captured in a graph).
+// `done` is one instantiation's mask of devices already set.
+inline hipError_t set_lds_limit_once(std::atomic<uint64_t>& done, const void* kern, size_t bytes) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const uint64_t bit = dev < 64 ? (uint64_t(1) << dev) : 0;
+  if (bit && (done.load(std::memory_order_acquire) & bit)) return hipSuccess;
+  e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  if (e == hipSuccess && bit) done.fetch_or(bit, std::memory_order_release);
+  return e;
+}
+
 // Per-block / per-tile partial results are stored [M][kMaxBlocks]; no
 // projection launch produces more column partials than this.
 constexpr int kMaxBlocks = 2048;
-// Largest LDS footprint the skinny kernels give to the staged rows of h.
-constexpr int kGemvLdsBytes = 60 * 1024;
+// Largest LDS footprint the skinny kernels give to the staged rows of h, and
+// to one row (a longer one is refused).  Rows that do not fit take another
+// launch, which reads the weights again, so all that one block can stage
+// beside its ids is better than room for a second block: 49152 positions x 7936
+// columns, 4 rows 233 us as 3 + 1 and 123 in one launch, 8 rows 362 (3 + 3 + 2)
+// and 145 (127 KB, one block a CU); E4M3 65536 x 4800, 8 rows 128 and 81.
+constexpr int kGemvLdsBytes = 136 * 1024;
+constexpr int kGemvRowBytes = 60 * 1024;
 // Largest row count handled by one skinny launch.
 constexpr int kGemvMaxRows = 8;
 // Largest contiguous share of subset positions one skinny block stages.

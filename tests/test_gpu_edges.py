@@ -240,3 +240,26 @@ def test_payload_with_and_without_padded_rows(M, n):
         sph.cloud_partial(h, w, sub, 8.0, workspace=torch.empty((least - 256,), dtype=torch.uint8, device="cuda"),
                           want_z=False)
     sub.close()
+
+
+# (rows, d_cloud, d_end, n): rows of h that fill the skinny kernels' LDS in one
+# launch (8 x 8704 columns), just exceed it (two launches) and need four
+SKINNY = [(8, 8704, 64, 301), (8, 8720, 64, 301), (7, 9952, 8712, 77), (8, 30720, 24, 70)]
+
+
+@pytest.mark.parametrize("wtype", ["bf16", "fp8"])
+@pytest.mark.parametrize("shape", SKINNY, ids=[f"M{m}dc{c}de{e}n{n}" for m, c, e, n in SKINNY])
+def test_skinny_rows_at_the_lds_limit(shape, wtype):
+    M, dc, de, n = shape
+    cfg = Config("skinny", 900 + dc % 100, d=dc + de, d_end=de, vocab=n + 9, n_sub=n, subset_kind="choice",
+                 sessions=1, rows_per_session=M, wtype=wtype, with_bias=True)
+    run_format_case(make_workload(cfg), 8, 0, f"skinny {shape} {wtype}")
+
+
+def test_skinny_row_longer_than_its_lds_is_refused():
+    h = torch.zeros((1, 30728), dtype=torch.bfloat16, device="cuda")
+    w = torch.zeros((4, 30728), dtype=torch.bfloat16, device="cuda")
+    sub = sph.Subset(vocab=4, full=True)
+    with pytest.raises(sph.SphError, match="too large"):
+        sph.cloud_partial(h, w, sub, 8.0)
+    sub.close()
