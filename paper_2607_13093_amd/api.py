@@ -23,13 +23,16 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
 
 
 def _stream_handle(device: torch.device) -> int:
-    return torch.cuda.current_stream(device).cuda_stream
+    # the handle alone: a Stream object costs 2 us, and a decode call is 10
+    if device.index is None:
+        return torch.cuda.current_stream(device).cuda_stream
+    return torch._C._cuda_getCurrentRawStream(device.index)
 
 
 def _require_gpu(name: str, t: torch.Tensor) -> None:
     if not t.is_cuda:
         raise ValueError(f"{name} must be a GPU tensor")
-    if t.dim() >= 1 and t.numel() > 0 and t.stride(-1) != 1:
+    if t.dim() >= 1 and t.stride(-1) != 1 and t.numel() > 0:
         raise ValueError(f"{name} must be contiguous along its last dimension")
 
 
@@ -114,17 +117,17 @@ def gcm_workspace(rows: int, row_bytes: int) -> int:
 
 def _rows_u8(t: torch.Tensor, name: str):
     _require_gpu(name, t)
-    if t.dim() != 2 or (t.shape[0] > 0 and t.shape[1] > 1 and t.stride(1) != 1):
+    shape, strides = t.shape, t.stride()
+    if len(shape) != 2 or (shape[0] > 0 and shape[1] > 1 and strides[1] != 1):
         raise ValueError(f"{name}: expected a 2-D tensor whose rows are contiguous")
-    rows = t.shape[0]
-    row_bytes = t.shape[1] * t.element_size()
-    ld = t.stride(0) * t.element_size() if rows > 0 else row_bytes
-    return rows, row_bytes, ld
+    rows, item = shape[0], t.element_size()
+    row_bytes = shape[1] * item
+    return rows, row_bytes, strides[0] * item if rows > 0 else row_bytes
 
 
 def _check_bytes(t: torch.Tensor, name: str, shape) -> None:
     _require_gpu(name, t)
-    if t.dtype != torch.uint8 or tuple(t.shape) != tuple(shape) or not t.is_contiguous():
+    if t.dtype != torch.uint8 or t.shape != shape or not t.is_contiguous():
         raise ValueError(f"{name}: expected contiguous uint8 {tuple(shape)}, got {t.dtype} {tuple(t.shape)}")
 
 
@@ -317,8 +320,8 @@ def cloud_partial(h_cloud: torch.Tensor, w_cloud: torch.Tensor, subset: Subset, 
         z = torch.empty((M, subset.n), dtype=torch.float32, device=dev) if want_z else None
     else:
         q, scale, z = out
-    need = cloud_partial_workspace(M, subset)
     if workspace is None:
+        need = cloud_partial_workspace(M, subset)
         workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=dev)
     check(lib.sph_cloud_partial_fmt(
         h_cloud.data_ptr(), h_cloud.stride(0) if M > 0 else d_cloud, M, d_cloud,
@@ -385,8 +388,8 @@ def fuse_verify(q: torch.Tensor, scale: torch.Tensor, h_end: Optional[torch.Tens
         fused = torch.empty((M, subset.n), dtype=torch.float32, device=dev) if want_fused else None
     else:
         tokens, accept, fused = out
-    need = fuse_verify_workspace(M, subset, mode)
     if workspace is None:
+        need = fuse_verify_workspace(M, subset, mode)
         workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=dev)
     check(lib.sph_fuse_verify_fmt(
         q.data_ptr(), scale.data_ptr(), int(bits), int(block), hp, ldh, d_end, wp, ldw, subset.handle,
@@ -451,8 +454,8 @@ def fuse_verify_hq(q: torch.Tensor, scale: torch.Tensor, hq: torch.Tensor, h_sca
         fused = torch.empty((M, subset.n), dtype=torch.float32, device=dev) if want_fused else None
     else:
         tokens, accept, fused = out
-    need = fuse_verify_hq_workspace(M, d_end, subset, mode)
     if workspace is None:
+        need = fuse_verify_hq_workspace(M, d_end, subset, mode)
         workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=dev)
     check(lib.sph_fuse_verify_hq(
         q.data_ptr(), scale.data_ptr(), int(bits), int(block), hp, ldh, sp, d_end, wp, ldw,

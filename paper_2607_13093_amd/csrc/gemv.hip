@@ -504,6 +504,26 @@ static int gemv_unr(int K, int wtype, int lpr) {
   return per_lane <= 4 ? 4 : 8;
 }
 
+// Blocks of an instantiation with `lds` bytes that are on the chip at once
+// (kMaxBlocks where the runtime cannot say).  The last answer is kept, with the
+// device and size it belongs to: the queries cost more than the launch.
+template <int MR, int LPR, int UNR, int WT, int EPI>
+static int resident_blocks(size_t lds) {
+  static std::atomic<uint64_t> known{0};  // device + 1 (8 bits), lds (24), blocks (32)
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev > 253) return kMaxBlocks;
+  const uint32_t key = (uint32_t)(dev + 1) << 24 | (uint32_t)lds;
+  const uint64_t k = known.load(std::memory_order_relaxed);
+  if ((uint32_t)(k >> 32) == key) return (int)(uint32_t)k;
+  int per_cu = 0, cus = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_gemv<MR, LPR, UNR, WT, EPI>, kBS, lds) != hipSuccess ||
+      per_cu <= 0 || cus <= 0)
+    return kMaxBlocks;
+  known.store((uint64_t)key << 32 | (uint32_t)(per_cu * cus), std::memory_order_relaxed);
+  return per_cu * cus;
+}
+
 template <int MR, int LPR, int UNR, int WT, int EPI>
 static hipError_t launch_one(GemvArgs a, hipStream_t s) {
   auto kern = k_gemv<MR, LPR, UNR, WT, EPI>;
@@ -517,14 +537,7 @@ static hipError_t launch_one(GemvArgs a, hipStream_t s) {
   const int iters = (a.n + rpi - 1) / rpi;
   // One round of resident blocks where possible: each block takes an equal
   // contiguous share of the subset positions.
-  int resident = kMaxBlocks;
-  int per_cu = 0, dev = 0, cus = 0;
-  const size_t lds_guess = hbytes + 512 * 4;
-  if (hipGetDevice(&dev) == hipSuccess &&
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kBS, lds_guess) == hipSuccess &&
-      per_cu > 0 && cus > 0)
-    resident = per_cu * cus;
+  const int resident = resident_blocks<MR, LPR, UNR, WT, EPI>(hbytes + 512 * 4);
   int grid = iters < resident ? iters : resident;
   if (grid > a.nblk) grid = a.nblk;
   int ipb = (iters + grid - 1) / grid;  // iterations per block
