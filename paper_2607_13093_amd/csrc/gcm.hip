@@ -515,6 +515,21 @@ __device__ __forceinline__ void hash_other(const uint8_t* aad, int la, int64_t L
   }
 }
 
+// A row's tag s: written (seal), or compared with the given one in constant
+// time (open).
+template <bool OPEN>
+__device__ __forceinline__ void finish_row(const uint32_t s[4], uint8_t* tg, int32_t* ok) {
+  if (OPEN) {
+    uint32_t diff = 0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) diff |= (uint32_t)((uint8_t)(s[i >> 2] >> (24 - 8 * (i & 3))) ^ tg[i]);
+    *ok = diff == 0 ? 1 : 0;
+  } else {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) tg[i] = (uint8_t)(s[i >> 2] >> (24 - 8 * (i & 3)));
+  }
+}
+
 // GHASH of a message of na AAD blocks and n data blocks is the sum of the
 // m = na + n + 1 terms X_k . H^(m+1-k) (k = 1..m, X_m the length block), and
 // the tag is that sum xor E_K(J0).  Every term is independent given the
@@ -523,13 +538,15 @@ __device__ __forceinline__ void hash_other(const uint8_t* aad, int la, int64_t L
 // the other na + 2 terms besides, in the threads after its last block: such a
 // workgroup takes the same one pass (or a second one, if its blocks leave too
 // few threads).  Each workgroup xor-reduces its terms into one 16-byte
-// partial of the row.
+// partial of the row, or into its tag where the row has one workgroup (which
+// saves the launch of k_gcm_finish: 26 rows of 3433 B 13.2 -> 9.7 us).
 // NR: 10 rounds (AES-128) or 14 (AES-256), fixed so that the rounds unroll
 template <bool OPEN, int NR>
 __global__ __launch_bounds__(1024) void k_gcm_blocks(const uint8_t* __restrict__ key_dev, const GcmSegs segs,
                                                      int64_t L, int n, int xpart, const uint8_t* __restrict__ iv,
                                                      const uint8_t* __restrict__ aad, int64_t ld_aad, int la,
-                                                     uint32_t* __restrict__ partial, int nparts) {
+                                                     uint32_t* __restrict__ partial, int nparts,
+                                                     uint8_t* __restrict__ tag, int32_t* __restrict__ ok) {
   __shared__ __attribute__((aligned(16))) GcmShared sh;
   __shared__ uint32_t red[16][4];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -578,7 +595,15 @@ __global__ __launch_bounds__(1024) void k_gcm_blocks(const uint8_t* __restrict__
     if (lane == 63) red[wave][k] = t[k];
   }
   __syncthreads();
-  if (tid < 4) {
+  if (nparts == 1) {
+    if (tid == 0) {
+      uint32_t s[4] = {0u, 0u, 0u, 0u};
+      for (int w = 0; w < (int)blockDim.x / 64; ++w)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) s[k] ^= red[w][k];
+      finish_row<OPEN>(s, tag + row * 16, ok + row);
+    }
+  } else if (tid < 4) {
     uint32_t v = 0u;
     for (int w = 0; w < (int)blockDim.x / 64; ++w) v ^= red[w][tid];
     partial[(row * nparts + blockIdx.x) * 4 + tid] = v;
@@ -689,8 +714,7 @@ __global__ __launch_bounds__(256) void k_gcm_zero(uint32_t* __restrict__ p, int 
   if (i < n) p[i] = 0u;
 }
 
-// One thread per row: the xor of the row's partials is its tag; write it
-// (seal) or compare it with the given one in constant time (open).
+// One thread per row: the xor of the row's partials is its tag.
 template <bool OPEN>
 __global__ __launch_bounds__(256) void k_gcm_finish(int rows, const uint32_t* __restrict__ partial,
                                                     int nparts, uint8_t* __restrict__ tag,
@@ -701,16 +725,7 @@ __global__ __launch_bounds__(256) void k_gcm_finish(int rows, const uint32_t* __
   for (int p = 0; p < nparts; ++p)
 #pragma unroll
     for (int k = 0; k < 4; ++k) s[k] ^= partial[(row * nparts + p) * 4 + k];
-  uint8_t* tg = tag + row * 16;
-  if (OPEN) {
-    uint32_t diff = 0;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) diff |= (uint32_t)((uint8_t)(s[i >> 2] >> (24 - 8 * (i & 3))) ^ tg[i]);
-    ok[row] = diff == 0 ? 1 : 0;
-  } else {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) tg[i] = (uint8_t)(s[i >> 2] >> (24 - 8 * (i & 3)));
-  }
+  finish_row<OPEN>(s, tag + row * 16, ok + row);
 }
 
 // Blocks a lane of k_gcm_bulk chains.  A wave's time is that of its chain and
@@ -755,7 +770,8 @@ hipError_t launch_gcm(bool open, const uint8_t* key_dev, int nr, const GcmSegs& 
     auto kern = open ? (nr == 10 ? k_gcm_blocks<true, 10> : k_gcm_blocks<true, 14>)
                      : (nr == 10 ? k_gcm_blocks<false, 10> : k_gcm_blocks<false, 14>);
     launch_kernel(kern, dim3(nparts, rows), dim3(kGcmStride * chain), 0, s, key_dev, segs, L, n, xpart, iv, aad,
-                  ld_aad, la, partial, nparts);
+                  ld_aad, la, partial, nparts, tag, ok);
+    if (nparts == 1) return hipGetLastError();
   } else {
     const int64_t others = (rows + 63) / 64 + ((int64_t)rows * ((la + 15) / 16 + 1) + 63) / 64;
     const int c = bulk_chain(rows, n, others), per_row = (n + 64 * c - 1) / (64 * c);
