@@ -184,6 +184,8 @@ SEALED = [
     (16, 33, (65535, 9), 0),       # 4097
     (16, 41, (30007, 20008), 16),  # a boundary inside a block, a ragged end
     (32, 24, (49153, 4), 1024),    # 768 threads, the largest AAD beside one block
+    (16, 9, (8128, 16), 23),       # 509 blocks, 3 other terms: one workgroup of 512 threads
+    (32, 9, (8144, 16), 23),       # one term more: two workgroups and a sum of sums
     (16, 40, (49136,), 1024),      # 1024 threads, 1023 blocks in the last sum: a second pass
 ]
 
