@@ -18,8 +18,8 @@
 //    most BN), one round of blocks on the 256 CUs per 65536 positions.  With
 //    fixed 256-position tiles 45001 positions left 80 CUs idle and 66096
 //    needed a second round for 3 tiles.
-//  * A stage is one 128-byte line of every weight row of the block (64 bf16
-//    or 128 E4M3 columns) and the same columns of h.  The lines are copied
+//  * A stage is one 128-byte line (narrow blocks: two) of every weight row of the
+//    block (64 bf16 or 128 E4M3 columns) and the same columns of h.  The lines are copied
 //    global-to-LDS (8 rows per instruction) and non-temporally: 7.3 against
 //    6.1 TB/s for plain copies in a probe of this chip; 60000 x 3840 columns
 //    18 rows 84 -> 75 us, 90 rows 93 -> 78.  That pays only for whole lines
@@ -150,10 +150,10 @@ __device__ __forceinline__ void wait_copies(int nb) {
 #undef SPH_WAIT
 }
 
-// RA stages of h and RW of weight lines: step t issues h of step t + RA - 1,
-// then line t + RW - 1.  LDS: [RA][h of BM rows][RW][a.width lines rounded up
-// to 8].
-template <int BM, int BN, int WT, int RA, int RW>
+// RA stages of h and RW of NL weight lines: step t issues h of step t + RA - 1,
+// then the lines of step t + RW - 1.  LDS: [RA][h of BM rows][RW][NL][a.width
+// lines rounded up to 8].
+template <int BM, int BN, int WT, int RA, int RW, int NL>
 __global__ __launch_bounds__(64 * stream_waves(BM)) __attribute__((amdgpu_waves_per_eu(stream_waves(BM) / 4)))
 void k_mfma_stream(const MfmaArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -163,10 +163,11 @@ void k_mfma_stream(const MfmaArgs a) {
   constexpr int WX = NW / WN;
   constexpr int WM = FR % WX == 0 ? WX : FR % 3 == 0 && WX > 3 ? 3 : FR % 2 == 0 && WX > 2 ? 2 : 1;
   constexpr int WROWS = BM / WM, WCOLS = BN / WN;        // rows and positions of a wave
-  constexpr int BK = WT == 0 ? 64 : 128;                 // columns per stage
+  constexpr int LK = WT == 0 ? 64 : 128;                 // columns per line
+  constexpr int BK = LK * NL;                            // and per stage
   constexpr int FM = WROWS / 32, FN = WCOLS / 32;
   static_assert(FM * 32 * WM == BM && FN * 32 * WN == BN && FN <= 2, "tile / waves");
-  constexpr int NA = WT == 0 ? 1 : 2;                    // 64-column pieces of h per stage
+  constexpr int NA = BK / 64;                            // 64-column pieces of h per stage
   constexpr int A_CP = NA * BM / 8;                      // copies of h per stage
   constexpr int A_INS = (A_CP + NW - 1) / NW, B_INS = BN / 8 / NW;  // copies per wave and stage
   static_assert(B_INS * 8 * NW == BN, "copies / waves");
@@ -188,15 +189,16 @@ void k_mfma_stream(const MfmaArgs a) {
   }
   const uint16_t* h = a.h + (int64_t)m0 * a.ldh;
   const int n0 = nt * a.width, w = min(a.width, n - n0);
-  const int nsteps = (K + BK - 1) / BK;
+  const int nsteps = (K + BK - 1) / BK, klines = (K + LK - 1) / LK;
   const int kch = K / (WT == 0 ? 8 : 16);  // 16-byte chunks of a weight row
   // rows start on a line, or stages t and t + 1 hold the columns of step t
   const bool aligned = ((reinterpret_cast<uintptr_t>(a.w) | (uint64_t)a.ldw_bytes) & 127) == 0;
   const int ahead = kLines && !aligned ? 1 : 0;
-  const int nlines = nsteps > 0 ? nsteps + ahead : 0;
+  const int nlines = nsteps > 0 ? nsteps + ahead : 0;  // stages of the weights
   const int groups = (w + 7) / 8;                 // weight copies per line
   const int nb = (groups - wave + NW - 1) / NW;   // this wave's
   const int wbytes = (a.width + 7) / 8 * 1024;    // a line of the block's rows
+  const int sbytes = NL * wbytes;                 // a stage of them
   const int wn = wave % WN, wm = wave / WN;
 
   // copy q of a stage's NA * BM / 8 copies of h fills 8 rows; wave w issues
@@ -242,31 +244,36 @@ void k_mfma_stream(const MfmaArgs a) {
       }
     }
   };
-  auto issueB = [&](int line, int stage) {
-    uint8_t* bs = smem + RA * ABYTES + stage * wbytes;
-    const int64_t kb = (int64_t)line * kStageRow;
-    if (line + 1 < nsteps && (line > 0 || !ahead)) {
+  auto issueB = [&](int st, int stage) {
 #pragma unroll
-      for (int i = 0; i < B_INS; ++i)
-        if (i < nb) {
-          if (kLines || aligned) put(pb[i] + kb, bs + (i * NW + wave) * 1024, Nt{});
-          else put(pb[i] + kb, bs + (i * NW + wave) * 1024, Plain{});
-        }
-    } else {
+    for (int l = 0; l < NL; ++l) {
+      const int line = st * NL + l;
+      uint8_t* bs = smem + RA * ABYTES + stage * sbytes + l * wbytes;
+      const int64_t kb = (int64_t)line * kStageRow;
+      if (line + 1 < klines && (line > 0 || !ahead)) {
 #pragma unroll
-      for (int i = 0; i < B_INS; ++i)
-        if (i < nb) {
-          const int c = chunk_of((i * NW + wave) * 8 + lr) - mb[i];
-          put(pb[i] + (min(max(line * 8 + c, 0), kch - 1) - c) * 16, bs + (i * NW + wave) * 1024, Plain{});
-        }
+        for (int i = 0; i < B_INS; ++i)
+          if (i < nb) {
+            if (kLines || aligned) put(pb[i] + kb, bs + (i * NW + wave) * 1024, Nt{});
+            else put(pb[i] + kb, bs + (i * NW + wave) * 1024, Plain{});
+          }
+      } else {
+#pragma unroll
+        for (int i = 0; i < B_INS; ++i)
+          if (i < nb) {
+            const int c = chunk_of((i * NW + wave) * 8 + lr) - mb[i];
+            put(pb[i] + (min(max(line * 8 + c, 0), kch - 1) - c) * 16, bs + (i * NW + wave) * 1024, Plain{});
+          }
+      }
     }
   };
 
   // fragment addresses: row (lane & 31) of a fragment; rows 32 apart share
   // the swizzle.  Sub-step p is 16 columns: chunks 2 p + lane / 32 of a bf16
   // row (64 columns per tile row), bytes 8 (lane / 32) of chunk p of an E4M3
-  // row.  A weight row's chunk c lies in stage t where c + its offset is below
-  // 8, else in stage t + 1 (bit 0 of adB; the addresses are multiples of 8).
+  // row.  A weight row's chunk c lies in line (c + its offset) / 8 of stage t,
+  // or past its lines in the first of stage t + 1 (bit 0 of adB; the addresses
+  // are multiples of 8).
   constexpr int NP = BK / 16;                     // sub-steps of a stage
   constexpr int NK = FM + FN <= 3 ? 4 : 2;        // of which one wait covers
   uint32_t adA[NP], adB[NP][FN];
@@ -294,7 +301,8 @@ void k_mfma_stream(const MfmaArgs a) {
 #pragma unroll
       for (int j = 0; j < FN; ++j) {
         const int c = (WT == 0 ? 2 * p + hh : p) + mis[j];
-        adB[p][j] = (rb[j] + (uint32_t)(((c & 7) ^ sw) << 4) + (WT == 0 ? 0u : 8u * hh)) | (c >= 8 ? 1u : 0u);
+        adB[p][j] = (rb[j] + (c >= 8 * NL ? 0u : (uint32_t)((c >> 3) * wbytes)) + (uint32_t)(((c & 7) ^ sw) << 4) +
+                     (WT == 0 ? 0u : 8u * hh)) | (c >= 8 * NL ? 1u : 0u);
       }
     }
   }
@@ -329,14 +337,14 @@ void k_mfma_stream(const MfmaArgs a) {
     // (D = RA - 1 whole steps less the first one's h)
     constexpr int X0 = (D0 == RA - 1 ? D0 - 1 : D0) * A_INS, X1 = D1 < 0 ? 0 : (D1 == RA - 1 ? D1 - 1 : D1) * A_INS;
     if (t + RX - 1 >= nsteps) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    else if (kLines && ahead) wait_copies<X1, D1 < 0 ? 0 : D1>(nb);
-    else wait_copies<X0, D0>(nb);
+    else if (kLines && ahead) wait_copies<X1, D1 < 0 ? 0 : D1 * NL>(nb);
+    else wait_copies<X0, D0 * NL>(nb);
     __builtin_amdgcn_s_barrier();
     if (t + RA - 1 < nsteps) issueA(t + RA - 1, fa);
     if (t + RW - 1 < nlines) issueB(t + RW - 1, fb);
     const int left = K - t * BK;  // columns from step t on
     const int nextb = sb + 1 == RW ? 0 : sb + 1;
-    const uint32_t oa = (uint32_t)(sa * ABYTES), so = (uint32_t)(sb * wbytes), sn = (uint32_t)(nextb * wbytes);
+    const uint32_t oa = (uint32_t)(sa * ABYTES), so = (uint32_t)(sb * sbytes), sn = (uint32_t)(nextb * sbytes);
     const bool tail = left < BK;
     if (tail) {
       // columns past K: zeros in h
@@ -445,14 +453,14 @@ void k_mfma_stream(const MfmaArgs a) {
 #endif
 }
 
-template <int BM, int BN, int WT, int RA, int RW>
+template <int BM, int BN, int WT, int RA, int RW, int NL = 1>
 static hipError_t launch_stream_tile(const MfmaArgs& a, hipStream_t s) {
   static std::atomic<uint64_t> lds_set{0};
-  constexpr int abytes = BM * (WT == 0 ? 1 : 2) * kStageRow;
-  constexpr size_t most = std::min((size_t)kLdsBytes, (size_t)RA * abytes + (size_t)RW * BN * kStageRow);
-  const size_t lds = (size_t)RA * abytes + (size_t)RW * ((a.width + 7) / 8 * 1024);
+  constexpr int abytes = BM * (WT == 0 ? 1 : 2) * NL * kStageRow;
+  constexpr size_t most = std::min((size_t)kLdsBytes, (size_t)RA * abytes + (size_t)RW * NL * BN * kStageRow);
+  const size_t lds = (size_t)RA * abytes + (size_t)RW * NL * ((a.width + 7) / 8 * 1024);
   if (lds > most || a.width > BN) return hipErrorInvalidValue;
-  auto k = k_mfma_stream<BM, BN, WT, RA, RW>;
+  auto k = k_mfma_stream<BM, BN, WT, RA, RW, NL>;
   hipError_t e = set_lds_limit_once(lds_set, reinterpret_cast<const void*>(k), most);
   if (e != hipSuccess) return e;
   launch_kernel(k, dim3((a.n + a.width - 1) / a.width * a.m_tiles), dim3(64 * stream_waves(BM)), lds, s, a);
@@ -483,17 +491,28 @@ int stream_width(int M, int n) {
   return w < 32 ? 32 : w;
 }
 
-// Stages by what fits: as many lines as possible, at least two of h.
+// Stages by what fits: as many lines as possible, at least two of h.  Narrow
+// blocks take two lines a stage where three such stages fit: with little to copy
+// and multiply a step is the barrier's and the fragment reads' latency (0.5 us
+// for 18 rows), so half as many are faster.  (us, one line / two: 18 rows x
+// 14464 x 7680 columns 66 / 51, 60 x 30000 x 3584 45 / 40, 90 x 8000 x 3584 40 /
+// 30, 256 x 8000 x 3584 in two groups 42 / 36, E4M3 30 x 5000 x 8128 52 / 41.)
 template <int BM, int WT>
 static hipError_t launch_stream_bm(const MfmaArgs& a, hipStream_t s) {
   constexpr int ak = BM * (WT == 0 ? 1 : 2) / 8;  // KB of a stage of h
-  if (a.width <= 64) {
-    constexpr int r = std::min(8, 160 / (ak + 8));
-    return launch_stream_tile<BM, 64, WT, r, r>(a, s);
+  if constexpr (BM != 160) {  // (launch_stream_rows: other row counts)
+    if (a.width <= 64) {
+      constexpr int r = std::min(8, 160 / (ak + 8)), r2 = std::min(8, 160 / (2 * (ak + 8)));
+      if constexpr (r2 >= 3) return launch_stream_tile<BM, 64, WT, r2, r2, 2>(a, s);
+      else return launch_stream_tile<BM, 64, WT, r, r>(a, s);
+    }
   }
-  if (a.width <= 128) {
-    constexpr int r = std::min(6, 160 / (ak + 16));
-    return launch_stream_tile<BM, 128, WT, r, r>(a, s);
+  if constexpr (BM != 160 && BM != 96) {
+    if (a.width <= 128) {
+      constexpr int r = std::min(6, 160 / (ak + 16)), r2 = std::min(6, 160 / (2 * (ak + 16)));
+      if constexpr (r2 >= 3) return launch_stream_tile<BM, 128, WT, r2, r2, 2>(a, s);
+      else return launch_stream_tile<BM, 128, WT, r, r>(a, s);
+    }
   }
   if constexpr (4 * (ak + 32) <= 160) {
     return launch_stream_tile<BM, 256, WT, 4, 4>(a, s);

@@ -63,6 +63,9 @@ STREAM = [
     (23, 4, 200, 9001),   # 92 rows, 36
     (31, 5, 136, 31000),  # 155 rows, 122
     (35, 5, 328, 14000),  # 175 rows, 55
+    (5, 3, 136, 4001),    # 15 rows, two lines a stage: the last one's second half empty
+    (31, 4, 1160, 9000),  # 124 rows, several rounds of its three stages
+    (12, 5, 904, 30001),  # 60 rows, 118 positions per block
 ]
 
 
