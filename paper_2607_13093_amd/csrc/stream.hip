@@ -471,7 +471,7 @@ static hipError_t launch_stream_tile(const MfmaArgs& a, hipStream_t s) {
 // faster way.  More than kStreamMaxRows rows are split into 2, 4 or 8 groups
 // (the CUs divide evenly) where 256-position tiles would leave half of the CUs
 // or more without work and the groups' shares fit one round.  (us, tiles /
-// groups, K 3584 ... 4032: 256 rows x 8000 69 / 42, 320 x 15000 99 / 65, 320 x
+// groups, K 3584 ... 4032: 256 rows x 8000 69 / 36, 320 x 15000 99 / 65, 320 x
 // 30000 103 / 93, 400 x 16000 85 / 75, 640 x 8000 88 / 64, 640 x 16000 107 /
 // 100, 1024 x 8000 83 / 76, E4M3 268 x 30000 116 / 93, 512 x 8000 83 / 47; past
 // the rule 384 x 32000 105 / 111, 768 x 16000 95 / 103, 1280 x 6000 78 / 85.)
