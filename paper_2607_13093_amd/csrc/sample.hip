@@ -33,9 +33,10 @@
 //      elements each weigh below 4e-11); a bucket's mass is estimated as its
 //      count times the weight of its middle.  Bucket order is value order, so
 //      the nucleus -- the shortest prefix of (p desc, id asc) reaching
-//      top_p * Z -- ends in or near the bucket where the running estimate
-//      reaches top_p of the total.  The window is that bucket, widened by a
-//      neighbour where the estimate lies near a bucket edge.
+//      top_p * Z -- ends near the bucket where the running estimate reaches
+//      top_p of the total.  The window is every bucket that may hold the cut,
+//      given how far off the estimate can be (pick_window); where those have
+//      more elements than the list, fewer buckets around the estimate.
 //   2. One exact pass: Z; the masses of the buckets below the window, per
 //      segment (runs of consecutive positions, at most 512 per row); the
 //      window's elements into an LDS list.  An exact histogram of the list
@@ -43,9 +44,9 @@
 //      one wave ranks its few elements by (key desc, position asc) to find
 //      the element completing the nucleus.  The nucleus is
 //      {key > T} + {key == T, position <= cut}.
-//      Should the window miss the cut (the estimate is only an estimate) or
-//      overflow the list, an exact histogram over groups of 4 buckets picks the
-//      group and the pass is redone on it; a sub-bucket holding more than 64 elements is ranked by
+//      Should a narrowed window miss the cut or overflow the list, the pass is
+//      redone on its neighbours, then an exact histogram over groups of 4
+//      buckets picks the group and the pass is redone on it; a sub-bucket holding more than 64 elements is ranked by
 //      a bitonic sort of the list, and a group with more than 1024 elements
 //      goes through an exact radix select over its keys (8 bits per pass),
 //      the cut among elements tied at the threshold key being the c-th in id
@@ -67,7 +68,7 @@ constexpr int kBuckets = 4096;     // value buckets of (fmax - f)/tau over [0, k
 constexpr int kBPT = kBuckets / kSThreads;
 constexpr int kCoarse = 1024;      // exact fallback histogram: 4 value buckets each
 constexpr int kSub = 128;          // sub-buckets per bucket of the window
-constexpr int kMaxSub = 4 * kSub;  // window of at most 4 buckets
+constexpr int kMaxSub = 4 * kSub;  // sub-buckets of a window (coarser ones past 4 buckets)
 constexpr int kMaxSeg = kSThreads; // segments per row, one per thread in scans
 constexpr int kMaxCand = 1024;     // window elements held in LDS
 constexpr int kChunk = 256;        // positions per wave iteration
@@ -333,8 +334,9 @@ struct SampleShared {
   uint64_t wkey[64];        // the crossing sub-bucket's elements
   uint64_t we[64];
   double tab[kTab];
+  float gmass[64];          // estimated masses and element counts of the 64 bucket groups
+  uint32_t gcnt[64];
   U128 xred[kSWaves], yred[kSWaves];
-  double dred[kSWaves];
   uint64_t kred[kSWaves];
   uint32_t ured[kSWaves];
   uint32_t off[64];
@@ -386,21 +388,6 @@ __device__ __forceinline__ void block_sum2_u128(U128 v, U128 w, SampleShared& sh
     sv = u128_add(sv, sh.xred[i]);
     sw = u128_add(sw, sh.yred[i]);
   }
-}
-
-__device__ double block_exscan_f64(double v, SampleShared& sh, double* total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const double inc = wave_inscan(v);
-  __syncthreads();
-  if (lane == 63) sh.dred[wave] = inc;
-  __syncthreads();
-  double base = 0.0, tot = 0.0;
-  for (int w = 0; w < kSWaves; ++w) {
-    if (w < wave) base += sh.dred[w];
-    tot += sh.dred[w];
-  }
-  *total = tot;
-  return base + inc - v;
 }
 
 __device__ uint32_t block_exscan_u32(uint32_t v, SampleShared& sh, uint32_t* total) {
@@ -474,17 +461,19 @@ __device__ __forceinline__ void for_chunks_contig(const float* __restrict__ row,
 // Few rows: the passes over a row are spread over several blocks (launch_sample
 // chooses), with the rest of the selection in one block per row as ever.
 //   k_sample_count  pass 1 over 1/p1 of a row: its bucket counts, and the
-//                   estimated masses of its 64 groups of 64 buckets
+//                   counts and estimated masses of its 64 groups of 64 buckets
 //   k_sample_mass   the window from those of all parts (a group, then a
 //                   bucket), then the exact pass over spp segments of the row
 //   k_sample<true>  takes the parts' sums and lists in place of its own passes
 
+constexpr int kCountParts = 8;   // parts of pass 1
 constexpr int kMaxParts = 32;    // parts of the exact pass
 constexpr int kPartCand = 128;   // window elements a part can list
+constexpr int kPartFull = 0x7FFFFFFF;
 constexpr int kMassThreads = 256;
 
 struct SplitScratch {
-  float* coarse;    // [M][p1][64]
+  uint2* coarse;    // [M][p1][64]: a group's count and mass
   uint32_t* count;  // [M][p1][kBuckets]
   int32_t* win;     // [M][2]: window
   uint64_t* part;   // [M][p2][4]: total (a, b), mass below the window (a, b)
@@ -494,9 +483,87 @@ struct SplitScratch {
   int p1, p2, spp;
 };
 
+// Estimated mass of c elements of bucket b: c times the weight of its middle.
 constexpr float kBucketStep = kYSpan / kBuckets;
-// error of the estimated masses, of their total: the spread inside the buckets
-constexpr double kSlack = 1e-4;
+__device__ __forceinline__ float bucket_weight(int b) { return __expf(-kBucketStep * ((float)b + 0.5f)); }
+// An element's weight is within a factor exp(+-kBucketStep / 2) of its bucket's
+// middle: 2.934e-3 of it, and 2.6e-5 for the float arithmetic (the place of an
+// element, exponentials, sums).  The last bucket's elements count as nothing:
+// each weighs below kLastWeight.
+constexpr double kMassErr = 2.96e-3, kLastWeight = 3.9e-11;
+
+// The window [lo, hi], found by a wave: lane g has the estimated mass and the
+// element count of group g (64 buckets), bucket(b) gives a bucket's count.
+// With A the estimated mass up to some bucket and Z that of all, A - p Z =
+// (1 - p) A - p (Z - A) decides whether the cut lies past it, and is off by at
+// most
+//   err(A) = kMassErr ((1 - p) (A - 1) + p (Z - A)) + p n kLastWeight,
+// as the row's maximum weighs 1 exactly and is counted so.  [lo, hi] is what
+// lies within err, so it holds the cut.  With more than kSureCand elements
+// there, none of which weighs much, the errors of the estimate average out, and
+// a shorter list is faster (640 rows of 65536 normal logits of sigma / tau 1.5:
+// 106 us, 111 with the whole of err): a quarter of err, a sixteenth if those are
+// more than `cap`, else the estimate's bucket alone.  A window that misses the
+// cut costs a further exact pass in the row's block, and one such row the whole
+// launch.  (us of the sampler with the estimate's bucket, widened within 1e-4 Z
+// of its edges, an error that a few large weights exceed / now: 640 x 65536, one
+// id of 0.8 of the mass and a normal tail, top_p 0.8, 228 / 103; sigma / tau 4,
+// top_p 0.9, 181 / 94; 64 x 65536 of it 112 / 36; 128 x 150000 339 / 71.)
+constexpr uint32_t kSureCand = 64;
+template <class B>
+__device__ __forceinline__ void pick_window(double p, int n, uint32_t cap, double mass, uint32_t count,
+                                            B&& bucket, int& lo, int& hi) {
+  const int lane = threadIdx.x & 63;
+  auto of_lane = [](double v, int l) {
+    return __longlong_as_double((long long)readlane_u64((uint64_t)__double_as_longlong(v), l));
+  };
+  if (lane == 0) mass += 1.0 - (double)bucket_weight(0);
+  const double inc = wave_inscan(mass);
+  const uint32_t kinc = wave_inscan(count);
+  const double Z = of_lane(inc, 63), need = p * Z, last = p * (double)n * kLastWeight;
+  auto err = [&](double A) { return kMassErr * ((1.0 - p) * fmax(A - 1.0, 0.0) + p * (Z - A)) + last; };
+  // buckets of the group looked at last: counts up to and in a lane's, masses up to it
+  int cg = -1;
+  uint32_t ck = 0u, cb = 0u;
+  double cA = 0.0;
+  // the first bucket whose A reaches `need` with f err(A) added, and the elements
+  // before it and up to it (bucket kBuckets: none does)
+  auto first = [&](double f, uint32_t& before, uint32_t& upto) {
+    const uint64_t hit = __ballot(inc + f * err(inc) >= need);
+    if (!hit) {
+      before = upto = (uint32_t)n;
+      return kBuckets;
+    }
+    const int g = __ffsll((unsigned long long)hit) - 1;
+    if (g != cg) {
+      cg = g;
+      const uint32_t k = bucket(64 * g + lane);
+      double d = (double)((float)k * bucket_weight(64 * g + lane));
+      if (g == 0 && lane == 0) d += 1.0 - (double)bucket_weight(0);
+      cA = of_lane(inc - mass, g) + wave_inscan(d);
+      ck = (uint32_t)__builtin_amdgcn_readlane((int)(kinc - count), g) + wave_inscan(k);
+      cb = ck - k;
+    }
+    const uint64_t hit2 = __ballot(cA + f * err(cA) >= need);
+    const int l = hit2 ? __ffsll((unsigned long long)hit2) - 1 : 63;  // (63: rounding of the group's sum)
+    before = (uint32_t)__builtin_amdgcn_readlane((int)cb, l);
+    upto = (uint32_t)__builtin_amdgcn_readlane((int)ck, l);
+    return 64 * g + l;
+  };
+  double f = 1.0;
+  for (int level = 0;; ++level, f *= 0.25) {
+    uint32_t b0, b1, other;
+    if (level == 3) f = 0.0;
+    lo = min(first(f, b0, other), kBuckets - 1);
+    if (level == 3) break;
+    hi = first(-f, other, b1);
+    if (b1 - b0 <= (level == 0 ? kSureCand : cap)) {
+      hi = min(hi, kBuckets - 1);
+      return;
+    }
+  }
+  hi = lo;
+}
 
 template <int NT>
 __device__ __forceinline__ float row_max(const unsigned long long* __restrict__ keys, int nblk,
@@ -509,6 +576,26 @@ __device__ __forceinline__ float row_max(const unsigned long long* __restrict__ 
 #pragma unroll
   for (int w = 0; w < NT / 64; ++w) k = max(k, red[w]);
   return from_orderable((uint32_t)(k >> 32));
+}
+
+// Counts c of thread t's kBPT buckets; count k and estimated mass d of its group
+// (valid in every eighth thread).
+__device__ __forceinline__ void group_sums(const uint32_t* hf, uint32_t (&c)[kBPT], float& d, uint32_t& k) {
+  static_assert(kBPT * 8 == 64, "eight threads per group");
+  const int b0 = kBPT * threadIdx.x;
+  d = 0.0f;
+  k = 0u;
+#pragma unroll
+  for (int i = 0; i < kBPT; ++i) {
+    c[i] = hf[b0 + i];
+    k += c[i];
+    d += (float)c[i] * bucket_weight(b0 + i);
+  }
+#pragma unroll
+  for (int o = 1; o < 8; o *= 2) {
+    k += __shfl_xor(k, o, 64);
+    d += __shfl_xor(d, o, 64);
+  }
 }
 
 __global__ __launch_bounds__(kSThreads) void k_sample_count(const float* __restrict__ f, int n,
@@ -534,21 +621,13 @@ __global__ __launch_bounds__(kSThreads) void k_sample_count(const float* __restr
   });
   __syncthreads();
   const int64_t at = (int64_t)m * sc.p1 + part;
-  float d = 0.0f;
-  uint32_t c[kBPT];
-#pragma unroll
-  for (int i = 0; i < kBPT; ++i) {
-    c[i] = hf[kBPT * t + i];
-    d += (float)c[i] * __expf(-kBucketStep * ((float)(kBPT * t + i) + 0.5f));
-  }
+  float d;
+  uint32_t k, c[kBPT];
+  group_sums(hf, c, d, k);
 #pragma unroll
   for (int i = 0; i < kBPT; i += 4)
     *reinterpret_cast<uint4*>(sc.count + at * kBuckets + kBPT * t + i) = make_uint4(c[i], c[i + 1], c[i + 2], c[i + 3]);
-  d += __shfl_xor(d, 1, 64);
-  d += __shfl_xor(d, 2, 64);
-  d += __shfl_xor(d, 4, 64);
-  static_assert(kBPT * 8 == 64, "eight threads per group");
-  if ((t & 7) == 0) sc.coarse[at * 64 + (t >> 3)] = d;
+  if ((t & 7) == 0) sc.coarse[at * 64 + (t >> 3)] = make_uint2(k, __float_as_uint(d));
 }
 
 __global__ __launch_bounds__(kMassThreads) void k_sample_mass(const float* __restrict__ f, int n,
@@ -571,27 +650,28 @@ __global__ __launch_bounds__(kMassThreads) void k_sample_mass(const float* __res
   if (t == 0) s_cnt = 0u;
   int lo = kBuckets, hi = kBuckets - 1;  // top_p 1: every bucket below lo, no window
   if (top_p < 1.0f && wave == 0) {
-    double c = 0.0;
-    for (int i = 0; i < sc.p1; ++i) c += (double)sc.coarse[((int64_t)m * sc.p1 + i) * 64 + lane];
-    const double inc = wave_inscan(c);
-    auto lane_f64 = [](double v, int l) {
-      return __longlong_as_double((long long)readlane_u64((uint64_t)__double_as_longlong(v), l));
-    };
-    const double ztot = lane_f64(inc, 63), need_a = (double)top_p * ztot, slack = kSlack * ztot;
-    const uint64_t hit = __ballot(inc - c < need_a && inc >= need_a);
-    lo = kBuckets - 2;
-    if (hit) {
-      const int g = __ffsll((unsigned long long)hit) - 1;
-      uint32_t k = 0u;
-      for (int i = 0; i < sc.p1; ++i) k += sc.count[((int64_t)m * sc.p1 + i) * kBuckets + g * 64 + lane];
-      const double d = (double)((float)k * __expf(-kBucketStep * ((float)(g * 64 + lane) + 0.5f)));
-      const double in2 = lane_f64(inc - c, g) + wave_inscan(d);
-      const uint64_t hit2 = __ballot(in2 >= need_a);
-      const int l = hit2 ? __ffsll((unsigned long long)hit2) - 1 : 63;  // (63: rounding of the group's sum)
-      const int b = g * 64 + l;
-      lo = lane_f64(in2 - d, l) >= need_a - slack && b > 0 ? b - 1 : b;
-      hi = lane_f64(in2, l) <= need_a + slack && b < kBuckets - 1 ? b + 1 : b;
+    // (the parts' values are all loaded before the first is used)
+    uint2 cg[kCountParts];
+#pragma unroll
+    for (int i = 0; i < kCountParts; ++i)
+      cg[i] = sc.coarse[((int64_t)m * sc.p1 + min(i, sc.p1 - 1)) * 64 + lane];
+    double mass = 0.0;
+    uint32_t count = 0u;
+#pragma unroll
+    for (int i = 0; i < kCountParts; ++i) {
+      mass += i < sc.p1 ? (double)__uint_as_float(cg[i].y) : 0.0;
+      count += i < sc.p1 ? cg[i].x : 0u;
     }
+    auto bucket = [&](int b) {
+      uint32_t c[kCountParts], k = 0u;
+#pragma unroll
+      for (int i = 0; i < kCountParts; ++i) c[i] = sc.count[((int64_t)m * sc.p1 + min(i, sc.p1 - 1)) * kBuckets + b];
+#pragma unroll
+      for (int i = 0; i < kCountParts; ++i) k += i < sc.p1 ? c[i] : 0u;
+      return k;
+    };
+    // (parts have room for twice their share)
+    pick_window((double)top_p, n, (uint32_t)min(kMaxCand, kPartCand / 2 * sc.p2), mass, count, bucket, lo, hi);
   }
   if (wave == 0 && lane == 0) {
     s_win[0] = lo;
@@ -788,7 +868,8 @@ __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(6))) 
     // barriers: segments and list complete
     block_sum2_u128(u128_join(za, zb), u128_join(ma, mb), sh, Z, above);
   };
-  // The same from the parts that k_sample_mass wrote.
+  // The same from the parts that k_sample_mass wrote (kPartFull if a part
+  // listed more than it has room for although the list has).
   auto gather = [&](U128& Z, U128& above) {
     const uint64_t* pt = sc.part + (int64_t)m * sc.p2 * 4;
     U128 z{0ull, 0ull}, a{0ull, 0ull};
@@ -807,7 +888,10 @@ __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(6))) 
       const uint32_t inc = wave_inscan(c);
       const bool fits = __ballot(c > (uint32_t)kPartCand) == 0ull;
       if (lane <= sc.p2) sh.off[lane] = inc - c;  // (lane p2: the total)
-      if (lane == 0) sh.ncand = fits ? (int)__builtin_amdgcn_readlane((int)inc, 63) : kMaxCand + 1;
+      if (lane == 0) {
+        const int nc = __builtin_amdgcn_readlane((int)inc, 63);
+        sh.ncand = fits || nc > kMaxCand ? nc : kPartFull;
+      }
     }
     block_sum2_u128(z, a, sh, Z, above);  // (and its barriers)
     if (sh.ncand <= kMaxCand) {
@@ -844,54 +928,37 @@ __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(6))) 
       }
     });
     __syncthreads();
-    float d[kBPT];
-    double dl = 0.0;
-    {
-      // weight of the middle of thread t's first bucket, then from bucket to bucket
-      float w = __expf(-kBucketStep * ((float)(kBPT * t) + 0.5f));
-      constexpr float kRatio = 0.994157758f;  // exp(-kBucketStep)
-#pragma unroll
-      for (int i = 0; i < kBPT; ++i) {
-        d[i] = (float)sh.u.hf[kBPT * t + i] * w;
-        dl += (double)d[i];
-        w *= kRatio;
-      }
-    }
-    double ztot;
-    double acc = block_exscan_f64(dl, sh, &ztot);
-    const double need_a = (double)top_p * ztot;
-    const double slack = kSlack * ztot;
-#pragma unroll
-    for (int i = 0; i < kBPT; ++i) {
-      if (acc < need_a && acc + (double)d[i] >= need_a) {
-        const int b = kBPT * t + i;
-        sh.lo = (acc >= need_a - slack && b > 0) ? b - 1 : b;
-        sh.hi = (acc + (double)d[i] <= need_a + slack && b < kBuckets - 1) ? b + 1 : b;
-        sh.bsel = b;
-      }
-      acc += (double)d[i];
+    float d;
+    uint32_t k, c[kBPT];
+    group_sums(sh.u.hf, c, d, k);
+    if ((t & 7) == 0) {
+      sh.gmass[t >> 3] = d;
+      sh.gcnt[t >> 3] = k;
     }
     __syncthreads();
-    if (sh.bsel >= 0) {
-      lo = sh.lo;
-      hi = sh.hi;
-    } else {
-      lo = kBuckets - 2;
-      hi = kBuckets - 1;
+    if (wave == 0) {
+      pick_window((double)top_p, n, (uint32_t)kMaxCand, (double)sh.gmass[lane], sh.gcnt[lane],
+                  [&](int b) { return sh.u.hf[b]; }, lo, hi);
+      if (lane == 0) {
+        sh.lo = lo;
+        sh.hi = hi;
+      }
     }
-    __syncthreads();
+    __syncthreads();  // (and the list may take the histogram's place)
+    lo = sh.lo;
+    hi = sh.hi;
   }
 
   // 2. exact pass: Z, segment masses below the window, the window's list; then
-  // the list's sub-bucket that holds the cut.  The estimate may have missed the
-  // cut by a bucket, or a widened window overflow the list: the pass is redone
-  // on another window next to it, three times at most, then on the group of 4
-  // buckets that an exact histogram gives.
+  // the list's sub-bucket that holds the cut.  A narrowed window may have missed
+  // the cut, or overflow the list: the pass is redone on another window next to
+  // it, three times at most, then on the group of 4 buckets that an exact
+  // histogram gives.
   U128 need{0ull, 0ull}, above;
-  int nc = 0, nsub = 0, ss = -1;
+  int nc = 0, nsub = 0, wsh = 0, ss = -1;
   auto sub_of = [&](uint64_t key) {
     const float x = from_orderable(~(uint32_t)(key >> 32));
-    return min(max(subbucket_of(ypos(x, vmax, kb)) - kSub * lo, 0), nsub - 1);
+    return min(max(subbucket_of(ypos(x, vmax, kb)) - kSub * lo, 0) >> wsh, nsub - 1);
   };
   bool group = false;  // [lo, hi] holds the cut
   for (int tries = 0;; ++tries) {
@@ -907,7 +974,8 @@ __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(6))) 
     const bool below = !u128_lt(above, need), over = nc > kMaxCand;
     if (!below && !over) {
       // exact histogram of the list over sub-buckets of the window
-      nsub = kSub * (hi - lo + 1);
+      wsh = hi - lo < 4 ? 0 : 30 - __clz(hi - lo);  // so that kSub (hi - lo + 1) >> wsh <= kMaxSub
+      nsub = min(kMaxSub, kSub * (hi - lo + 1));
       sh.u.c.sa[t] = 0ull;
       sh.u.c.sb[t] = 0ull;
       sh.u.c.scnt[t] = 0u;
@@ -934,7 +1002,9 @@ __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(6))) 
     }
     if (group) break;
     __syncthreads();
-    if (tries < 3 && below && lo > 0) {
+    if (SPLIT && nc == kPartFull && !below) {
+      // the same window in this block
+    } else if (tries < 3 && below && lo > 0) {
       hi = lo - 1;
       lo = max(0, lo - 2);
     } else if (tries < 3 && !below && over && hi > lo) {
@@ -1318,7 +1388,7 @@ static SplitPlan split_plan(int M, int n) {
   const int G = kChunk * std::max(kSegChunks, (n + kChunk * kMaxSeg - 1) / (kChunk * kMaxSeg));
   const int NS = (n + G - 1) / G;
   SplitPlan p;
-  p.p1 = std::min(8, (NC + 31) / 32);
+  p.p1 = std::min(kCountParts, (NC + 31) / 32);
   p.spp = 4 * ((NS + 4 * kMaxParts - 1) / (4 * kMaxParts));
   p.p2 = (NS + p.spp - 1) / p.spp;
   return p;
@@ -1333,7 +1403,7 @@ static size_t take(uint8_t* base, size_t& at, size_t bytes, void** out) {
 static size_t split_layout(int M, const SplitPlan& p, uint8_t* base, SplitScratch* sc) {
   size_t at = 0;
   void* q[7];
-  take(base, at, (size_t)M * p.p1 * 64 * 4, &q[0]);
+  take(base, at, (size_t)M * p.p1 * 64 * 8, &q[0]);
   take(base, at, (size_t)M * p.p1 * kBuckets * 4, &q[1]);
   take(base, at, (size_t)M * 8, &q[2]);
   take(base, at, (size_t)M * p.p2 * 32, &q[3]);
@@ -1341,7 +1411,7 @@ static size_t split_layout(int M, const SplitPlan& p, uint8_t* base, SplitScratc
   take(base, at, (size_t)M * kMaxSeg * 16, &q[5]);
   take(base, at, (size_t)M * p.p2 * kPartCand * 16, &q[6]);
   if (sc)
-    *sc = SplitScratch{(float*)q[0], (uint32_t*)q[1], (int32_t*)q[2], (uint64_t*)q[3],
+    *sc = SplitScratch{(uint2*)q[0], (uint32_t*)q[1], (int32_t*)q[2], (uint64_t*)q[3],
                        (uint32_t*)q[4], (uint64_t*)q[5], (uint64_t*)q[6], p.p1, p.p2, p.spp};
   return at;
 }

@@ -138,6 +138,74 @@ def test_sampling_few_long_rows(shape):
     sub.close()
 
 
+def _rows(M, n, kind, seed):
+    """Fused logits of M rows at tau 1: normal ones of deviation s, for "top" with
+    one id besides that has share p of the mass, for "zipf" 200 ids that have it
+    (through the payload: 8-bit codes of their logits), for "crowd" with all ids
+    but the first 4096 far below."""
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    shape, s, p = kind
+    h = torch.randn((M, 64), device="cuda", generator=g)
+    h = (h * (8.0 / h.norm(dim=1, keepdim=True))).to(torch.bfloat16)
+    w = (torch.randn((n, 64), device="cuda", generator=g) * (s / 8.0)).to(torch.bfloat16)
+    q = torch.zeros((M, n), dtype=torch.int8, device="cuda")
+    scale = torch.ones((M,), device="cuda")
+    if shape == "crowd":
+        q[:, 4096:] = -127
+        scale[:] = 0.4
+    elif shape != "normal":
+        ids = torch.stack([torch.randperm(n, device="cuda", generator=g)[:1 if shape == "top" else 200] for _ in range(M)])
+        lw = -1.1 * torch.log(torch.arange(1, ids.shape[1] + 1, device="cuda").double())
+        lw += np.log(n) + s * s / 2 + np.log(p / (1 - p)) - torch.logsumexp(lw, 0)
+        scale[:] = float(lw.max()) / 127.0
+        q.scatter_(1, ids, (lw * (127.0 / lw.max())).round().clamp(0, 127).to(torch.int8).expand(M, -1).contiguous())
+    return q, scale, h, w
+
+
+# (kind, top_p): a few ids hold much of the mass and the cut lies just past them
+# (in a thin tail or a crowded one), between them, or where ids are far apart;
+# and a window whose ids all lie in one block's part, which cannot list them
+PEAKED = [(("top", 1.0, 0.8), 0.8), (("top", 0.3, 0.5), 0.5), (("top", 1.0, 0.8), 0.9), (("top", 2.0, 0.8), 0.8),
+          (("zipf", 1.5, 0.7), 0.8), (("normal", 4.0, 0), 0.9), (("normal", 6.0, 0), 0.95),
+          (("crowd", 0.05, 0), 0.7)]
+
+
+@pytest.mark.parametrize("split", [True, False], ids=["split", "one_block"])
+@pytest.mark.parametrize("kind,top_p", PEAKED, ids=[f"{k[0]}s{k[1]}m{k[2]}-p{p}" for k, p in PEAKED])
+def test_sampling_peaked_rows(kind, top_p, split):
+    """Rows with a few large weights sample what the oracle does, in one exact pass
+    like flat ones: a second one over 65536 positions takes longer than half of the
+    whole launch."""
+    import oracle
+    from test_gpu_sampling import _exempt
+
+    M, n, seed = 48, 65536, 11
+    sub = sph.Subset(vocab=n, full=True)
+    full = sph.fuse_verify_workspace(M, sub, sph.SAMPLE)
+    base = M * 16384 + M * n * 4
+    assert full > base and base % 256 == 0
+    ws = torch.empty((full if split else base,), dtype=torch.uint8, device="cuda")
+    best, out = [], None
+    for k, p in ((("normal", 1.5, 0), 0.9), (kind, top_p)):
+        q, s, h, w = _rows(M, n, k, seed)
+        sph.trace_start(400)
+        for _ in range(20):
+            out = sph.fuse_verify(q, s, h, w, sub, M, 1, None, mode=sph.SAMPLE, temperature=1.0, top_p=p, seed=seed,
+                                  want_fused=True, workspace=ws)
+        torch.cuda.synchronize()
+        best.append(min(ms for name, ms in sph.trace_collect(400) if name == "fuse_sample"))
+    tok, _, f = out
+    rows = [0, 1, M // 2, M - 1]
+    ref, info = oracle.sample_select(f[rows].cpu().numpy(), np.arange(n, dtype=np.int32), 1.0, np.float32(top_p), seed, 1,
+                                     row_index=np.asarray(rows))
+    bad = (tok[rows].cpu().numpy() != ref) & ~_exempt(info)
+    assert not bad.any(), (tok[rows], ref)
+    print(f"sampler: flat {best[0] * 1e3:.1f} us, {kind} {best[1] * 1e3:.1f} us", flush=True)
+    if kind[0] != "crowd":
+        assert best[1] < 1.3 * best[0], best
+    sub.close()
+
+
 # (sessions, R, d_cloud, n): partial K steps and ragged edges, first of the row
 # groups of the streaming kernel (193 to 1024 rows over few positions), then of
 # the 256- and 320-row tiles
