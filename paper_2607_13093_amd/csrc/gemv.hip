@@ -425,6 +425,16 @@ void k_gemv(const GemvArgs a) {
     for (int m = 0; m < MR; ++m) acc[m] = 0.0f;
   };
 
+  // Without columns (d_end or d_cloud 0) only the epilogue is left: codes, bias.
+  if constexpr (LPR == 8 && UNR == 4) {
+    if (nchunk == 0) {
+      for (int i = 0; i < iters; ++i) {
+        load_epi(i, s_ids[pos_of(i) - r0], ecur);
+        finish(i, ecur);
+      }
+    }
+  }
+
   // Items 0 .. T-2: chunk u is consumed and its registers are refilled at
   // once with chunk u of the next item, so about UNR loads per lane stay in
   // flight through the products and the epilogue.  The last item, which
@@ -486,6 +496,7 @@ void k_gemv(const GemvArgs a) {
 // Lanes per vocabulary row: enough that each lane loads about four 16-byte
 // chunks of the row, so short rows (the endpoint slice) are not spread over
 // a whole wave and reduced across 64 lanes.
+// (8 for K = 0, whose epilogues k_gemv<.., 8, 4, ..> runs)
 int gemv_lpr(int K, int wtype) {
   const int epc = wtype == 0 ? 8 : 16;
   const int chunks = (K + epc - 1) / epc;

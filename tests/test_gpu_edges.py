@@ -336,3 +336,56 @@ def test_skinny_row_longer_than_its_lds_is_refused():
     with pytest.raises(sph.SphError, match="too large"):
         sph.cloud_partial(h, w, sub, 8.0)
     sub.close()
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("M", [1, 3, 8])
+def test_few_rows_without_endpoint_columns(M, bits):
+    """d_end = 0 on the skinny kernel: the fused logits are the dequantised payload,
+    the token its largest."""
+    n = 1571
+    g = torch.Generator(device="cuda").manual_seed(M)
+    sub = sph.Subset(vocab=n, full=True)
+    scale = torch.rand((M,), device="cuda", generator=g) * 0.05 + 0.01
+    top = 127 if bits == 8 else 7
+    codes = torch.randint(-top, top, (M, n), device="cuda", generator=g)
+    best = torch.arange(M, device="cuda") * 97 + 5
+    codes[torch.arange(M, device="cuda"), best] = top
+    if bits == 8:
+        q = codes.to(torch.int8)
+    else:
+        c = torch.nn.functional.pad(codes, (0, 1)).to(torch.uint8) & 15
+        q = c[:, 0::2] | (c[:, 1::2] << 4)
+    tok, acc, f = sph.fuse_verify(q, scale, None, None, sub, 1, M, best[:M - 1].to(torch.int32)[None] if M > 1 else None,
+                                  want_fused=True, bits=bits)
+    assert torch.equal(f, codes.float() * scale[:, None])
+    assert torch.equal(tok, best.to(torch.int32)) and int(acc) == M - 1
+    sub.close()
+
+
+@pytest.mark.parametrize("wtype", ["bf16", "fp8"])
+@pytest.mark.parametrize("M", [2, 20])
+def test_no_cloud_columns(M, wtype):
+    """d_cloud = 0 (through the C interface): the partial logits are the bias, on the
+    skinny kernel as on the streaming one."""
+    from paper_2607_13093_amd import _lib
+
+    n = 777
+    g = torch.Generator(device="cuda").manual_seed(n)
+    bias = torch.randn((n,), device="cuda", generator=g)
+    w = torch.zeros((n, 16), device="cuda", dtype=torch.bfloat16)
+    ones = torch.ones((n,), device="cuda")
+    sub = sph.Subset(vocab=n, full=True)
+    q = torch.empty((M, n), dtype=torch.int8, device="cuda")
+    s, z = torch.empty((M,), device="cuda"), torch.full((M, n), float("nan"), device="cuda")
+    ws = torch.empty((sph.cloud_partial_workspace(M, sub),), dtype=torch.uint8, device="cuda")
+    fp8 = wtype == "fp8"
+    _lib.check(_lib.load().sph_cloud_partial_fmt(
+        None, 0, M, 0, w.data_ptr(), 16, _lib.SPH_W_FP8_E4M3 if fp8 else _lib.SPH_W_BF16, ones.data_ptr() if fp8 else None,
+        bias.data_ptr(), sub.handle, 30.0, 8, 0, q.data_ptr(), s.data_ptr(), z.data_ptr(), ws.data_ptr(), ws.numel(),
+        torch.cuda.current_stream().cuda_stream))
+    assert torch.equal(z, bias.expand(M, -1))
+    amax = bias.abs().max()
+    assert torch.equal(s, (amax / 127.0).expand(M))
+    assert torch.equal(q, torch.round(bias / (amax / 127.0)).to(torch.int8).expand(M, -1))
+    sub.close()
