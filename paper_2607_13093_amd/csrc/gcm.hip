@@ -689,8 +689,9 @@ __global__ __launch_bounds__(kBulkThreads) __attribute__((amdgpu_waves_per_eu(8)
       const int64_t w = p - pieces, i = w < more ? w * 64 + lane : (w - more) * 64 + lane;
       const int64_t row = w < more ? i : i / (na + 1);
       const int u = w < more ? na + 1 : (int)(i - row * (na + 1));
+      uint32_t t[4] = {0u, 0u, 0u, 0u};
       if (row < rows) {
-        uint32_t c[4], t[4];
+        uint32_t c[4];
         if (u > na) {
           uint32_t ivw[3];
           load_iv(iv + row * 12, ivw);
@@ -702,9 +703,28 @@ __global__ __launch_bounds__(kBulkThreads) __attribute__((amdgpu_waves_per_eu(8)
           const uint32_t h4[4] = {hp[0], hp[1], hp[2], hp[3]};
           gf128_mul_comb(c, h4, t);
         }
+      }
+      // a row's terms are in lanes next to each other, the last of which adds
+      // their sum (with an atomic for every term a row's met one by one: 667 rows
+      // of 37 B with 1 KB of AAD 53 -> 19 us, 2212 of 27 KB 175 -> 116)
+      bool last = true;
+      if (w >= more && na > 0) {
+#pragma unroll
+        for (int o = 1; o < 64; o *= 2) {
+          const int r = __shfl_up((int)row, o, 64);
+          const bool mine = lane >= o && r == (int)row;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const uint32_t v = __shfl_up(t[k], o, 64);
+            t[k] ^= mine ? v : 0u;
+          }
+        }
+        const int next = __shfl_down((int)row, 1, 64);  // (by every lane)
+        last = lane == 63 || next != (int)row;
+      }
+      if (last && row < rows)
 #pragma unroll
         for (int k = 0; k < 4; ++k) atomicXor(&partial[row * 4 + k], t[k]);
-      }
     }
   }
 }

@@ -251,6 +251,8 @@ def test_tiled_cloud_projection_partial_steps(shape, wtype, fmt):
 SEALED = [
     (32, 520, (5, 2, 3), 7),       # 520 rows of one block over three segments
     (16, 520, (0,), 33),           # no data
+    (32, 667, (37,), 1024),        # rows of 65 other terms, over one wave and the next
+    (16, 700, (4, 30), 1000),      # 64, the last one short
     (32, 130, (16381, 4), 20),     # 1025 blocks a row, chained
     (16, 33, (65535, 9), 0),       # 4097
     (16, 41, (30007, 20008), 16),  # a boundary inside a block, a ragged end
@@ -290,6 +292,27 @@ def test_sealed_batches(case):
     want = torch.ones_like(ok)
     want[bad] = 0
     assert torch.equal(ok, want)
+
+
+def test_sealing_with_associated_data_costs_what_it_hashes():
+    """1 KB of AAD to every row of a batch is as many blocks more as 1 KB of data
+    without its encryption: not more time than that (the terms of a row are summed
+    before they meet in memory)."""
+    rows = 1500
+    key = sph.GcmKey(bytes(range(32)))
+    g = torch.Generator(device="cuda").manual_seed(5)
+    iv = torch.randint(0, 256, (rows, 12), dtype=torch.uint8, device="cuda", generator=g)
+    best = []
+    for data, la in ((37 + 1024, 0), (37, 1024)):
+        x = torch.randint(0, 256, (rows, data), dtype=torch.uint8, device="cuda", generator=g)
+        aad = torch.randint(0, 256, (rows, la), dtype=torch.uint8, device="cuda", generator=g) if la else None
+        sph.trace_start(400)
+        for _ in range(20):
+            sph.gcm_seal_segments(key, (x,), iv, aad)
+        torch.cuda.synchronize()
+        best.append(min(ms for name, ms in sph.trace_collect(400)))
+    print(f"sealed: data {best[0] * 1e3:.1f} us, AAD {best[1] * 1e3:.1f} us", flush=True)
+    assert best[1] < 1.3 * best[0], best
 
 
 @pytest.mark.parametrize("M,n", [(37, 1001), (300, 33025), (1030, 259)], ids=["stream", "tiles320", "tiles256"])
