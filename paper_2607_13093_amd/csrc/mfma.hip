@@ -952,11 +952,24 @@ static hipError_t launch_bm(const MfmaArgs& a, hipStream_t s) {
 // (256 rows).  Where the tile rule picks
 // 320 rows the separate quantiser is used: on 640 rows, 256-row tiles with
 // the fused quantiser ran 598 us against 428 + 43 us.
-bool mfma_quantises_in_epilogue(int M) { return mfma_bm(M) != 320; }
+// With a partial last K step only where there are four rounds of tiles or more
+// (a tile's quantising epilogue keeps its CU some 30 us, the separate one
+// shares out evenly), and for E4M3 weights, whose steps hide less of it, only
+// for long K and code rows that start on 128-byte lines.  (us, in the epilogue /
+// separate, bf16: 1964 rows x 863 positions x 208 columns 45 / 21, 512 x 100000 x
+// 1008 243 / 224, 1200 x 60000 x 1008 291 / 279, 2048 x 32768 x 1008 240 / 265,
+// 1024 x 128256 x 4016 1248 / 1300; E4M3: 2048 x 32768 x 1008 264 / 257, x 4016
+// 572 / 590, 2048 x 60000 x 208 353 / 291, x 4016 1105 / 1073.)
+bool mfma_quantises_in_epilogue(int M, int n, int K, int wtype, int bits) {
+  if (mfma_bm(M) == 320) return false;
+  if (K % kBK == 0) return true;
+  if (mfma_tiles(M, n) < 4 * kCUs) return false;
+  return wtype == 0 || (K >= 2048 && (int64_t)n * bits % (128 * 8) == 0);
+}
 
 template <int WT>
 static hipError_t launch_bm_q(const MfmaArgs& a, hipStream_t s) {
-  if (!mfma_quantises_in_epilogue(a.M)) return hipErrorInvalidValue;
+  if (!mfma_quantises_in_epilogue(a.M, a.n, a.K, WT, a.qout_bits)) return hipErrorInvalidValue;
   return launch_tile<256, kMfmaBN, WT, kEpiCloudQ>(a, s);
 }
 

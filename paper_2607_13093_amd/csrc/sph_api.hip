@@ -439,7 +439,8 @@ int sph_cloud_partial_fmt(const void* h_cloud, int64_t ldh, int64_t M, int64_t d
     a.bias = bias;
     a.clip = clip_c;
     const bool few = sph::stream_groups((int)M, (int)n) > 0;
-    if (!few && block == sph::kMfmaBN && sph::mfma_quantises_in_epilogue((int)M)) {
+    if (!few && block == sph::kMfmaBN &&
+        sph::mfma_quantises_in_epilogue((int)M, (int)n, (int)d_cloud, wtype, bits)) {
       // a scale block is one 256-position tile: the projection's epilogue
       // quantises from its accumulators, z is written only on request
       a.z = z_out;

@@ -161,8 +161,8 @@ hipError_t launch_stream(int wtype, MfmaArgs a, hipStream_t s);
 hipError_t launch_fuse_mfma(const MfmaArgs& a, hipStream_t s);
 // its argmax keys go to slot j / tile, fuse_n_tiles of them
 int fuse_n_tiles(int M, int n, int K);
-// true where the cloud projection can quantise blocks of 256 positions in its epilogue
-bool mfma_quantises_in_epilogue(int M);
+// true where the cloud projection quantises blocks of 256 positions in its epilogue
+bool mfma_quantises_in_epilogue(int M, int n, int K, int wtype, int bits);
 int mfma_n_tiles(int n);
 int mfma_tiles(int M, int n);  // all tiles of the cloud projection
 

@@ -244,6 +244,41 @@ def test_tiled_cloud_projection_partial_steps(shape, wtype, fmt):
     run_format_case(make_workload(cfg), fmt[0], fmt[1], f"tiles {shape} {wtype} {fmt}", sessions=sessions)
 
 
+@pytest.mark.parametrize("wtype,d_cloud", [("bf16", 72), ("fp8", 2064)])
+def test_block_quantising_epilogue_with_a_partial_step(wtype, d_cloud):
+    """1028 rows x 52736 positions: enough tiles (five row tiles by 206) for the
+    quantising epilogue in spite of the partial K step."""
+    cfg = Config("tiles_q", 870, d=d_cloud + 8, d_end=8, vocab=53000, n_sub=52736, subset_kind="choice",
+                 sessions=257, rows_per_session=4, wtype=wtype, with_bias=True)
+    run_format_case(make_workload(cfg), 4, 256, f"quantising tiles {wtype}", sessions=[0, 128, 256])
+
+
+def _cloud_us(M, n, K, block):
+    g = torch.Generator(device="cuda").manual_seed(K)
+    h = torch.randn((M, K), device="cuda", generator=g).to(torch.bfloat16)
+    w = torch.randn((n, K), device="cuda", generator=g).to(torch.bfloat16)
+    sub = sph.Subset(vocab=n, full=True)
+    sph.trace_start(400)
+    for _ in range(20):
+        sph.cloud_partial(h, w, sub, 30.0, block=block)
+    torch.cuda.synchronize()
+    t = sph.trace_collect(400)
+    sub.close()
+    names = sorted({k for k, _ in t})
+    return sum(min(ms for k, ms in t if k == name) for name in names) * 1e3, names
+
+
+def test_few_tiles_with_a_partial_step_quantise_apart():
+    """32 tiles of a 208-column projection: blocks of 256 positions cost what blocks
+    of 1024 do (both by the separate quantiser), as the epilogue would keep a CU per
+    tile for longer than all the rest takes."""
+    t1024, n1 = _cloud_us(1964, 863, 208, 1024)
+    t256, n2 = _cloud_us(1964, 863, 208, 256)
+    print(f"blocks of 1024 {t1024:.1f} us, of 256 {t256:.1f} us", flush=True)
+    assert n1 == n2 == ["cloud_mfma", "cloud_quantize"]
+    assert t256 < 1.5 * t1024
+
+
 # (key bytes, rows, segment bytes, aad bytes): batches whose lanes chain blocks
 # (the last piece of a row full, one block, a few), short rows in large numbers,
 # blocks over two and three segments, and sums whose workgroup has no thread
