@@ -31,19 +31,6 @@
 
 namespace sph {
 
-// Epilogue of a BM x BN tile held as acc[FM][FN] 32x32 fragments by the
-// WM x WN waves.  Row of accumulator r in fragment (i, j):
-// 8*(r/4) + 4*(lane/32) + r%4; column: lane % 32.
-// s_q: LDS the main loop no longer needs (BM*BN bytes; kEpiCloudQ only).  The
-// caller has passed a barrier after its last LDS read.
-// z of one accumulator: fp8 row scale, then the bias (eq. 12)
-template <int WT>
-__device__ __forceinline__ float cloud_value(float dot, const MfmaArgs& a, int id) {
-  float zv = dot;
-  if constexpr (WT == 1) zv = zv * a.wscale[id];
-  if (a.bias) zv = zv + a.bias[id];
-  return zv;
-}
 
 // Descriptor of `rows` rows of z from the tile's first one (at most 320 rows of
 // 2^19 positions, below 2^30 bytes), an offset past any tile's, and the
@@ -65,6 +52,11 @@ __device__ __forceinline__ void next_row(uint32_t& off, int r, int ldz) {
   asm volatile("" : "+v"(off));
 }
 
+// Epilogue of a BM x BN tile held as acc[FM][FN] 32x32 fragments by the
+// WM x WN waves.  Row of accumulator r in fragment (i, j):
+// 8*(r/4) + 4*(lane/32) + r%4; column: lane % 32.
+// s_q: LDS the main loop no longer needs (BM*BN bytes; kEpiCloudQ only).  The
+// caller has passed a barrier after its last LDS read.
 template <int BM, int BN, int WM, int WN, int WT, int EPI, int FM, int FN>
 __device__ __forceinline__ void tile_epilogue(f32x16_t (&acc)[FM][FN], const MfmaArgs& a,
                                               const int32_t* s_ids, uint32_t* s_rmax, int m0,
@@ -113,9 +105,7 @@ __device__ __forceinline__ void tile_epilogue(f32x16_t (&acc)[FM][FN], const Mfm
         float best = 0.0f;
 #pragma unroll
         for (int j = 0; j < FN; ++j) {
-          float zv = acc[i][j][r];
-          if constexpr (WT == 1) zv = zv * cs[j];
-          if constexpr (HB) zv = hb ? zv + cb[j] : zv;
+          const float zv = cloud_value<WT>(acc[i][j][r], cs[j], HB && hb, cb[j]);
           if constexpr (ST) store_z(zv, rsrc, off + oj[j]);
           best = fmaxf(best, fminf(fabsf(zv), clip));
         }
@@ -157,6 +147,13 @@ __device__ __forceinline__ void tile_epilogue(f32x16_t (&acc)[FM][FN], const Mfm
     // stored row by row, two codes per byte for b = 4; codes of positions
     // past n are 0 (the pad nibble).
     const float qmax = a.qout_bits == 8 ? 127.0f : 7.0f;
+    float cs[FN], cb[FN];
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+      const int id = s_ids[wn * TN + j * 32 + (lane & 31)];
+      cs[j] = WT == 1 ? a.wscale[id] : 1.0f;
+      cb[j] = a.bias ? a.bias[id] : 0.0f;
+    }
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
 #pragma unroll
@@ -168,7 +165,9 @@ __device__ __forceinline__ void tile_epilogue(f32x16_t (&acc)[FM][FN], const Mfm
           const int lcol = wn * TN + j * 32 + (lane & 31);
           int code = 0;
           if (n0 + lcol < n) {
-            const float y = fminf(fmaxf(cloud_value<WT>(acc[i][j][r], a, s_ids[lcol]), -a.clip), a.clip);
+            // (without a bias 0 is added, which changes no code)
+            const float zq = cloud_value<WT>(acc[i][j][r], cs[j], true, cb[j]);
+            const float y = fminf(fmaxf(zq, -a.clip), a.clip);
             const float t = sc > 0.0f ? y / sc : 0.0f;
             code = (int)fminf(fmaxf(rintf(t), -qmax), qmax);
           }

@@ -26,6 +26,15 @@ __device__ __forceinline__ unsigned long long argmax_key_m(float v, int pos) {
   return ((unsigned long long)u << 32) | (unsigned long long)(0xFFFFFFFFu - (uint32_t)pos);
 }
 
+// z of one accumulator (eq. 12): E4M3 row scale and bias in one rounding, the same
+// wherever it is computed (the quantising epilogue computes it twice, and a code
+// belongs to the z that its scale came from).
+template <int WT>
+__device__ __forceinline__ float cloud_value(float dot, float scale, bool has_bias, float bias) {
+  if constexpr (WT == 1) return has_bias ? __builtin_fmaf(dot, scale, bias) : dot * scale;
+  else return has_bias ? dot + bias : dot;
+}
+
 constexpr int kBK = 64;          // K elements per staged step
 constexpr int kGM = 8;           // m-tiles grouped per n-tile in the tile order
 
@@ -63,7 +72,6 @@ __device__ __forceinline__ uint32_t lane_xor_u32(uint32_t v) {
 template <class T>
 __device__ __forceinline__ T vmax(T a, T b) { return a > b ? a : b; }
 
-// The 64-bit value of lane l ^ 32.
 // v of lane l ^ 32: a permlane32 swap trades lanes [32, 64) of its first
 // operand with lanes [0, 32) of its second, so with v in both a low lane
 // finds its partner's value in the second result, a high lane in the first

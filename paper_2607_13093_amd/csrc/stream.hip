@@ -427,9 +427,7 @@ void k_mfma_stream(const MfmaArgs a) {
       for (int i = 0; i < FM; ++i) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          float zv = acc[i][j][r];
-          if constexpr (WT == 1) zv = zv * cs;
-          zv = hb ? zv + cb : zv;
+          const float zv = cloud_value<WT>(acc[i][j][r], cs, hb, cb);
           const uint32_t row = (uint32_t)(wm * WROWS + i * 32 + 8 * (r >> 2) + 4 * hh + (r & 3));
           const uint32_t off = rel < w ? (row * (uint32_t)a.ldz + (uint32_t)col) * 4u : 0xF0000000u;
           __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(zv), rsrc, (int)off, 0, 0);

@@ -253,6 +253,37 @@ def test_block_quantising_epilogue_with_a_partial_step(wtype, d_cloud):
     run_format_case(make_workload(cfg), 4, 256, f"quantising tiles {wtype}", sessions=[0, 128, 256])
 
 
+@pytest.mark.parametrize("bits", [8, 4])
+def test_codes_of_the_quantising_epilogue_are_those_of_its_logits(bits):
+    """E4M3 weights with a bias: every code is the one that the written logit rounds
+    to, among enough logits (66 million) that computing them twice in two roundings
+    shows."""
+    M, n, K = 1100, 60000, 64
+    g = torch.Generator(device="cuda").manual_seed(3)
+    h = torch.randn((M, K), device="cuda", generator=g).to(torch.bfloat16)
+    w = torch.randn((n, K), device="cuda", generator=g).to(torch.float8_e4m3fn)
+    ws = torch.rand((n,), device="cuda", generator=g) * 0.3 + 0.1
+    bias = torch.randn((n,), device="cuda", generator=g)
+    sub = sph.Subset(vocab=n, full=True)
+    sph.trace_start(10)
+    q, s, z = sph.cloud_partial(h, w, sub, 6.0, w_row_scale=ws, bias=bias, want_z=True, bits=bits, block=256)
+    torch.cuda.synchronize()
+    assert [k for k, _ in sph.trace_collect(10)] == ["cloud_mfma"]  # no quantiser of its own
+    if bits == 4:
+        q = torch.stack((q & 15, q >> 4), 2).view(M, n).to(torch.int8)
+        q = torch.where(q >= 8, q - 16, q)
+    qmax = 127.0 if bits == 8 else 7.0
+    for r in range(0, M, 100):
+        y = z[r:r + 100].clamp(-6.0, 6.0)
+        a = torch.nn.functional.pad(y.abs(), (0, -n % 256)).view(len(y), -1, 256).amax(2)
+        # fp32 quotients, correctly rounded (exact enough in 64 bits before the rounding)
+        sc = (a.double() / qmax).float()
+        assert torch.equal(sc, s[r:r + 100])
+        t = (y.double() / sc.repeat_interleave(256, 1)[:, :n].double()).float().round()
+        assert torch.equal(t.to(torch.int8), q[r:r + 100]), int((t != q[r:r + 100]).sum())
+    sub.close()
+
+
 def _cloud_us(M, n, K, block):
     g = torch.Generator(device="cuda").manual_seed(K)
     h = torch.randn((M, K), device="cuda", generator=g).to(torch.bfloat16)
