@@ -644,6 +644,10 @@ void k_mfma_w1(const MfmaArgs a) {
   // are read
   w1_wait_mem();
   w1_wait_lds();
+  // (the sets that the last reads fill stay allocated until those have landed:
+  // without this a register of theirs was given to the epilogue before the wait)
+  asm volatile("" :: "v"(f0a[0]), "v"(f0a[1]), "v"(f0a[2]), "v"(f0a[3]), "v"(f0b[0]), "v"(f0b[1]), "v"(f0b[2]), "v"(f0b[3]));
+  asm volatile("" :: "v"(f1a[0]), "v"(f1a[1]), "v"(f1a[2]), "v"(f1a[3]), "v"(f1b[0]), "v"(f1b[1]), "v"(f1b[2]), "v"(f1b[3]));
   asm volatile("s_nop 7\n s_nop 7\n s_nop 7\n s_nop 7\n s_nop 7\n s_nop 7\n s_nop 7\n s_nop 7" ::: "memory");
   if constexpr (NB == 3) {
     __syncthreads();  // every wave is done with the stages: the row maxima take the first
