@@ -311,9 +311,8 @@ typedef struct sph_gcm_key_s* sph_gcm_key;
 
 /* Expand a 16- or 32-byte AES key (host memory) into a device key object
  * (round keys, tables, the powers of the GHASH key and the product tables
- * of H^256, ~272 KB); blocks
- * until the upload on `stream` has finished.  Destroy with
- * sph_gcm_key_destroy. */
+ * of H^64, ~272 KB); blocks until the upload on `stream` has finished.
+ * Destroy with sph_gcm_key_destroy. */
 int sph_gcm_key_create(const uint8_t* key, int key_bytes, void* stream, sph_gcm_key* out);
 void sph_gcm_key_destroy(sph_gcm_key key);
 

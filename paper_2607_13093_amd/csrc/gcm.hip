@@ -748,13 +748,17 @@ __global__ __launch_bounds__(256) void k_gcm_finish(int rows, const uint32_t* __
   finish_row<OPEN>(s, tag + row * 16, ok + row);
 }
 
+// Waves of k_gcm_bulk that take the rows' other terms.
+static int64_t bulk_others(int64_t rows, int64_t na) { return (rows + 63) / 64 + (rows * (na + 1) + 63) / 64; }
+
 // Blocks a lane of k_gcm_bulk chains.  A wave's time is that of its chain and
 // of its last product, which costs about 2 blocks; the waves of a SIMD share
 // it once there are 5 of them, below that a chain's latency is the time.
 // (us, 32-byte keys, chains of 1 / 2 / 3 / 4 / 5 / 7: 320 rows of 60 KB 77, 61,
 // 52, 49, 49, 58; 1024 of 16 KB 70, 59, 49, 54, 51, 57; 155 of 45 KB 38, 34,
 // 33, 34, 37, 45.)
-static int bulk_chain(int64_t rows, int64_t n, int64_t others) {
+int gcm_bulk_chain(int64_t rows, int64_t n, int64_t na) {
+  const int64_t others = bulk_others(rows, na);
   int best = 1;
   double t_best = 0;
   for (int k = 1; k <= kGcmMaxChain; ++k) {
@@ -799,8 +803,8 @@ hipError_t launch_gcm(bool open, const uint8_t* key_dev, int nr, const GcmSegs& 
                   aad, ld_aad, la, partial, one ? 1 : nparts, tag, ok);
     if (one) return hipGetLastError();
   } else {
-    const int64_t others = (rows + 63) / 64 + ((int64_t)rows * ((la + 15) / 16 + 1) + 63) / 64;
-    const int c = bulk_chain(rows, n, others), per_row = (n + 64 * c - 1) / (64 * c);
+    const int64_t na = (la + 15) / 16, others = bulk_others(rows, na);
+    const int c = gcm_bulk_chain(rows, n, na), per_row = (n + 64 * c - 1) / (64 * c);
     auto kern = open ? (nr == 10 ? k_gcm_bulk<true, 10> : k_gcm_bulk<true, 14>)
                      : (nr == 10 ? k_gcm_bulk<false, 10> : k_gcm_bulk<false, 14>);
     launch_kernel(k_gcm_zero, dim3((rows * 4 + 255) / 256), dim3(256), 0, s, partial, rows * 4);

@@ -911,6 +911,14 @@ static hipError_t launch_w1(const MfmaArgs& a, size_t lds, hipStream_t s) {
   return hipGetLastError();
 }
 
+// (the one-wave kernels copy their first steps unconditionally: they need at
+// least 6 or 2 steps; fewer take the two-wave kernel)
+int mfma_w1_stages(int K) {
+  if (K % kBK != 0 || K < 2 * kBK) return 0;
+  const int steps = K / kBK;
+  return steps % 6 == 0 ? 3 : steps % 2 == 0 ? 2 : 0;
+}
+
 template <int BM, int BN, int WT, int EPI>
 static hipError_t launch_tile(MfmaArgs a, hipStream_t s) {
   a.m_tiles = (a.M + BM - 1) / BM;
@@ -918,12 +926,9 @@ static hipError_t launch_tile(MfmaArgs a, hipStream_t s) {
   if (a.n_tiles > kMaxBlocks || a.K % (WT == 0 ? 8 : 16) != 0) return hipErrorInvalidValue;
   const bool o32 = copy_offsets_fit(a), tail = a.K % kBK != 0;
   if constexpr (BM == 256 && WT == 0 && EPI == kEpiCloud) {
-    // (the one-wave kernels copy their first steps unconditionally: they
-    // need at least 6 or 2 steps; fewer take the kernel below)
-    if (!tail && o32 && a.K >= 6 * kBK && (a.K / kBK) % 6 == 0)  // all 160 KB of LDS
-      return launch_w1<3>(a, (size_t)5 * BM * kBK * 2, s);
-    if (!tail && o32 && a.K >= 2 * kBK && (a.K / kBK) % 2 == 0)
-      return launch_w1<2>(a, mfma_dma_lds_bytes<BM, BN>(), s);
+    const int stages = o32 ? mfma_w1_stages(a.K) : 0;
+    if (stages == 3) return launch_w1<3>(a, (size_t)5 * BM * kBK * 2, s);  // all 160 KB of LDS
+    if (stages == 2) return launch_w1<2>(a, mfma_dma_lds_bytes<BM, BN>(), s);
   }
   if (o32)
     return tail ? launch_dma<BM, BN, WT, EPI, true, true>(a, s) : launch_dma<BM, BN, WT, EPI, true, false>(a, s);
@@ -935,7 +940,7 @@ static hipError_t launch_tile(MfmaArgs a, hipStream_t s) {
 // the batched shape (M = 320, 60000 ids): 320-row tiles, one per 256 ids,
 // 156 us against 265 us for 256-row tiles; M = 640 with fp8 weights: 460 us
 // against 537 us for 256-row tiles.
-static int mfma_bm(int M) {
+int mfma_bm(int M) {
   const int pad256 = (M + 255) / 256 * 256 - M;
   const int pad320 = (M + 319) / 320 * 320 - M;
   return pad320 < pad256 ? 320 : 256;

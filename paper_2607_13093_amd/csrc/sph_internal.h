@@ -158,13 +158,20 @@ constexpr int kStreamMaxRows = 192;
 int stream_groups(int M, int n);
 int stream_width(int M, int n);
 hipError_t launch_stream(int wtype, MfmaArgs a, hipStream_t s);
+// Its instance for such a call: row tile, positions per block at most, stages of
+// h and of the weights, lines a stage.
+void stream_tile(int M, int n, int wtype, int tile[5]);
 hipError_t launch_fuse_mfma(const MfmaArgs& a, hipStream_t s);
 // its argmax keys go to slot j / tile, fuse_n_tiles of them
 int fuse_n_tiles(int M, int n, int K);
 // true where the cloud projection quantises blocks of 256 positions in its epilogue
 bool mfma_quantises_in_epilogue(int M, int n, int K, int wtype, int bits);
 int mfma_n_tiles(int n);
-int mfma_tiles(int M, int n);  // all tiles of the cloud projection
+int mfma_bm(int M);            // row tile of the cloud projection
+int mfma_tiles(int M, int n);  // all its tiles
+// weight stages of the one-wave kernel for bf16 weights and 256-row tiles, 0:
+// the two-wave kernel
+int mfma_w1_stages(int K);
 
 // Clip + quantise z [M, n] to b-bit codes (bits 8 or 4; 4-bit codes two per
 // byte, low nibble first) with one scale per row (qshift < 0: from the
@@ -248,6 +255,9 @@ inline int gcm_parts(int64_t n, int64_t na, int chain, int* extra_part = nullptr
   if (extra_part) *extra_part = (int)xp;
   return (int)(xp + 1);
 }
+// Blocks that a lane chains at most where the batch is too large for one block a
+// thread (more than 512 workgroups of partial sums, or gcm_chain above 4).
+int gcm_bulk_chain(int64_t rows, int64_t n, int64_t na);
 // rows <= 65535 messages of L = segs.end[nseg-1] bytes with la <= kGcmMaxAad
 // bytes of AAD; partial: rows * gcm_parts(n, ceil(la/16), gcm_chain(rows, n))
 // * 16 bytes with n = ceil(L/16)

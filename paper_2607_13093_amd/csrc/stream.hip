@@ -451,7 +451,7 @@ void k_mfma_stream(const MfmaArgs a) {
 #endif
 }
 
-template <int BM, int BN, int WT, int RA, int RW, int NL = 1>
+template <int BM, int BN, int WT, int RA, int RW, int NL>
 static hipError_t launch_stream_tile(const MfmaArgs& a, hipStream_t s) {
   static std::atomic<uint64_t> lds_set{0};
   constexpr int abytes = BM * (WT == 0 ? 1 : 2) * NL * kStageRow;
@@ -495,30 +495,36 @@ int stream_width(int M, int n) {
 // for 18 rows), so half as many are faster.  (us, one line / two: 18 rows x
 // 14464 x 7680 columns 66 / 51, 60 x 30000 x 3584 45 / 40, 90 x 8000 x 3584 40 /
 // 30, 256 x 8000 x 3584 in two groups 42 / 36, E4M3 30 x 5000 x 8128 52 / 41.)
-template <int BM, int WT>
-static hipError_t launch_stream_bm(const MfmaArgs& a, hipStream_t s) {
+template <int BM_, int BN_, int RA_, int RW_, int NL_ = 1>
+struct StreamTile {
+  static constexpr int BM = BM_, BN = BN_, RA = RA_, RW = RW_, NL = NL_;
+};
+
+// f(StreamTile<...>{}) of the instance for row tile BM and this width
+template <int BM, int WT, class F>
+static hipError_t with_stream_tile(int width, F f) {
   constexpr int ak = BM * (WT == 0 ? 1 : 2) / 8;  // KB of a stage of h
-  if constexpr (BM != 160) {  // (launch_stream_rows: other row counts)
-    if (a.width <= 64) {
+  if constexpr (BM != 160) {  // (with_stream_rows: other row counts)
+    if (width <= 64) {
       constexpr int r = std::min(8, 160 / (ak + 8)), r2 = std::min(8, 160 / (2 * (ak + 8)));
-      if constexpr (r2 >= 3) return launch_stream_tile<BM, 64, WT, r2, r2, 2>(a, s);
-      else return launch_stream_tile<BM, 64, WT, r, r>(a, s);
+      if constexpr (r2 >= 3) return f(StreamTile<BM, 64, r2, r2, 2>{});
+      else return f(StreamTile<BM, 64, r, r>{});
     }
   }
   if constexpr (BM != 160 && BM != 96) {
-    if (a.width <= 128) {
+    if (width <= 128) {
       constexpr int r = std::min(6, 160 / (ak + 16)), r2 = std::min(6, 160 / (2 * (ak + 16)));
-      if constexpr (r2 >= 3) return launch_stream_tile<BM, 128, WT, r2, r2, 2>(a, s);
-      else return launch_stream_tile<BM, 128, WT, r, r>(a, s);
+      if constexpr (r2 >= 3) return f(StreamTile<BM, 128, r2, r2, 2>{});
+      else return f(StreamTile<BM, 128, r, r>{});
     }
   }
   if constexpr (4 * (ak + 32) <= 160) {
-    return launch_stream_tile<BM, 256, WT, 4, 4>(a, s);
+    return f(StreamTile<BM, 256, 4, 4>{});
   } else {
-    if (2 * ak + 4 * ((a.width + 7) / 8) <= 160) return launch_stream_tile<BM, 256, WT, 2, 4>(a, s);
-    if constexpr (3 * (ak + 32) <= 160) return launch_stream_tile<BM, 256, WT, 3, 3>(a, s);
-    if (2 * ak + 3 * ((a.width + 7) / 8) <= 160) return launch_stream_tile<BM, 256, WT, 2, 3>(a, s);
-    return launch_stream_tile<BM, 256, WT, 2, 2>(a, s);
+    if (2 * ak + 4 * ((width + 7) / 8) <= 160) return f(StreamTile<BM, 256, 2, 4>{});
+    if constexpr (3 * (ak + 32) <= 160) return f(StreamTile<BM, 256, 3, 3>{});
+    if (2 * ak + 3 * ((width + 7) / 8) <= 160) return f(StreamTile<BM, 256, 2, 3>{});
+    return f(StreamTile<BM, 256, 2, 2>{});
   }
 }
 
@@ -526,18 +532,37 @@ static hipError_t launch_stream_bm(const MfmaArgs& a, hipStream_t s) {
 // row fragments, which it does not divide, run as 4 and 6 (but 3 over four
 // rows of waves, at most 64 positions).  155 rows x 16000 x 3584 columns 85 ->
 // 54 us, x 30000 x 4000 102 -> 78; 90 x 30000 x 3584 64 -> 56.
+template <int WT, class F>
+static hipError_t with_stream_rows(int M, int groups, int width, F f) {
+  int fr = ((M + groups - 1) / groups + 31) / 32;
+  if (width <= 128 && (fr == 5 || (fr == 3 && width > 64))) ++fr;
+  switch (fr) {
+    case 1: return with_stream_tile<32, WT>(width, f);
+    case 2: return with_stream_tile<64, WT>(width, f);
+    case 3: return with_stream_tile<96, WT>(width, f);
+    case 4: return with_stream_tile<128, WT>(width, f);
+    case 5: return with_stream_tile<160, WT>(width, f);
+    default: return with_stream_tile<192, WT>(width, f);
+  }
+}
+
 template <int WT>
 static hipError_t launch_stream_rows(const MfmaArgs& a, hipStream_t s) {
-  int fr = ((a.M + a.m_tiles - 1) / a.m_tiles + 31) / 32;
-  if (a.width <= 128 && (fr == 5 || (fr == 3 && a.width > 64))) ++fr;
-  switch (fr) {
-    case 1: return launch_stream_bm<32, WT>(a, s);
-    case 2: return launch_stream_bm<64, WT>(a, s);
-    case 3: return launch_stream_bm<96, WT>(a, s);
-    case 4: return launch_stream_bm<128, WT>(a, s);
-    case 5: return launch_stream_bm<160, WT>(a, s);
-    default: return launch_stream_bm<192, WT>(a, s);
-  }
+  return with_stream_rows<WT>(a.M, a.m_tiles, a.width, [&](auto t) {
+    using T = decltype(t);
+    return launch_stream_tile<T::BM, T::BN, WT, T::RA, T::RW, T::NL>(a, s);
+  });
+}
+
+void stream_tile(int M, int n, int wtype, int tile[5]) {
+  auto put = [&](auto t) {
+    using T = decltype(t);
+    const int v[5] = {T::BM, T::BN, T::RA, T::RW, T::NL};
+    std::copy(v, v + 5, tile);
+    return hipSuccess;
+  };
+  const int g = std::max(1, stream_groups(M, n)), w = stream_width(M, n);
+  (void)(wtype == 0 ? with_stream_rows<0>(M, g, w, put) : with_stream_rows<1>(M, g, w, put));
 }
 
 hipError_t launch_stream(int wtype, MfmaArgs a, hipStream_t s) {

@@ -2,15 +2,15 @@
 synchronisation mode.
 
 The same verification session (5 rows) is placed, at different row offsets,
-into batches of 5, 20, 100, 300 and 400 rows, which the library runs with
-the skinny VALU kernel and with 32-, 128-, 320- and 256-row MFMA tiles (the
-last one with the session straddling two row tiles).  Every MFMA tile adds
-the products of an output element in the same order (K steps of 64, the
-32x32x16 instruction's 16 products per step), so the session's fp32
-partials, payload, fused logits, tokens and accept length must be bit
-identical across the four MFMA geometries.  The skinny kernel sums in
-another order: its partials agree within the fp32 tolerance and its tokens
-equal the MFMA ones unless a competitor lies within that bound.
+into batches of 5 to 1590 rows, which the library runs with the skinny VALU
+kernel, the streaming kernel (one group of rows and several) and 256- and
+320-row MFMA tiles (with the session straddling two row tiles).  Every MFMA
+kernel adds the products of an output element in the same order (the 32x32x16
+instruction's 16 products at a time), so the session's fp32 partials, payload,
+fused logits, tokens and accept length must be bit identical across the MFMA
+geometries.  The skinny kernel sums in another order: its partials agree within
+the fp32 tolerance and its tokens equal the MFMA ones unless a competitor lies
+within that bound.
 """
 
 import sys
@@ -23,14 +23,16 @@ import oracle
 import paper_2607_13093_amd as sph
 from synth import Config, make_drafts, make_workload
 
+import kernel_rules as rules
 import parity as P
 
 pytestmark = pytest.mark.gpu
 
 R = 5
-# (batch rows, row offset of the session): skinny, then MFMA tiles of 32,
-# 128, 320 and 256 rows (255..259 straddles the first 256-row boundary)
-GEOMETRIES = [(5, 0), (20, 15), (100, 60), (300, 250), (400, 255)]
+# (batch rows, row offset of the session, cloud kernel): 1020..1024 straddles
+# the fourth 256-row boundary
+GEOMETRIES = [(5, 0, "gemv"), (20, 15, "stream"), (100, 60, "stream"), (300, 250, "stream"),
+              (400, 255, "stream"), (1100, 1020, "w1<2>"), (1590, 1275, "dma320")]
 
 
 def say(*a):
@@ -73,15 +75,16 @@ def test_results_across_launch_geometries():
     one = cfg.replace(sessions=1)
     drafts_one = make_drafts(one, ep["tokens"], wl.subset)[0]
     res = {}
-    for M, off in GEOMETRIES:
+    for M, off, kernel in GEOMETRIES:
+        assert rules.cloud_kernel(M, cfg.n_sub, cfg.d - cfg.d_end) == kernel
         say(f"[gpu] geometry M={M} session rows {off}..{off + R - 1}")
         res[M] = _run(cfg, wl, dw, M, off, drafts_one)
     ref = res[20]
-    for M in (100, 300, 400):
+    for M in (100, 300, 400, 1100, 1590):
         r = res[M]
         for k in ("z", "f"):
             np.testing.assert_array_equal(r[k].view(np.uint32), ref[k].view(np.uint32),
-                                          err_msg=f"{k} differs between MFMA tiles (M={M})")
+                                          err_msg=f"{k} differs between MFMA kernels (M={M})")
         np.testing.assert_array_equal(r["q"], ref["q"])
         np.testing.assert_array_equal(r["s"].view(np.uint32), ref["s"].view(np.uint32))
         np.testing.assert_array_equal(r["tok"], ref["tok"])

@@ -12,6 +12,7 @@ import paper_2607_13093_amd as sph
 from oracle import gcm as ogcm
 from synth import Config, make_workload
 
+import kernel_rules as rules
 from test_gpu_payload import run_format_case
 
 pytestmark = pytest.mark.gpu
@@ -43,9 +44,10 @@ def test_endpoint_partial_steps_and_unaligned_rows(shape, fmt):
     run_format_case(make_workload(cfg), fmt[0], fmt[1], f"endpoint edge {shape} {fmt}", sessions=sessions)
 
 
-# (sessions, R, d_cloud, n): every row tile of the streaming cloud projection
-# and each of its widths (32 ... 256 positions per block), one-chunk and
-# partial K steps, weight rows that start at every 16-byte place of a line
+# (sessions, R, d_cloud, n): the row tiles of the streaming cloud projection at
+# the edges of their rows, widths (32 ... 256 positions per block) and K steps
+# (one chunk, partial steps; tests/test_gpu_instances.py has every instance with
+# long K), weight rows that start at every 16-byte place of a line
 STREAM = [
     (3, 3, 8, 33),        # 9 rows, one chunk
     (4, 8, 136, 8193),    # 32 rows, 33 positions per block, the last one
@@ -310,16 +312,16 @@ def test_few_tiles_with_a_partial_step_quantise_apart():
     assert t256 < 1.5 * t1024
 
 
-# (key bytes, rows, segment bytes, aad bytes): batches whose lanes chain blocks
-# (the last piece of a row full, one block, a few), short rows in large numbers,
-# blocks over two and three segments, and sums whose workgroup has no thread
-# left for the other terms
+# (key bytes, rows, segment bytes, aad bytes): batches whose lanes take one block
+# each (the last piece of a row one block, three, a few), short rows in large
+# numbers, blocks over two and three segments, and sums whose workgroup has no
+# thread left for the other terms
 SEALED = [
     (32, 520, (5, 2, 3), 7),       # 520 rows of one block over three segments
     (16, 520, (0,), 33),           # no data
     (32, 667, (37,), 1024),        # rows of 65 other terms, over one wave and the next
     (16, 700, (4, 30), 1000),      # 64, the last one short
-    (32, 130, (16381, 4), 20),     # 1025 blocks a row, chained
+    (32, 130, (16381, 4), 20),     # 1025 blocks a row
     (16, 33, (65535, 9), 0),       # 4097
     (16, 41, (30007, 20008), 16),  # a boundary inside a block, a ragged end
     (32, 24, (49153, 4), 1024),    # 768 threads, the largest AAD beside one block
@@ -329,11 +331,35 @@ SEALED = [
 ]
 
 
+# the same and the blocks that a lane chains: a last piece with a shorter chain and
+# a first round that is partly empty, pieces that are all whole, and segments that
+# meet inside a chained piece
+CHAINED = [
+    (32, 60, (200000,), 0, 2),          # last piece 84 blocks, two rounds
+    (16, 64, (123457,), 13, 2),
+    (16, 64, (131072, 118928), 7, 3),   # boundary on a block, last piece 73 of 192
+    (32, 320, (60000, 4), 32, 4),       # 167 of 256: three rounds, the first 39 blocks
+    (16, 1024, (16384,), 0, 4),         # whole pieces only
+    (32, 128, (150001, 49999), 64, 6),  # a boundary inside a block of a chained piece
+    (16, 256, (131, 260869), 1000, 10),
+]
+
+
+@pytest.mark.parametrize("case", CHAINED, ids=[f"k{k}r{r}L{'_'.join(map(str, b))}a{a}c{c}" for k, r, b, a, c in CHAINED])
+def test_sealed_batches_with_chains(case):
+    assert rules.gcm_chain(case[1], sum(case[2]), case[3]) == case[4]
+    _sealed(*case[:4])
+
+
 @pytest.mark.parametrize("case", SEALED, ids=[f"k{k}r{r}L{'_'.join(map(str, b))}a{a}" for k, r, b, a in SEALED])
 def test_sealed_batches(case):
+    assert rules.gcm_chain(case[1], sum(case[2]), case[3]) <= 1
+    _sealed(*case)
+
+
+def _sealed(klen, rows, seg, la):
     """A batch's rows equal the same rows sealed one at a time (and the oracle),
     and open; a changed byte fails its row alone."""
-    klen, rows, seg, la = case
     rng = np.random.default_rng(rows + sum(seg) + la)
     key = sph.GcmKey(k := rng.bytes(klen))
     x = [rng.integers(0, 256, (rows, b), dtype=np.uint8) for b in seg]

@@ -92,10 +92,10 @@ def test_large_batch():
     np.testing.assert_array_equal(np.delete(P.host(back), 5, axis=0), np.delete(pt, 5, axis=0))
 
 
-def test_longest_chains_with_a_ragged_part():
-    # 64 rows x 7717 blocks: every thread chains 16 blocks (two workgroups
-    # per row, the second ragged); two rows checked against the oracle, all
-    # rows opened, one tampered row rejected
+def test_chains_with_a_ragged_part():
+    # 64 rows x 7717 blocks: a lane chains 2 blocks, the last of a row's 61
+    # pieces has 37; two rows checked against the oracle, all rows opened, one
+    # tampered row rejected
     rng = np.random.default_rng(33)
     key = rng.bytes(16)
     rows, L, la = 64, 123457, 13

@@ -163,14 +163,14 @@ RAGGED = [
     # dense (MFMA) path: more than 8 rows
     (3, 3, 520, 40, 3000, 1001),    # 9 rows, ragged m- and n-tiles
     (8, 5, 1032, 0, 4000, 2500),    # 40 rows, d_end = 0
-    (17, 17, 1096, 72, 9000, 4097), # 289 rows: one 320-row m-tile (8 waves), ragged n
-    (24, 25, 1096, 72, 9000, 4097), # 600 rows: two 320-row m-tiles, the second ragged
-    (13, 10, 2056, 8, 9000, 8193),  # 130 rows: two m-tiles, last n-tile of one column
-    # 256-row tiles at the edges of the one-wave kernel's step counts
-    (32, 8, 128, 64, 3000, 1001),   # one K step (the two-wave kernel)
-    (32, 8, 192, 64, 3000, 1001),   # two K steps (one wave, two weight stages)
-    (32, 8, 448, 64, 3000, 1001),   # six K steps (one wave, three weight stages)
-    # 32-row tiles (9..32 rows, K a multiple of 64 in both calls)
+    # (streaming cloud projection up to 1024 rows over so few positions)
+    (17, 17, 1096, 72, 9000, 4097), # 289 rows: two groups
+    (24, 25, 1096, 72, 9000, 4097), # 600 rows: four groups
+    (13, 10, 2056, 8, 9000, 8193),  # 130 rows, a share of one position
+    (32, 8, 128, 64, 3000, 1001),   # 256 rows, one line of columns
+    (32, 8, 192, 64, 3000, 1001),   # two
+    (32, 8, 448, 64, 3000, 1001),   # six
+    # 9..32 rows, K a multiple of 64 in both calls
     (3, 3, 1088, 64, 5000, 2501),   # 9 rows
     (4, 8, 2304, 256, 9000, 4097),  # 32 rows, ragged n
     (1, 9, 4096, 256, 20000, 9001), # the decode step with k = 8 drafts
@@ -282,7 +282,8 @@ def test_fp8_cloud_partial_dense():
 
 
 def test_fp8_cloud_partial_dense_320_row_tiles():
-    # 300 rows: one 320-row tile of 8 waves, fp8 codes copied to LDS directly
+    # 300 rows: two groups of the streaming kernel (320-row tiles: from 33025
+    # positions on, test_gpu_instances.py), a 320-row tile of the endpoint
     cfg = Config("fp8_dense_320", 29, d=1088, d_end=64, vocab=7000, n_sub=3003, subset_kind="choice",
                  sessions=60, rows_per_session=5, wtype="fp8", with_bias=True)
     run_greedy_case(make_workload(cfg), tag="fp8 dense, 320-row tiles")
@@ -299,13 +300,9 @@ def test_fp8_cloud_partial_32_row_tiles():
                                                     ("bf16", 32, 8, 832), ("bf16", 50, 10, 832),
                                                     ("bf16", 32, 8, 1024)])
 def test_bias_and_weight_scales_on_whole_tiles(wtype, sessions, rows, d):
-    # 256 or 320 rows fill their row tile, so every n-tile but the last lies
-    # wholly inside z: the cloud epilogue's straight-line form adds the bias
-    # (and, for E4M3 weights, multiplies by the row scale) once per column.
-    # bf16 on 256-row tiles runs one wave per SIMD: 16 K steps (d = 1088)
-    # take two weight stages, 12 (d = 832) three, whose ragged tiles read
-    # the bias ids from global memory (500 rows: a ragged row tile too);
-    # 15 steps (d = 1024) take the two-wave kernel
+    # bias (and E4M3 row scales) of the streaming kernel's row groups: whole
+    # ones (256 rows, 320 in two) and four with a short last one (500).  The
+    # same of the tiled kernels: test_gpu_instances.py
     cfg = Config(f"whole_tiles_{wtype}_{sessions * rows}_{d}", 37, d=d, d_end=64, vocab=6000,
                  n_sub=3001, subset_kind="choice", sessions=sessions, rows_per_session=rows,
                  wtype=wtype, with_bias=True)
@@ -313,8 +310,7 @@ def test_bias_and_weight_scales_on_whole_tiles(wtype, sessions, rows, d):
 
 
 def test_fp8_cloud_partial_dense_k_not_multiple_of_64():
-    # d_cloud = 1040: the fp8 codes are widened on their way into LDS instead
-    # of being copied there directly
+    # d_cloud = 1040: the last line of a weight row holds one 16-byte chunk
     cfg = Config("fp8_dense_k", 28, d=1072, d_end=32, vocab=5000, n_sub=2999, subset_kind="choice",
                  sessions=13, rows_per_session=3, wtype="fp8")
     run_greedy_case(make_workload(cfg), tag="fp8 dense, K % 64 = 16")

@@ -12,6 +12,7 @@ import pytest
 
 from synth import Config, make_workload
 
+import kernel_rules as rules
 from test_gpu_hidden import run_hq_case
 from test_gpu_payload import run_format_case
 from test_gpu_sampling import run_sample_case
@@ -80,32 +81,50 @@ def test_random_sampling_configuration(c):
     run_sample_case(make_workload(cfg), tag=f"random sample {c['i']}")
 
 
-def _draw_one_wave(i, rng):
-    """bf16 shapes that the one-wave cloud kernel takes: 256-row tiles (129 to
-    256 rows, or 321 to 512) and an even number of 64-wide K steps, a multiple
-    of 6 in half of the cases (three weight stages)."""
+def _draw_tiles(i, rng, ranges, sessions):
+    """bf16 shapes of 256-row tiles (row counts in one of `ranges`) and an even
+    number of 64-wide K steps, a multiple of 6 in half of the cases (three weight
+    stages of the one-wave kernel)."""
     while True:
-        sessions = int(rng.integers(8, 65))
+        S = int(rng.integers(*sessions))
         R = int(rng.integers(4, 9))
-        M = sessions * R
-        if 129 <= M <= 256 or 321 <= M <= 512:
+        if any(lo <= S * R <= hi for lo, hi in ranges):
             break
     steps = int(rng.choice([6, 12, 18, 24])) if i % 2 == 0 else int(rng.choice([2, 4, 8, 10, 14, 16]))
     d_end = int(rng.choice([0, 64, 128]))
     n = int(rng.integers(1, 6001))
     V = n + int(rng.integers(0, 4000))
     bits, block = _FORMATS[int(rng.integers(0, 2))]  # per-row scales: the cloud kernel writes z
-    return dict(i=i, sessions=sessions, R=R, d=d_end + 64 * steps, d_end=d_end, V=V, n=n,
+    return dict(i=i, sessions=S, R=R, d=d_end + 64 * steps, d_end=d_end, V=V, n=n,
                 wtype="bf16", bits=bits, block=block, hq=False)
 
 
+def _tile_case(c, base, tag):
+    cfg = Config("random_one_wave", base + c["i"], d=c["d"], d_end=c["d_end"], vocab=c["V"],
+                 n_sub=c["n"], subset_kind="choice", sessions=c["sessions"], rows_per_session=c["R"],
+                 wtype="bf16", with_bias=bool(c["i"] % 3 == 1))
+    sessions = None if c["sessions"] < 65 else [0, c["sessions"] // 2, c["sessions"] - 1]
+    run_format_case(make_workload(cfg), c["bits"], c["block"], f"{tag} {_id(c)}", sessions=sessions)
+
+
+# few positions: the streaming kernel, in one or two groups of rows
 _RNG_W = np.random.default_rng(2609)
-ONE_WAVE_CASES = [_draw_one_wave(i, _RNG_W) for i in range(10)]
+GROUP_CASES = [_draw_tiles(i, _RNG_W, [(129, 256), (321, 512)], (8, 65)) for i in range(10)]
+
+
+@pytest.mark.parametrize("c", GROUP_CASES, ids=[_id(c) for c in GROUP_CASES])
+def test_row_group_cloud_configuration(c):
+    assert rules.cloud_kernel(c["sessions"] * c["R"], c["n"], c["d"] - c["d_end"]) == "stream"
+    _tile_case(c, 700, "row groups")
+
+
+# more rows than the streaming kernel takes
+_RNG_W1 = np.random.default_rng(2610)
+ONE_WAVE_CASES = [_draw_tiles(i, _RNG_W1, [(1025, 1280)], (129, 321)) for i in range(10)]
 
 
 @pytest.mark.parametrize("c", ONE_WAVE_CASES, ids=[_id(c) for c in ONE_WAVE_CASES])
 def test_one_wave_cloud_configuration(c):
-    cfg = Config("random_one_wave", 700 + c["i"], d=c["d"], d_end=c["d_end"], vocab=c["V"],
-                 n_sub=c["n"], subset_kind="choice", sessions=c["sessions"], rows_per_session=c["R"],
-                 wtype="bf16", with_bias=bool(c["i"] % 3 == 1))
-    run_format_case(make_workload(cfg), c["bits"], c["block"], f"one-wave {_id(c)}")
+    K = c["d"] - c["d_end"]
+    assert rules.cloud_kernel(c["sessions"] * c["R"], c["n"], K) == ("w1<3>" if K % 384 == 0 else "w1<2>")
+    _tile_case(c, 720, "one-wave")
