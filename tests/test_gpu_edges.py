@@ -208,6 +208,120 @@ def test_sampling_peaked_rows(kind, top_p, split):
     sub.close()
 
 
+BUCKET = np.float32(24.0 / 4096)
+
+
+def _off_middle(d, p, per, mass, before, n=65536):
+    """Logits (largest 0, tau 1) whose bucket counts mislead: a head of large weights,
+    `per` logits in each of 60 buckets around the cut of top_p = p, each of `mass` of
+    the total, and a tail; those in front of the cut lie at the start (d < 0) or the
+    end of their buckets, those behind it at the other."""
+    s, rng = float(BUCKET), np.random.default_rng(per)
+    front, back = (0.02, 0.97) if d < 0 else (0.97, 0.02)
+    head = np.r_[0.0, 3 + np.arange(20) * 2 + front]
+    q0 = int(-np.log(mass * np.exp(-head * s).sum() / p) / s)
+    i = np.arange(60)
+    cut = np.repeat(q0 + i + np.where(i < 60 * before, front, back), per)
+    w, k = np.exp(-cut * s), int(60 * before) * per
+    nt = n - len(head) - len(cut)
+    tail = (np.exp(-head * s).sum() + w[:k].sum()) * (1 - p) / p - w[k:].sum()
+    q1 = np.floor(-np.log(tail / nt) / s) + np.arange(nt) % 7 - 3 + back
+    return -(rng.permutation(np.r_[head, cut, q1]) * s).astype(np.float32)
+
+
+def _windows(f, p):
+    """The sampler's window of one row and what becomes of it: a replay of its rules
+    in 64 bits."""
+    n, last = f.size, 4095
+    b = np.minimum((f.max() - f) * np.float32(4096.0 / 24.0), np.float32(last)).astype(int)
+    count = np.bincount(b, minlength=4096)
+    k = count.astype(float)
+    k[last] = 0
+    w = np.exp(-float(BUCKET) * (np.arange(4096) + 0.5))
+    m = k * w
+    m[0] += 1 - w[0]
+    A, C = np.cumsum(m), np.r_[0, np.cumsum(k)]
+    err = 2.96e-3 * ((1 - p) * np.maximum(A - 1, 0) + p * (A[-1] - A)) + p * n * 3.9e-11
+
+    def first(x):
+        h = np.nonzero(A + x * err >= p * A[-1])[0]
+        return int(h[0]) if len(h) else 4096
+
+    for share, most in ((1.0, 64), (0.25, 1024), (0.0625, 1024), (0.0, n)):
+        lo, hi = min(first(share), last), first(-share)
+        if share == 0.0:
+            hi = lo
+        if (C[hi + 1] if hi <= last else n) - C[lo] <= most:
+            hi = min(hi, last)
+            break
+    e = np.cumsum(np.bincount(b, weights=np.exp(f.astype(float) - f.max()), minlength=4096))
+    cut = int(np.nonzero(e >= p * e[-1])[0][0])
+    path = []
+    while True:
+        below, over = lo > 0 and e[lo - 1] >= p * e[-1], count[lo:hi + 1].sum() > 1024
+        if lo <= cut <= hi and not over:
+            return path
+        if len(path) < 3 and below:
+            lo, hi = max(0, lo - 2), lo - 1
+            path.append("down")
+        elif len(path) < 3 and over and hi > lo:
+            hi -= 1
+            path.append("shrink")
+        elif len(path) < 3 and not over and hi < last:
+            lo, hi = hi + 1, min(hi + 2, last)
+            path.append("up")
+        else:
+            return path + ["group"]
+
+
+# (direction, top_p, logits a bucket, weight of one, share of the 60 buckets in front
+# of the cut) and the moves of the window
+MISSED = [
+    ((-1, 0.9, 100, 5e-6, 0.3), ["down"]),
+    ((1, 0.9, 100, 5e-6, 0.3), ["up"]),
+    ((1, 0.9, 520, 2e-6, 0.2), ["up", "shrink"]),
+    ((-1, 0.9, 520, 2e-6, 0.2), ["down", "shrink", "up", "group"]),
+    ((-1, 0.5, 1, 2e-5, 0.3), ["down", "down", "down", "group"]),
+    ((1, 0.5, 1, 2e-5, 0.3), ["up", "up", "up", "group"]),
+    ((-1, 0.5, 350, 4e-7, 0.2), ["group"]),
+]
+
+
+@pytest.mark.parametrize("split", [True, False], ids=["split", "one_block"])
+@pytest.mark.parametrize("row,path", MISSED, ids=["-".join(p) for _, p in MISSED])
+def test_sampling_rows_whose_window_misses(row, path, split):
+    """A window that misses the cut, or whose neighbours overflow the list, moves until
+    it is found; rows of the same logits sample with other random numbers."""
+    import oracle
+    from test_gpu_sampling import _exempt
+
+    M, n, p = 128, 65536, row[1]
+    f0 = _off_middle(*row)
+    assert _windows(f0, p) == path
+    # the logits as three bf16 numbers each: every sum of them is exact
+    rest, parts = torch.from_numpy(f0).cuda(), []
+    for _ in range(3):
+        parts.append(rest.to(torch.bfloat16))
+        rest = rest - parts[-1].float()
+    w = torch.zeros((n, 8), device="cuda", dtype=torch.bfloat16)
+    w[:, :3] = torch.stack(parts, 1)
+    h = torch.ones((M, 8), device="cuda", dtype=torch.bfloat16)
+    sub = sph.Subset(vocab=n, full=True)
+    full, base = sph.fuse_verify_workspace(M, sub, sph.SAMPLE), M * 16384 + M * n * 4
+    assert full > base and base % 256 == 0
+    ws = torch.empty((full if split else base,), dtype=torch.uint8, device="cuda")
+    q, s = torch.zeros((M, n), dtype=torch.int8, device="cuda"), torch.ones((M,), device="cuda")
+    tok, _, f = sph.fuse_verify(q, s, h, w, sub, M, 1, None, mode=sph.SAMPLE, temperature=1.0, top_p=p, seed=5,
+                                want_fused=True, workspace=ws)
+    assert torch.equal(f, torch.from_numpy(f0).cuda().expand(M, -1))
+    ref, info = oracle.sample_select(np.broadcast_to(f0, (M, n)), np.arange(n, dtype=np.int32), 1.0, np.float32(p), 5, 1,
+                                     row_index=np.arange(M))
+    bad = (tok.cpu().numpy() != ref) & ~_exempt(info)
+    assert not bad.any(), (tok, ref)
+    assert (~_exempt(info)).sum() > M // 2  # (a tenth of them logits near the cut)
+    sub.close()
+
+
 # (sessions, R, d_cloud, n): partial K steps and ragged edges, first of the row
 # groups of the streaming kernel (193 to 1024 rows over few positions), then of
 # the 256- and 320-row tiles
