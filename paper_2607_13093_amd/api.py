@@ -22,11 +22,15 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
+# the stream's handle alone, where torch gives it: a Stream object costs 2 us, and a
+# decode call is 10
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_handle(device: torch.device) -> int:
-    # the handle alone: a Stream object costs 2 us, and a decode call is 10
-    if device.index is None:
+    if device.index is None or _raw_stream is None:
         return torch.cuda.current_stream(device).cuda_stream
-    return torch._C._cuda_getCurrentRawStream(device.index)
+    return _raw_stream(device.index)
 
 
 def _require_gpu(name: str, t: torch.Tensor) -> None:

@@ -395,7 +395,6 @@ void k_fuse_dma(const MfmaArgs a) {
 #endif
 }
 
-
 template <int BM, int BN, int WNN, int WMM, int BPC>
 static hipError_t launch_fuse_tile(MfmaArgs a, hipStream_t s) {
   static std::atomic<uint64_t> lds_set[4];
@@ -437,7 +436,11 @@ int fuse_n_tiles(int M, int n, int K) { return fuse_small_tiles(M, n, K) ? (n + 
 hipError_t launch_fuse_mfma(const MfmaArgs& a, hipStream_t s) {
   if (fuse_small_tiles(a.M, a.n, a.K))
     return a.M <= 32 ? launch_fuse_tile<32, 128, 4, 1, 3>(a, s) : launch_fuse_tile<64, 128, 4, 1, 3>(a, s);
-  if (a.M <= 128) return launch_fuse_tile<64, 256, 4, 1, 2>(a, s);  // more than 262144 positions
+  // More than 262144 positions, for which the small tiles have no slots.  (us, 64 x
+  // 256 / 256 x 256 tiles: 10 rows x 262145 positions x 256 columns 40 / 65, 60 x
+  // 300001 x 96 37 / 64, 64 x 400000 x 512 101 / 150, 100 x 262145 x 96 55 / 63;
+  // about even past 64 rows with long K: 128 x 300001 x 512 130 / 120.)
+  if (a.M <= 128) return launch_fuse_tile<64, 256, 4, 1, 2>(a, s);
   return fuse_bm_large(a.M) == 320 ? launch_fuse_tile<320, 256, 4, 2, 1>(a, s)
                                    : launch_fuse_tile<256, 256, 2, 4, 1>(a, s);
 }

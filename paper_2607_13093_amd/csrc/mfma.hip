@@ -31,7 +31,6 @@
 
 namespace sph {
 
-
 // Descriptor of `rows` rows of z from the tile's first one (at most 320 rows of
 // 2^19 positions, below 2^30 bytes), an offset past any tile's, and the
 // non-temporal store of one value.
@@ -225,8 +224,7 @@ __device__ __forceinline__ void tile_epilogue(f32x16_t (&acc)[FM][FN], const Mfm
 
 // Tiles of bf16 weights, K a multiple of 8 (TAIL: no multiple of the K step;
 // the missing chunks of the last step read its first chunk and are cleared in
-// LDS).  gfx950's
-// global_load_lds_dwordx4 writes a wave's 64 x 16 bytes straight into LDS
+// LDS).  gfx950's global_load_lds_dwordx4 writes a wave's 64 x 16 bytes straight into LDS
 // (lane l at base + 16*l), so tiles never pass through registers and no
 // ds_write is issued.  A wave instruction fills 8 rows x 128 bytes; rows are
 // unpadded and their 16-byte chunks are XOR-swizzled with
@@ -399,7 +397,6 @@ __device__ __forceinline__ void w1_wait_lds() { asm volatile("s_waitcnt lgkmcnt(
 __device__ __forceinline__ void w1_wait_lds8() { asm volatile("s_waitcnt lgkmcnt(8)" ::: "memory"); }
 __device__ __forceinline__ void w1_wait_mem() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 typedef __attribute__((address_space(3))) const char* lds_cptr_t;
-
 
 // NB weight stages: 2 (an even number of K steps; 128 KB of LDS), or 3 (a
 // multiple of 6 steps; all 160 KB of LDS, and the ids and row maxima live
@@ -957,9 +954,9 @@ static hipError_t launch_bm(const MfmaArgs& a, hipStream_t s) {
 
 // Cloud projection with the block quantiser in the epilogue, for the row
 // tile whose accumulators and row maxima fit in the registers together
-// (256 rows).  Where the tile rule picks
-// 320 rows the separate quantiser is used: on 640 rows, 256-row tiles with
-// the fused quantiser ran 598 us against 428 + 43 us.
+// (256 rows).  Where the tile rule picks 320 rows the separate quantiser is
+// used: on 640 rows, 256-row tiles with the fused quantiser ran 598 us against
+// 428 + 43 us.
 // With a partial last K step only where there are four rounds of tiles or more
 // (a tile's quantising epilogue keeps its CU some 30 us, the separate one
 // shares out evenly), and for E4M3 weights, whose steps hide less of it, only

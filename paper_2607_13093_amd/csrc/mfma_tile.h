@@ -52,16 +52,11 @@ __device__ __forceinline__ void tile_of_block(int b, int m_tiles, int n_tiles, i
   nt = in / gm;
 }
 
-
 // Lane exchanges of the butterfly below, all VALU except the 4-lane step:
 // v_permlane16_swap exchanges the upper 16 lanes of each 32-lane half of one
 // register with the lower 16 of another, so the larger of its two results is,
 // in lanes l & 16 == 0, max(x[l], x[l ^ 16]) and otherwise max(y[l], y[l ^ 16]);
 // DPP row_ror:8 and quad permutations read lane l ^ 8, l ^ 2 and l ^ 1.
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);
-}
 template <int O>
 __device__ __forceinline__ uint32_t lane_xor_u32(uint32_t v) {
   if constexpr (O == 8) return dpp_u32<0x128>(v);       // row_ror:8

@@ -230,10 +230,6 @@ __device__ uint32_t philox_x0(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3
 // v_permlane16_swap (both results summed), then DPP rotations by 8, 4, 2
 // and 1 lanes inside each 16-lane row finish the sum.
 template <int CTRL>
-__device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);
-}
-template <int CTRL>
 __device__ __forceinline__ uint64_t dpp_u64(uint64_t v) {
   return ((uint64_t)dpp_u32<CTRL>((uint32_t)(v >> 32)) << 32) | dpp_u32<CTRL>((uint32_t)v);
 }

@@ -34,6 +34,12 @@ inline void launch_kernel(K kernel, dim3 grid, dim3 block, uint32_t lds, hipStre
   }
 }
 
+// v of the lane that a DPP control names.
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);
+}
+
 // The dynamic-LDS limit of a kernel is raised once per device (a host call,
 // kept out of every launch so that launches can be captured in a graph).
 // `done` is one instantiation's mask of devices already set.
