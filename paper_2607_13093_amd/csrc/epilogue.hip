@@ -23,7 +23,8 @@ __device__ __forceinline__ int quantize_one(float z, float clip, float s, float 
 // straddles a chunk) the chunk's blocks take their maxima from z itself.
 // The division is correctly rounded.  8-bit codes are bytes; 4-bit codes go
 // two per byte, the even position in the low nibble (two's complement).
-template <int BITS>
+// FEW: rows of less than four columns.
+template <int BITS, bool FEW>
 __global__ __launch_bounds__(256) void k_quantize(const float* __restrict__ z, int ldz,
                                                   const float* __restrict__ amax_part, int nblk,
                                                   int n, float clip, int qshift,
@@ -47,15 +48,20 @@ __global__ __launch_bounds__(256) void k_quantize(const float* __restrict__ z, i
 #pragma unroll
   for (int t = 0; t < VT; ++t) {
     const int j = j0 + tid * 4 + 1024 * t;
-    if (j + 4 <= j1) {  // one load at any alignment
-      __builtin_memcpy(&v[t], z + zrow + j, 16);
+    if constexpr (!FEW) {
+      v[t] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (j + 4 <= n) __builtin_memcpy(&v[t], z + zrow + j, 16);  // one load at any alignment
     } else {
-      v[t].x = j < j1 ? z[zrow + j] : 0.f;
-      v[t].y = j + 1 < j1 ? z[zrow + j + 1] : 0.f;
-      v[t].z = j + 2 < j1 ? z[zrow + j + 2] : 0.f;
-      v[t].w = j + 3 < j1 ? z[zrow + j + 3] : 0.f;
+      v[t] = make_float4(j < n ? z[zrow + j] : 0.f, j + 1 < n ? z[zrow + j + 1] : 0.f,
+                         j + 2 < n ? z[zrow + j + 2] : 0.f, 0.f);
     }
   }
+  // the row's last columns where n is no multiple of four: loaded by every thread,
+  // put in place below (a branch with loads of its own for the one thread that has
+  // them cost 0.5 us of a call over 300 or 1500 positions)
+  const int left = !FEW && j1 == n ? n & 3 : 0;
+  float4 last = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (left > 0) __builtin_memcpy(&last, z + zrow + n - 4, 16);
   float srow = 0.0f;
   if (per_row) {
     // all of a thread's partial maxima are loaded at once (no load waits on
@@ -79,6 +85,15 @@ __global__ __launch_bounds__(256) void k_quantize(const float* __restrict__ z, i
     if (blockIdx.y == 0 && tid == 0) scale[(int64_t)m * qnb] = srow;
   } else if (tid < kQuantChunk / 256) {
     s_bmax[tid] = 0u;
+  }
+
+  if (left > 0) {
+    const float4 e = left == 1   ? make_float4(last.w, 0.f, 0.f, 0.f)
+                     : left == 2 ? make_float4(last.z, last.w, 0.f, 0.f)
+                                 : make_float4(last.y, last.z, last.w, 0.f);
+#pragma unroll
+    for (int t = 0; t < VT; ++t)
+      if (j0 + tid * 4 + 1024 * t == n - left) v[t] = e;
   }
 
   auto absclip = [&](float x) { return fabsf(fminf(fmaxf(x, -clip), clip)); };
@@ -138,12 +153,10 @@ hipError_t launch_quantize(const float* z, int ldz, const float* amax_part, int 
   const int chunks = (n + kQuantChunk - 1) / kQuantChunk;
   if (chunks > 65535 || (bits != 8 && bits != 4)) return hipErrorInvalidValue;
   if (qshift >= 0 && (qshift < 8 || (1 << qshift) > kQuantChunk)) return hipErrorInvalidValue;
-  if (bits == 8)
-    launch_kernel(k_quantize<8>, dim3(M, chunks), dim3(256), 0, s, z, ldz, amax_part, nblk, n,
-                  clip, qshift, q, qstride, scale, qnb);
-  else
-    launch_kernel(k_quantize<4>, dim3(M, chunks), dim3(256), 0, s, z, ldz, amax_part, nblk, n,
-                  clip, qshift, q, qstride, scale, qnb);
+  auto k = n < 4 ? (bits == 8 ? k_quantize<8, true> : k_quantize<4, true>)
+                 : (bits == 8 ? k_quantize<8, false> : k_quantize<4, false>);
+  launch_kernel(k, dim3(M, chunks), dim3(256), 0, s, z, ldz, amax_part, nblk, n, clip, qshift, q,
+                qstride, scale, qnb);
   return hipGetLastError();
 }
 

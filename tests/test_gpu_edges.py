@@ -400,18 +400,57 @@ def test_codes_of_the_quantising_epilogue_are_those_of_its_logits(bits):
     sub.close()
 
 
-def _cloud_us(M, n, K, block):
+@pytest.mark.parametrize("bits,block", [(8, 0), (4, 0), (8, 256), (4, 1024)])
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 6, 7, 8, 255, 1022, 4093, 4094, 4095, 4096, 4097, 4098, 4099, 8193, 12287])
+def test_quantiser_at_the_ends_of_rows(n, bits, block):
+    """Rows whose last four columns straddle a chunk of the quantiser or are fewer,
+    from partial logits n apart (any alignment) and whole lines apart: the codes
+    and scales are those of the logits."""
+    M, K = 5, 64
+    g = torch.Generator(device="cuda").manual_seed(n)
+    h = torch.randn((M, K), device="cuda", generator=g).to(torch.bfloat16)
+    w = torch.randn((n, K), device="cuda", generator=g).to(torch.bfloat16)
+    sub = sph.Subset(vocab=n, full=True)
+    q, s, z = sph.cloud_partial(h, w, sub, 12.0, want_z=True, bits=bits, block=block)
+    q2, s2, _ = sph.cloud_partial(h, w, sub, 12.0, bits=bits, block=block)
+    sub.close()
+    qmax = 127.0 if bits == 8 else 7.0
+    y, wide = z.clamp(-12.0, 12.0), block or n
+    a = torch.nn.functional.pad(y.abs(), (0, -n % wide)).view(M, -1, wide).amax(2)
+    sc = (a.double() / qmax).float()
+    code = (y.double() / sc.repeat_interleave(wide, 1)[:, :n].double()).float().round().to(torch.int8)
+    if bits == 4:
+        code = torch.nn.functional.pad(code, (0, n & 1)).to(torch.uint8) & 15
+        code = code[:, 0::2] | (code[:, 1::2] << 4)
+    assert torch.equal(sc.view(s.shape), s) and torch.equal(code, q)
+    assert torch.equal(s, s2) and torch.equal(q, q2)
+
+
+def test_a_partial_chunk_costs_what_its_columns_do():
+    """Rows of 1500 columns take the quantiser 0.52 to 0.55 of the time of 4096 (with
+    loads in branches for the ends of rows 0.62 to 0.64)."""
+    ratio = []
+    for _ in range(3):
+        us = []
+        for n in (1500, 4096):
+            us.append(_cloud_us(2048, n, 64, 0, "cloud_quantize")[0])
+        ratio.append(us[0] / us[1])
+    print(f"1500 columns against 4096: {ratio}", flush=True)
+    assert min(ratio) < 0.6
+
+
+def _cloud_us(M, n, K, block, only=None):
     g = torch.Generator(device="cuda").manual_seed(K)
     h = torch.randn((M, K), device="cuda", generator=g).to(torch.bfloat16)
     w = torch.randn((n, K), device="cuda", generator=g).to(torch.bfloat16)
     sub = sph.Subset(vocab=n, full=True)
     sph.trace_start(400)
-    for _ in range(20):
+    for _ in range(60):
         sph.cloud_partial(h, w, sub, 30.0, block=block)
     torch.cuda.synchronize()
     t = sph.trace_collect(400)
     sub.close()
-    names = sorted({k for k, _ in t})
+    names = sorted({k for k, _ in t if k == (only or k)})
     return sum(min(ms for k, ms in t if k == name) for name in names) * 1e3, names
 
 
