@@ -173,7 +173,8 @@ constexpr int kFinalWaves = 16;  // rows of a session reduced in parallel
 // per-block argmax keys (every lane loads its share of up to kMaxBlocks keys
 // at once) into the greedy token, ties to the lowest subset position = the
 // lowest id; then count the drafts that match the verification rows in
-// order (Section 5.5, Algorithm 1 verification step).
+// order (Section 5.5, Algorithm 1 verification step).  WPR > 1: every row has
+// its waves at once (R * WPR <= kFinalWaves).
 template <int WPR>
 __global__ __launch_bounds__(64 * kFinalWaves) void k_final_greedy(
     const unsigned long long* __restrict__ best, int nblk, const int32_t* __restrict__ ids, int n,
@@ -182,14 +183,20 @@ __global__ __launch_bounds__(64 * kFinalWaves) void k_final_greedy(
   constexpr int PER_LANE = kMaxBlocks / 64 / WPR, RP = kFinalWaves / WPR;
   const int s = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  __shared__ unsigned long long s_key[kMaxRowsPerSession];
+  __shared__ unsigned long long s_key[kFinalWaves];
   __shared__ int32_t s_tok[kMaxRowsPerSession];
   __shared__ int32_t s_draft[kMaxRowsPerSession];
   // the session's drafts are staged while the keys are read, so the prefix
   // match below reads LDS only
   for (int r = tid; r < R - 1; r += blockDim.x) s_draft[r] = drafts[(int64_t)s * (R - 1) + r];
-  for (int r = tid; r < R; r += blockDim.x) s_key[r] = 0ull;
-  __syncthreads();
+  auto token = [&](int r, unsigned long long k) {
+    // every position of the row produced a key, so pos < n; the clamp only
+    // keeps a corrupted key from reading outside the id table
+    const uint32_t pos = min(0xFFFFFFFFu - (uint32_t)k, (uint32_t)(n - 1));
+    const int32_t tok = ids[pos];
+    tokens[(int64_t)s * R + r] = tok;
+    s_tok[r] = tok;
+  };
   for (int r = wave / WPR; r < R; r += RP) {
     const int64_t m = (int64_t)s * R + r;
     unsigned long long x[PER_LANE];
@@ -206,16 +213,19 @@ __global__ __launch_bounds__(64 * kFinalWaves) void k_final_greedy(
       const unsigned long long y = shfl_xor_u64(k, o);
       k = y > k ? y : k;
     }
-    if (lane == 0) atomicMax(&s_key[r], k);
+    if (lane == 0) {
+      if constexpr (WPR == 1) token(r, k);
+      else s_key[wave] = k;
+    }
   }
-  __syncthreads();
-  for (int r = tid; r < R; r += blockDim.x) {
-    // every position of the row produced a key, so pos < n; the clamp only
-    // keeps a corrupted key from reading outside the id table
-    const uint32_t pos = min(0xFFFFFFFFu - (uint32_t)s_key[r], (uint32_t)(n - 1));
-    const int32_t tok = ids[pos];
-    tokens[(int64_t)s * R + r] = tok;
-    s_tok[r] = tok;
+  if constexpr (WPR > 1) {
+    __syncthreads();
+    if (tid < R) {
+      unsigned long long k = s_key[tid * WPR];
+#pragma unroll
+      for (int w = 1; w < WPR; ++w) k = s_key[tid * WPR + w] > k ? s_key[tid * WPR + w] : k;
+      token(tid, k);
+    }
   }
   __syncthreads();
   if (tid == 0) {
@@ -230,8 +240,12 @@ hipError_t launch_final_greedy(const uint64_t* best_part, int nblk, const int32_
                                int n_sessions, int R, const int32_t* drafts, int32_t* tokens,
                                int32_t* accept, hipStream_t s) {
   if (R > kMaxRowsPerSession || n < 1 || nblk > kMaxBlocks) return hipErrorInvalidValue;
-  // rows of few-row sessions take several waves each
-  const int wpr = R <= kFinalWaves / 4 ? 4 : R <= kFinalWaves / 2 ? 2 : 1;
+  // Rows of few-row sessions take several waves each where a row has more keys than
+  // a wave has lanes.  (us of a call, one wave / this rule: 5 rows x 49152 positions x
+  // 256 columns 12.4 / 11.0, 3 x 30000 x 96 8.4 / 7.2, 155 x 30000 x 512 16.5 / 15.7;
+  // several waves also for few keys: 2048 rows x 2001 x 256 10.1 / 10.4, 8 x 300 x 256
+  // 5.97 / 6.13.)
+  const int wpr = nblk <= 64 ? 1 : R <= kFinalWaves / 4 ? 4 : R <= kFinalWaves / 2 ? 2 : 1;
   const int waves = R * wpr < kFinalWaves ? R * wpr : kFinalWaves;
   auto kern = wpr == 4 ? k_final_greedy<4> : wpr == 2 ? k_final_greedy<2> : k_final_greedy<1>;
   launch_kernel(kern, dim3(n_sessions), dim3(64 * waves), 0, s,

@@ -631,6 +631,33 @@ def test_few_rows_without_endpoint_columns(M, bits):
     sub.close()
 
 
+@pytest.mark.parametrize("n", [300, 4096, 70001])
+@pytest.mark.parametrize("R", [1, 2, 4, 5, 8, 9, 16, 17, 40])
+def test_final_selection_at_its_rows_per_session(R, n):
+    """One, two and four waves a row, few keys and many: the largest of every row,
+    the lowest of its ties, and the drafts up to the first that differs."""
+    S = 3
+    M = S * R
+    g = torch.Generator(device="cuda").manual_seed(R + n)
+    q = torch.randint(-100, 100, (M, n), device="cuda", generator=g).to(torch.int8)
+    best = torch.randint(0, n, (M,), device="cuda", generator=g)
+    tie = torch.randint(0, n, (M,), device="cuda", generator=g)
+    q[torch.arange(M), best] = 127
+    q[torch.arange(M), tie] = 127
+    want = torch.minimum(best, tie).to(torch.int32)
+    drafts = want.view(S, R)[:, :R - 1].clone()
+    match = [R - 1, 0, max(0, R - 2)]
+    for i, k in enumerate(match):
+        if k < R - 1:
+            drafts[i, k] = (drafts[i, k] + 1) % n
+    sub = sph.Subset(vocab=n, full=True)
+    tok, acc, _ = sph.fuse_verify(q, torch.full((M,), 0.01, device="cuda"), None, None, sub, S, R,
+                                  drafts if R > 1 else None)
+    sub.close()
+    assert torch.equal(tok, want)
+    assert acc.tolist() == [min(k, R - 1) for k in match]
+
+
 @pytest.mark.parametrize("wtype", ["bf16", "fp8"])
 @pytest.mark.parametrize("M", [2, 20])
 def test_no_cloud_columns(M, wtype):
