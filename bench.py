@@ -42,7 +42,7 @@ OTHER_WORKLOADS = ("dense_sub", "batched", "sample_fp8", "decode", "tiny")
 # the kernel source files each traced kernel is built from (for the counter
 # summaries' source digests)
 KERNEL_SOURCES = {"cloud_gemv": ("gemv.hip", "sph_internal.h"),
-                  "cloud_mfma": ("mfma.hip", "mfma_tile.h", "sph_internal.h")}
+                  "cloud_mfma": ("mfma.hip", "stream.hip", "mfma_tile.h", "sph_internal.h")}
 
 
 def parse():
