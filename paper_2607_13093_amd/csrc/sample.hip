@@ -308,6 +308,12 @@ __device__ __forceinline__ uint64_t readlane_u64(uint64_t v, int lane) {
          (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
 }
 
+constexpr int kLevels = 4;  // windows a block considers (level_window)
+struct Window {
+  int32_t lo, hi;
+  uint32_t elements;
+};
+
 struct SampleShared {
   union {
     uint32_t hf[kBuckets + 64];  // element counts of the buckets, 64 per-lane spill slots
@@ -336,9 +342,10 @@ struct SampleShared {
   uint64_t kred[kSWaves];
   uint32_t ured[kSWaves];
   uint32_t off[64];
+  Window win[kLevels];
   U128 above, claim_base;
   uint32_t tie_base, T;
-  int32_t bsel, lo, hi, ncand, cut_idx, cut_pos, claim_seg, tie_seg;
+  int32_t bsel, ncand, cut_idx, cut_pos, claim_seg, tie_seg;
 };
 
 __device__ unsigned long long block_max_u64(unsigned long long v, SampleShared& sh) {
@@ -488,11 +495,11 @@ __device__ __forceinline__ float bucket_weight(int b) { return __expf(-kBucketSt
 // each weighs below kLastWeight.
 constexpr double kMassErr = 2.96e-3, kLastWeight = 3.9e-11;
 
-// The window [lo, hi], found by a wave: lane g has the estimated mass and the
-// element count of group g (64 buckets), bucket(b) gives a bucket's count.
-// With A the estimated mass up to some bucket and Z that of all, A - p Z =
-// (1 - p) A - p (Z - A) decides whether the cut lies past it, and is off by at
-// most
+// The window [lo, hi], found by four waves, one for each share f of the error:
+// lane g has the estimated mass and the element count of group g (64 buckets),
+// bucket(b) gives a bucket's count.  With A the estimated mass up to some bucket and
+// Z that of all, A - p Z = (1 - p) A - p (Z - A) decides whether the cut lies past
+// it, and is off by at most
 //   err(A) = kMassErr ((1 - p) (A - 1) + p (Z - A)) + p n kLastWeight,
 // as the row's maximum weighs 1 exactly and is counted so.  [lo, hi] is what
 // lies within err, so it holds the cut.  With more than kSureCand elements
@@ -506,9 +513,10 @@ constexpr double kMassErr = 2.96e-3, kLastWeight = 3.9e-11;
 // id of 0.8 of the mass and a normal tail, top_p 0.8, 228 / 103; sigma / tau 4,
 // top_p 0.9, 181 / 94; 64 x 65536 of it 112 / 36; 128 x 150000 339 / 71.)
 constexpr uint32_t kSureCand = 64;
+
+// The window of one share (level 0 ... 3: f = 1, 1/4, 1/16, 0) of the error, by a wave.
 template <class B>
-__device__ __forceinline__ void pick_window(double p, int n, uint32_t cap, double mass, uint32_t count,
-                                            B&& bucket, int& lo, int& hi) {
+__device__ __forceinline__ Window level_window(double p, int n, int level, double mass, uint32_t count, B&& bucket) {
   const int lane = threadIdx.x & 63;
   auto of_lane = [](double v, int l) {
     return __longlong_as_double((long long)readlane_u64((uint64_t)__double_as_longlong(v), l));
@@ -546,19 +554,28 @@ __device__ __forceinline__ void pick_window(double p, int n, uint32_t cap, doubl
     upto = (uint32_t)__builtin_amdgcn_readlane((int)ck, l);
     return 64 * g + l;
   };
-  double f = 1.0;
-  for (int level = 0;; ++level, f *= 0.25) {
-    uint32_t b0, b1, other;
-    if (level == 3) f = 0.0;
-    lo = min(first(f, b0, other), kBuckets - 1);
-    if (level == 3) break;
-    hi = first(-f, other, b1);
-    if (b1 - b0 <= (level == 0 ? kSureCand : cap)) {
-      hi = min(hi, kBuckets - 1);
-      return;
-    }
+  const double f = level == 0 ? 1.0 : level == 1 ? 0.25 : level == 2 ? 0.0625 : 0.0;
+  uint32_t b0, b1, other;
+  Window w;
+  w.lo = min(first(f, b0, other), kBuckets - 1);
+  w.hi = w.lo;
+  w.elements = 0u;  // (the estimate's bucket alone: whatever it holds)
+  if (level < kLevels - 1) {
+    w.hi = first(-f, other, b1);
+    w.elements = b1 - b0;
+    w.hi = min(w.hi, kBuckets - 1);
   }
-  hi = lo;
+  return w;
+}
+
+// The first level with few enough elements.
+__device__ __forceinline__ void pick_window(const Window (&w)[kLevels], uint32_t cap, int& lo, int& hi) {
+  int k = kLevels - 1;
+#pragma unroll
+  for (int i = kLevels - 2; i >= 0; --i)
+    if (w[i].elements <= (i == 0 ? kSureCand : cap)) k = i;
+  lo = w[k].lo;
+  hi = w[k].hi;
 }
 
 template <int NT>
@@ -634,7 +651,7 @@ __global__ __launch_bounds__(kMassThreads) void k_sample_mass(const float* __res
   __shared__ double tab[kTab];
   __shared__ uint64_t red[NWV];
   __shared__ uint64_t sums[NWV][4];
-  __shared__ int32_t s_win[2];
+  __shared__ Window s_win[kLevels];
   __shared__ uint32_t s_cnt;
   const int m = blockIdx.y, part = blockIdx.x, t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -645,7 +662,8 @@ __global__ __launch_bounds__(kMassThreads) void k_sample_mass(const float* __res
   tab[t] = exp2((double)t * (1.0 / kTab));
   if (t == 0) s_cnt = 0u;
   int lo = kBuckets, hi = kBuckets - 1;  // top_p 1: every bucket below lo, no window
-  if (top_p < 1.0f && wave == 0) {
+  static_assert(NWV == kLevels, "a wave per level");
+  if (top_p < 1.0f) {
     // (the parts' values are all loaded before the first is used)
     uint2 cg[kCountParts];
 #pragma unroll
@@ -666,20 +684,16 @@ __global__ __launch_bounds__(kMassThreads) void k_sample_mass(const float* __res
       for (int i = 0; i < kCountParts; ++i) k += i < sc.p1 ? c[i] : 0u;
       return k;
     };
-    // (parts have room for twice their share)
-    pick_window((double)top_p, n, (uint32_t)min(kMaxCand, kPartCand / 2 * sc.p2), mass, count, bucket, lo, hi);
+    const Window w = level_window((double)top_p, n, wave, mass, count, bucket);
+    if (lane == 0) s_win[wave] = w;
   }
-  if (wave == 0 && lane == 0) {
-    s_win[0] = lo;
-    s_win[1] = hi;
-    if (part == 0) {
-      sc.win[2 * m] = lo;
-      sc.win[2 * m + 1] = hi;
-    }
+  const float vmax = row_max<kMassThreads>(best + (int64_t)m * kMaxBlocks, nblk, red);  // and the table, the levels
+  // (parts have room for twice their share)
+  if (top_p < 1.0f) pick_window(s_win, (uint32_t)min(kMaxCand, kPartCand / 2 * sc.p2), lo, hi);
+  if (part == 0 && t == 0) {
+    sc.win[2 * m] = lo;
+    sc.win[2 * m + 1] = hi;
   }
-  const float vmax = row_max<kMassThreads>(best + (int64_t)m * kMaxBlocks, nblk, red);  // and the table
-  lo = s_win[0];
-  hi = s_win[1];
   const double kk = (double)kTab / (kLn2 * (double)temperature);
   const double c0 = -(double)vmax * kk;
   const float kb = (float)kBuckets / (kYSpan * temperature);
@@ -932,17 +946,13 @@ __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(6))) 
       sh.gcnt[t >> 3] = k;
     }
     __syncthreads();
-    if (wave == 0) {
-      pick_window((double)top_p, n, (uint32_t)kMaxCand, (double)sh.gmass[lane], sh.gcnt[lane],
-                  [&](int b) { return sh.u.hf[b]; }, lo, hi);
-      if (lane == 0) {
-        sh.lo = lo;
-        sh.hi = hi;
-      }
+    if (wave < kLevels) {
+      const Window w = level_window((double)top_p, n, __builtin_amdgcn_readfirstlane(wave), (double)sh.gmass[lane],
+                                    sh.gcnt[lane], [&](int b) { return sh.u.hf[b]; });
+      if (lane == 0) sh.win[wave] = w;
     }
     __syncthreads();  // (and the list may take the histogram's place)
-    lo = sh.lo;
-    hi = sh.hi;
+    pick_window(sh.win, (uint32_t)kMaxCand, lo, hi);
   }
 
   // 2. exact pass: Z, segment masses below the window, the window's list; then
