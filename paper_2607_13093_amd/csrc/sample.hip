@@ -1379,9 +1379,9 @@ __global__ void k_accept(const int32_t* __restrict__ tokens, const int32_t* __re
 
 // Whether the passes are spread over several blocks: two more launches, for
 // rows that keep one block busy longer than that.  Measured (one block / spread,
-// tau 0.7, top_p 0.9): 5 rows x 16384 22.0 / 27.5 us, x 32768 31.8 / 28.6,
-// x 65536 51.8 / 32.2; 64 rows x 32768 32.4 / 32.0; 128 rows x 32768 33.5 /
-// 38.3, x 65536 56.0 / 51.8, x 150000 119 / 80.
+// tau 0.7, top_p 0.9): 5 rows x 16384 22.0 / 27.5 us, x 32768 32.6 / 27.2,
+// x 65536 55.1 / 28.8; 64 rows x 32768 32.6 / 31.0; 128 rows x 32768 33.5 /
+// 38.3, x 65536 55.5 / 52.0, x 150000 119 / 77.
 static bool split_rows(int64_t M, int64_t n) {
   return M > 0 && M <= 128 && n >= std::max<int64_t>(32768, 512 * M) && n <= 0x7FFFFFFF;
 }
